@@ -233,6 +233,8 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
   A((void**)&c->att_ml, (size_t)d.n_heads * c->max_splits * c->Bpad * 2 * sizeof(float));
   A((void**)&c->logits, (size_t)c->Bpad * c->Vpad * sizeof(float));
   A(&c->top2, (size_t)c->Bpad * (c->Vpad / 64 + 1) * 16);
+  // (goose_harvest_topk takes up to GOOSE_MAX_B rows whatever the context's max_B)
+  A(&c->harvest, goose_harvest_ws_bytes(d.vocab, c->Bpad > GOOSE_MAX_B ? c->Bpad : GOOSE_MAX_B));
   A((void**)&c->inv_freq, (size_t)(d.head_dim / 2) * sizeof(double));
   A(&c->rope_cs, (size_t)c->Bpad * (d.head_dim / 2) * 2 * sizeof(float));
   A((void**)&c->s_mask, (size_t)c->Bpad * 2 * sizeof(uint64_t));
@@ -259,7 +261,7 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
 
 void goose_destroy(goose_ctx* c) {
   if (!c) return;
-  void* ptrs[] = {c->xn, c->part, c->q, c->o, c->h, c->att_o, c->att_ml, c->logits, c->top2, c->inv_freq, c->rope_cs,
+  void* ptrs[] = {c->xn, c->part, c->q, c->o, c->h, c->att_o, c->att_ml, c->logits, c->top2, c->harvest, c->inv_freq, c->rope_cs,
                   c->s_mask, c->s_depth, c->s_pos, c->s_x, c->flags, c->s_P};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -460,12 +462,9 @@ int goose_verify_layer(goose_ctx* c, const void* d_packed_layer, float* d_x, voi
                     nullptr);
 }
 
-struct HarvestArgs {  // optional harvest of the logits into the successor tables
-  const int32_t* tokens = nullptr;
-  int K = 0;
-  int32_t* ids = nullptr;
-  float* scores = nullptr;
-  bool keep_logits = false;  // write the logits to the workspace even though nothing is harvested here
+struct HarvestArgs {  // optional harvest of the logits into the requests' successor tables
+  HarvestReq req[GOOSE_MAX_REQUESTS];
+  int n = 0;
 };
 static int lm_head_impl(goose_ctx* c, const void* d_packed_head, const float* d_x, int B, int32_t* d_argmax,
                         float* d_logits_or_null, float* d_margin_or_null, hipStream_t st, bool xhat_ready,
@@ -497,7 +496,7 @@ static int lm_head_impl(goose_ctx* c, const void* d_packed_head, const float* d_
     static const int lm_nw = env_int("GOOSE_LM_NW", 4) == 2 ? 2 : 4;
     // (the harvest needs them too: into the workspace then)
     const bool bounce = d_logits_or_null && (d.vocab % 32) != 0;
-    float* out = (bounce || (!d_logits_or_null && (hv.ids || hv.keep_logits))) ? c->logits : d_logits_or_null;
+    float* out = (bounce || (!d_logits_or_null && hv.n > 0)) ? c->logits : d_logits_or_null;
     const size_t ld = out == c->logits ? (size_t)c->Vpad : (size_t)d.vocab;
     const int groups = (c->Vpad / 32 + lm_nw - 1) / lm_nw;
     { PROF(PK_LM_HEAD);
@@ -509,17 +508,17 @@ static int lm_head_impl(goose_ctx* c, const void* d_packed_head, const float* d_
                                      (size_t)d.vocab * 4, B, hipMemcpyDeviceToDevice, st));
     { PROF(PK_ARGMAX);
       rc = launch_argmax_top2(c->top2, groups, B, d_argmax, d_margin_or_null, st); }
-    if (rc || !hv.ids) return rc;
+    if (rc || hv.n == 0) return rc;
     PROF(PK_HARVEST);
-    return launch_harvest_topk(out, ld, d.vocab, hv.tokens, B, hv.K, d.vocab, hv.ids, hv.scores, st);
+    return launch_harvest_topk(out, ld, d.vocab, hv.req, hv.n, c->harvest, st);
   }
   float* logits = d_logits_or_null ? d_logits_or_null : c->logits;
   const size_t ld = d_logits_or_null ? (size_t)d.vocab : (size_t)c->Vpad;
   rc = launch_gemm_f32((const float*)c->xn, c->Kh, (const float*)(w + c->ph.wlm), d.vocab, d.hidden, B, logits, ld, st);
   if (rc) return rc;
   rc = launch_argmax(logits, ld, d.vocab, B, d_argmax, d_margin_or_null, st);
-  if (rc || !hv.ids) return rc;
-  return launch_harvest_topk(logits, ld, d.vocab, hv.tokens, B, hv.K, d.vocab, hv.ids, hv.scores, st);
+  if (rc || hv.n == 0) return rc;
+  return launch_harvest_topk(logits, ld, d.vocab, hv.req, hv.n, c->harvest, st);
 }
 
 int goose_harvest_topk(goose_ctx* c, const float* d_logits, size_t ld, const int32_t* d_tokens, int B, int K,
@@ -527,8 +526,8 @@ int goose_harvest_topk(goose_ctx* c, const float* d_logits, size_t ld, const int
   if (!c || !d_logits || !d_tokens || !d_succ_ids || !d_succ_scores) return GOOSE_ERR_ARG;
   if (B < 1 || K < 1 || K > 16 || ld < (size_t)c->d.vocab) return GOOSE_ERR_ARG;
   if (B > GOOSE_MAX_B) return GOOSE_ERR_CAPACITY;
-  return launch_harvest_topk(d_logits, ld, c->d.vocab, d_tokens, B, K, c->d.vocab, d_succ_ids, d_succ_scores,
-                             as_stream(stream));
+  const HarvestReq q{d_tokens, d_succ_ids, d_succ_scores, B, 0, K};
+  return launch_harvest_topk(d_logits, ld, c->d.vocab, &q, 1, c->harvest, as_stream(stream));
 }
 
 int goose_accept(goose_ctx* c, const int32_t* d_parent, const int32_t* d_tokens, const uint8_t* d_is_spine_or_null,
@@ -587,10 +586,7 @@ int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_
   HarvestArgs hv;
   if (io->d_succ_ids_or_null) {
     if (!io->d_succ_scores_or_null || io->harvest_k < 1 || io->harvest_k > 16) return GOOSE_ERR_ARG;
-    hv.tokens = io->d_tokens;
-    hv.K = io->harvest_k;
-    hv.ids = io->d_succ_ids_or_null;
-    hv.scores = io->d_succ_scores_or_null;
+    hv.req[hv.n++] = HarvestReq{io->d_tokens, io->d_succ_ids_or_null, io->d_succ_scores_or_null, B, 0, io->harvest_k};
   }
   rc = lm_head_impl(c, m->d_packed_head, c->s_x, B, io->d_argmax, io->d_logits_or_null, io->d_margin_or_null, st,
                     true, hv);
@@ -611,7 +607,6 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
   hipStream_t st = as_stream(stream);
   AttnSeg segs[GOOSE_MAX_REQUESTS];
   int rows = 0;
-  bool any_harvest = false;
   for (int r = 0; r < n_req; ++r) {
     const goose_request& q = reqs[r];
     int rc = check_tree_args(c, q.B, q.P_max);
@@ -621,7 +616,6 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
       return GOOSE_ERR_ARG;
     if ((q.d_succ_ids_or_null == nullptr) != (q.d_succ_scores_or_null == nullptr)) return GOOSE_ERR_ARG;
     if (q.d_succ_ids_or_null && (q.harvest_k < 1 || q.harvest_k > 16)) return GOOSE_ERR_ARG;
-    any_harvest = any_harvest || q.d_succ_ids_or_null != nullptr;
     segs[r] = AttnSeg{rows, q.B, q.P_max, nullptr, nullptr, q.d_P, c->s_mask + (size_t)rows * 2};
     rows += round_up(q.B, 32);
   }
@@ -653,16 +647,13 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
     if (rc) return rc;
   }
   HarvestArgs hv;
-  hv.keep_logits = any_harvest;
+  for (int r = 0; r < n_req; ++r) {  // every request into its own tables, from its rows of the logits
+    const goose_request& q = reqs[r];
+    if (q.d_succ_ids_or_null)
+      hv.req[hv.n++] = HarvestReq{q.d_tokens, q.d_succ_ids_or_null, q.d_succ_scores_or_null, q.B, segs[r].row0, q.harvest_k};
+  }
   rc = lm_head_impl(c, m->d_packed_head, c->s_x, rows, d_argmax_all, nullptr, nullptr, st, true, hv);
   if (rc) return rc;
-  for (int r = 0; r < n_req && any_harvest; ++r) {  // every request into its own tables, from its rows of the logits
-    const goose_request& q = reqs[r];
-    if (!q.d_succ_ids_or_null) continue;
-    rc = launch_harvest_topk(c->logits + (size_t)segs[r].row0 * c->Vpad, (size_t)c->Vpad, d.vocab, q.d_tokens, q.B,
-                             q.harvest_k, d.vocab, q.d_succ_ids_or_null, q.d_succ_scores_or_null, st);
-    if (rc) return rc;
-  }
   return launch_batch_end(br, n_req, d_argmax_all, d.n_layers, c->n_kv, c->cap, d.head_dim, c->flags, st);
 }
 

@@ -71,6 +71,7 @@ struct goose_ctx {
   float* att_o;    // f32 [n_heads][max_splits][Bpad][head_dim]
   float* att_ml;   // f32 [n_heads][max_splits][Bpad][2]
   float* logits;   // f32 [Bpad][Vpad]  (fp32 models; vocabularies that are no multiple of 32)
+  void* harvest;   // per-chunk results of the logit harvest (goose_harvest_ws_bytes)
   void* top2;      // float4 [Bpad][Vpad/64]  per-workgroup reductions of the LM head
   double* inv_freq;  // f64 [head_dim/2]
   void* rope_cs;     // float2 [128][head_dim/2]  (cos, sin) of the current tree's positions
@@ -174,8 +175,20 @@ int launch_gemm_rows_16(int dtype, int epi, const void* A, int lda, int terms, c
 // `out` (f32 [B][ldo]) may be null when only the reduction is wanted.
 int launch_gemm_top2_16(int dtype, const void* A, int lda, int terms, const void* Wp, int Npad, int Kpad, int B, int nw,
                         float* out, size_t ldo, void* top2, int n_valid, float out_scale, hipStream_t st);
-int launch_harvest_topk(const float* logits, size_t ld, int V, const int32_t* tokens, int B, int K, int table_rows,
-                        int32_t* succ_ids, float* succ_scores, hipStream_t st);
+// Logit harvest of up to GOOSE_MAX_REQUESTS requests (goose_harvest_topk's semantics each): request r's nodes are rows
+// [row0, row0 + B) of `logits` (f32, row length ld >= V) and its tables have V rows of K entries.
+// ws: at least goose_harvest_ws_bytes(V, last row + 1) bytes of device memory.
+struct HarvestReq {
+  const int32_t* tokens;
+  int32_t* ids;
+  float* scores;
+  int32_t B, row0, K;
+};
+enum { GOOSE_HARVEST_CHUNK = 8192, GOOSE_HARVEST_KMAX = 16 };
+static inline size_t goose_harvest_ws_bytes(int V, int rows) {  // per (row, chunk): (max, sum) and KMAX (value, id) pairs
+  return (size_t)rows * ((V + GOOSE_HARVEST_CHUNK - 1) / GOOSE_HARVEST_CHUNK) * (GOOSE_HARVEST_KMAX + 1) * 8;
+}
+int launch_harvest_topk(const float* logits, size_t ld, int V, const HarvestReq* reqs, int n, void* ws, hipStream_t st);
 int launch_split_operand(int dtype, const float* src, int rows, int cols, int ld_src, void* dst, int ld_dst,
                          hipStream_t st);
 int launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st);

@@ -313,170 +313,183 @@ __global__ __launch_bounds__(64) void k_argmax_top2(const float4* __restrict__ t
 // [vocab][K] successor tables receives the K most likely next tokens of node m (ids, ordered by
 // decreasing logit, equal logits by increasing id) and their softmax probabilities.  When several
 // nodes carry the same token the highest node index writes (the others skip the store).
-// One workgroup per node, two passes over its row:
-//   1. every thread finds the best (logit, id) pair of its strided share and an online
-//      log-sum-exp; the K-th best of the 256 thread-bests, tau, is a lower bound of the K-th best
-//      of the row (there are K pairs at or above it);
-//   2. the pairs at or above tau -- K of them plus a few -- are appended to a short list in LDS,
-//      from which K rounds of a workgroup-wide maximum pop the winners in order.
-// A row whose list would overflow (many pairs above tau inside one thread's share) takes the
-// plain route instead: every thread keeps its best KMAX pairs in sorted registers.
-__device__ inline bool cand_before(float av, int ai, float bv, int bi) { return av > bv || (av == bv && ai < bi); }
+//
+// What bounds it is reading the logits once, so a row is cut into chunks of 8192 columns and every
+// (row, chunk) is a workgroup of its own, its values in registers (32 per thread, all loads in flight
+// together): 64 rows of 128256 columns are 1024 workgroups.  One workgroup per row, walking it
+// twice, left three quarters of the chip idle and took 113 us where this takes 23 (64 x 128256, 33 MB;
+// k_harvest_merge included), and a batch ran one such launch per request (16 x 121 us, now 75 us in all).
+// k_harvest_part leaves (max, sum of exponentials) and the K best pairs of its chunk;
+// k_harvest_merge combines the chunks of a row.
+//   tau: every group of four threads knows its best pair; the K-th best of these 64 pairs is a lower
+//   bound of the chunk's K-th best.  At most K groups hold pairs at or above it, so the list of such
+//   pairs never exceeds K * 4 * 32 = 2048 entries whatever the data (it usually holds K and a few).
+// NaNs are no candidates and count in no sum.
+//
+// A pair travels as one 64-bit key, larger = earlier: the value's bits made monotonic (-0 counts as +0) over the complement
+// of the id; 0 stands for "no pair".  Ranking the 160 pairs of a row by comparing (float, int) took three quarters of the merge.
+typedef unsigned long long hkey;
+__device__ inline hkey harvest_key(float v, int id) {
+  const unsigned b = __float_as_uint(v + 0.f);
+  return (hkey)(b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u)) << 32 | (unsigned)~id;
+}
+__device__ inline float harvest_value(hkey k) {
+  const unsigned b = (unsigned)(k >> 32);
+  return __uint_as_float(b ^ ((b >> 31) ? 0x80000000u : 0xFFFFFFFFu));
+}
+__device__ inline int harvest_id(hkey k) { return (int)~(unsigned)k; }
+// exp(v - m) for v <= m, also where both are the same infinity
+__device__ inline float exp_below(float v, float m) { return v == m ? 1.f : __expf(v - m); }
 
-// Workgroup-wide best of every thread's (v, i); all 256 threads call it.  s_v/s_i: 4-entry LDS scratch.
-__device__ inline void block_best(float& v, int& i, float* s_v, int* s_i) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float ov = __shfl_xor(v, off, 64);
-    const int oi = __shfl_xor(i, off, 64);
-    if (cand_before(ov, oi, v, i)) { v = ov; i = oi; }
+constexpr int HARVEST_VPT = 32, HARVEST_CHUNK = 256 * HARVEST_VPT, HARVEST_KMAX = 16;
+constexpr int HARVEST_MERGE = 1024;  // pairs a merge round ranks
+static_assert(HARVEST_CHUNK == GOOSE_HARVEST_CHUNK && HARVEST_KMAX == GOOSE_HARVEST_KMAX, "the workspace is sized for these");
+
+struct HarvestTable { HarvestReq r[GOOSE_MAX_REQUESTS]; };
+
+// `n` pairs in LDS -> out(0 ..), the best `keep` of them in order.  All 256 threads call it.
+template <typename Out>
+__device__ inline void rank_pairs(const hkey* list, int n, int keep, Out out) {
+  for (int e = threadIdx.x; e < n; e += 256) {
+    const hkey mine = list[e];
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < n; ++j) rank += list[j] > mine ? 1 : 0;
+    if (rank < keep) out(rank, mine);
   }
-  __syncthreads();  // the previous call's readers are done
-  if ((threadIdx.x & 63) == 0) { s_v[threadIdx.x >> 6] = v; s_i[threadIdx.x >> 6] = i; }
+}
+
+// Grid (chunk, node, request).  pairs: keys [row][chunks][K]; lse: float2 (max, sum) [row][chunks].
+__global__ __launch_bounds__(256) void k_harvest_part(const float* __restrict__ logits, size_t ld, int V, int K,
+                                                      const HarvestTable t, hkey* __restrict__ pairs,
+                                                      float2* __restrict__ lse) {
+  __shared__ hkey best[64], list[HARVEST_KMAX * 4 * HARVEST_VPT], tau_s;
+  __shared__ float red[8];
+  __shared__ int n_s;
+  const HarvestReq& q = t.r[blockIdx.z];
+  if ((int)blockIdx.y >= q.B) return;
+  const int tid = threadIdx.x, c0 = blockIdx.x * HARVEST_CHUNK;
+  const size_t row = (size_t)q.row0 + blockIdx.y;
+  const float* src = logits + row * ld + c0;
+  const int nc = min(HARVEST_CHUNK, V - c0);  // columns of this chunk (>= 1)
+  float v[HARVEST_VPT];
+#pragma unroll
+  for (int u = 0; u < HARVEST_VPT; ++u) v[u] = (tid + u * 256 < nc) ? src[tid + u * 256] : NAN;
+  if (tid == 0) {
+    n_s = 0;
+    tau_s = 0;  // (kept if fewer than K groups hold a value: every pair qualifies)
+  }
+  float bv = -INFINITY;
+  int bi = -1;
+#pragma unroll
+  for (int u = 0; u < HARVEST_VPT; ++u)
+    if (v[u] > bv || (v[u] == bv && bi < 0)) { bv = v[u]; bi = c0 + tid + u * 256; }  // (ids ascend: '>' keeps the lowest)
+  hkey bk = bi < 0 ? 0 : harvest_key(bv, bi);
+#pragma unroll
+  for (int off = 1; off < 4; off <<= 1) {
+    const hkey o = __shfl_xor(bk, off, 64);
+    bk = o > bk ? o : bk;
+  }
+  if ((tid & 3) == 0) best[tid >> 2] = bk;
+  float mx = bv;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  if ((tid & 63) == 0) red[tid >> 6] = mx;
   __syncthreads();
-  v = s_v[0]; i = s_i[0];
-#pragma unroll
-  for (int w = 1; w < 4; ++w)
-    if (cand_before(s_v[w], s_i[w], v, i)) { v = s_v[w]; i = s_i[w]; }
-}
-
-// Sorted insert of (v, c) into a thread's best-first list of N pairs.
-template <int N>
-__device__ inline void list_insert(float (&tv)[N], int (&ti)[N], float v, int c) {
-  if (!cand_before(v, c, tv[N - 1], ti[N - 1])) return;
-  tv[N - 1] = v;
-  ti[N - 1] = c;
-#pragma unroll
-  for (int j = N - 1; j > 0; --j) {
-    if (cand_before(tv[j], ti[j], tv[j - 1], ti[j - 1])) {
-      const float fv = tv[j]; tv[j] = tv[j - 1]; tv[j - 1] = fv;
-      const int fi = ti[j]; ti[j] = ti[j - 1]; ti[j - 1] = fi;
-    }
+  const float M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  if (tid < 64) {  // the rank of a group's best among the 64
+    const hkey mine = best[tid];
+    int rank = 0;
+#pragma unroll 8
+    for (int j = 0; j < 64; ++j) rank += best[j] > mine ? 1 : 0;
+    if (rank == K - 1 && mine != 0) tau_s = mine;
   }
-}
-
-// K rounds: the workgroup's best head wins, its owner pops it, thread 0 stores the winner.
-template <int N>
-__device__ inline void pop_rounds(float (&tv)[N], int (&ti)[N], int K, bool writes, int tok, float M, float S,
-                                  int32_t* succ_ids, float* succ_scores, float* s_v, int* s_i) {
-  for (int k = 0; k < K; ++k) {
-    float bv = tv[0];
-    int bi = ti[0];
-    block_best(bv, bi, s_v, s_i);
-    if (ti[0] == bi && bi != INT_MAX) {  // token ids are unique: exactly one owner
+  float sm = 0.f;
 #pragma unroll
-      for (int j = 0; j < N - 1; ++j) { tv[j] = tv[j + 1]; ti[j] = ti[j + 1]; }
-      tv[N - 1] = -INFINITY;
-      ti[N - 1] = INT_MAX;
-    }
-    if (threadIdx.x == 0 && writes) {
-      const bool real = bi != INT_MAX;
-      succ_ids[(size_t)tok * K + k] = real ? bi : -1;
-      succ_scores[(size_t)tok * K + k] = real ? __expf(bv - M) / S : 0.f;
-    }
+  for (int u = 0; u < HARVEST_VPT; ++u) sm += v[u] == v[u] ? exp_below(v[u], M) : 0.f;
+  sm = wave_sum(sm);
+  if ((tid & 63) == 0) red[4 + (tid >> 6)] = sm;
+  __syncthreads();
+  const hkey tau = tau_s;
+  const bool all = tau == 0;
+  const float tv = harvest_value(tau);
+  const int ti = harvest_id(tau);
+#pragma unroll
+  for (int u = 0; u < HARVEST_VPT; ++u) {
+    const int c = c0 + tid + u * 256;
+    if (v[u] == v[u] && (all || v[u] > tv || (v[u] == tv && c <= ti))) list[atomicAdd(&n_s, 1)] = harvest_key(v[u], c);
   }
+  __syncthreads();
+  const size_t slot = row * gridDim.x + blockIdx.x;
+  const int n = n_s;
+  rank_pairs(list, n, K, [&](int k, hkey p) { pairs[slot * K + k] = p; });
+  if (tid >= n && tid < K) pairs[slot * K + tid] = 0;
+  if (tid == 0) lse[slot] = make_float2(M, red[4] + red[5] + red[6] + red[7]);
 }
 
-template <int KMAX>
-__global__ __launch_bounds__(256) void k_harvest_topk(const float* __restrict__ logits, size_t ld, int V,
-                                                      const int32_t* __restrict__ tokens, int B, int K, int table_rows,
-                                                      int32_t* __restrict__ succ_ids,
-                                                      float* __restrict__ succ_scores) {
-  constexpr int DEPTH = 16;   // loads in flight per thread: the row was written by the previous kernel
-  constexpr int LIST = 4;     // list entries per thread on the short route
-  constexpr int CAP = 256 * LIST;
-  __shared__ float s_v[4];
-  __shared__ int s_i[4];
-  __shared__ float s_m[4], s_s[4];
-  __shared__ float c_v[CAP];
-  __shared__ int c_i[CAP];
-  __shared__ int c_n, s_dup;
+// Grid (node, request): the chunks of a row, K pairs each, into the request's tables.
+__global__ __launch_bounds__(256) void k_harvest_merge(int chunks, int table_rows, int Kpart, const HarvestTable t,
+                                                       const hkey* __restrict__ pairs, const float2* __restrict__ lse) {
+  __shared__ hkey list[HARVEST_MERGE], top[HARVEST_KMAX];
+  __shared__ float red[8];
+  const HarvestReq& q = t.r[blockIdx.y];
   const int m = blockIdx.x, tid = threadIdx.x;
-  const float* row = logits + (size_t)m * ld;
-  if (tid == 0) { c_n = 0; s_dup = 0; }
-
-  // ---- pass 1: thread-best pair and log-sum-exp
-  float bv = -INFINITY, mx = -INFINITY, sm = 0.f;
-  int bi = INT_MAX;
-  for (int c0 = tid; c0 < V; c0 += 256 * DEPTH) {
-    float vals[DEPTH];
+  if (m >= q.B) return;
+  const size_t slot0 = ((size_t)q.row0 + m) * chunks;
+  const hkey* src = pairs + slot0 * Kpart;
+  const int total = chunks * Kpart;
+  // everything the row needs is loaded up front: the kernel is a chain of trips to memory and little else
+  hkey first[HARVEST_MERGE / 256];
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u) vals[u] = (c0 + u * 256 < V) ? row[c0 + u * 256] : NAN;
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) {
-      const float v = vals[u];
-      if (!(v == v)) continue;  // past the row, or NaN: not a candidate
-      if (v > mx) { sm = sm * __expf(mx - v) + 1.f; mx = v; }
-      else sm += __expf(v - mx);
-      if (v > bv) { bv = v; bi = c0 + u * 256; }  // ids ascend within a thread: '>' keeps the lowest
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    const float om = __shfl_xor(mx, off, 64), os = __shfl_xor(sm, off, 64);
-    const float nm = fmaxf(mx, om);
-    sm = (nm == -INFINITY) ? 0.f : sm * __expf(mx - nm) + os * __expf(om - nm);
+  for (int u = 0; u < HARVEST_MERGE / 256; ++u)
+    if (tid + 256 * u < total) first[u] = src[tid + 256 * u];
+  float2 l0 = make_float2(-INFINITY, 0.f);
+  if (tid < chunks) l0 = lse[slot0 + tid];
+  const int tok = q.tokens[m], tok_t = tid < q.B ? q.tokens[tid] : 0;
+  // (max, sum of exponentials) of the row: every thread's chunks, then across the workgroup
+  float mx = l0.x, sm = l0.y;
+  for (int c = tid + 256; c < chunks; c += 256) {
+    const float2 e = lse[slot0 + c];
+    const float nm = fmaxf(mx, e.x);
+    sm = sm * exp_below(mx, nm) + e.y * exp_below(e.x, nm);
     mx = nm;
   }
-  if ((tid & 63) == 0) { s_m[tid >> 6] = mx; s_s[tid >> 6] = sm; }
+  float M = mx;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+  sm = wave_sum(sm * exp_below(mx, M));
+  if ((tid & 63) == 0) { red[tid >> 6] = M; red[4 + (tid >> 6)] = sm; }
+#pragma unroll
+  for (int u = 0; u < HARVEST_MERGE / 256; ++u)
+    if (tid + 256 * u < total) list[tid + 256 * u] = first[u];
+  if (tid < HARVEST_KMAX) top[tid] = 0;
   // does this node write?  (a valid token, and no later node with the same token)
-  const int tok = tokens[m];
-  __syncthreads();
-  if (tid > m && tid < B && tokens[tid] == tok) s_dup = 1;
-  const float M = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+  const bool dup = __syncthreads_or(tid > m && tid < q.B && tok_t == tok);
+  // rounds of up to HARVEST_MERGE pairs, the best so far among them (zero keys rank after
+  // every real pair, and the slots they do not fill are zero already)
+  int n = min(total, HARVEST_MERGE), at = n;
+  for (;;) {
+    rank_pairs(list, n, q.K, [&](int k, hkey p) { top[k] = p; });
+    __syncthreads();
+    if (at >= total) break;
+    const int take = min(HARVEST_MERGE - q.K, total - at);
+    if (tid < q.K) list[tid] = top[tid];
+    for (int e = tid; e < take; e += 256) list[q.K + e] = src[at + e];
+    __syncthreads();
+    if (tid < HARVEST_KMAX) top[tid] = 0;
+    __syncthreads();
+    n = q.K + take;
+    at += take;
+  }
+  M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   float S = 0.f;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) S += (s_m[w] == -INFINITY) ? 0.f : s_s[w] * __expf(s_m[w] - M);
-
-  // ---- tau: the K-th best of the thread-bests
-  float tau_v = -INFINITY;
-  int tau_i = INT_MAX;
-  for (int k = 0; k < K; ++k) {
-    float wv = bv;
-    int wi = bi;
-    block_best(wv, wi, s_v, s_i);
-    if (wi == bi && bi != INT_MAX) { bv = -INFINITY; bi = INT_MAX; }
-    tau_v = wv;
-    tau_i = wi;  // (-inf, INT_MAX) once the thread-bests run out: then every pair qualifies
+  for (int w = 0; w < 4; ++w) S += red[4 + w] * exp_below(red[w], M);
+  if (tid < q.K && tok >= 0 && tok < table_rows && !dup) {
+    const hkey p = top[tid];
+    q.ids[(size_t)tok * q.K + tid] = p != 0 ? harvest_id(p) : -1;
+    q.scores[(size_t)tok * q.K + tid] = p != 0 ? exp_below(harvest_value(p), M) / S : 0.f;
   }
-  const bool writes = tok >= 0 && tok < table_rows && s_dup == 0;  // s_dup settled by the barriers above
-
-  // ---- pass 2: pairs at or above tau into the list
-  for (int c0 = tid; c0 < V; c0 += 256 * DEPTH) {
-    float vals[DEPTH];
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) vals[u] = (c0 + u * 256 < V) ? row[c0 + u * 256] : NAN;
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) {
-      const float v = vals[u];
-      const int c = c0 + u * 256;
-      if (v == v && !cand_before(tau_v, tau_i, v, c)) {
-        const int pos = atomicAdd(&c_n, 1);
-        if (pos < CAP) { c_v[pos] = v; c_i[pos] = c; }
-      }
-    }
-  }
-  __syncthreads();
-  const int n = c_n;
-  if (n <= CAP) {
-    float tv[LIST];
-    int ti[LIST];
-#pragma unroll
-    for (int j = 0; j < LIST; ++j) { tv[j] = -INFINITY; ti[j] = INT_MAX; }
-    for (int e = tid; e < n; e += 256) list_insert<LIST>(tv, ti, c_v[e], c_i[e]);
-    pop_rounds<LIST>(tv, ti, K, writes, tok, M, S, succ_ids, succ_scores, s_v, s_i);
-    return;
-  }
-  // ---- plain route (wave-uniform: n is shared)
-  float tv[KMAX];
-  int ti[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) { tv[j] = -INFINITY; ti[j] = INT_MAX; }
-  for (int c = tid; c < V; c += 256) {
-    const float v = row[c];
-    if (v == v) list_insert<KMAX>(tv, ti, v, c);
-  }
-  pop_rounds<KMAX>(tv, ti, K, writes, tok, M, S, succ_ids, succ_scores, s_v, s_i);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -756,12 +769,46 @@ int launch_argmax_top2(const void* top2, int n_groups, int B, int32_t* argmax, f
   return goose_launch_status();
 }
 
-int launch_harvest_topk(const float* logits, size_t ld, int V, const int32_t* tokens, int B, int K, int table_rows,
-                        int32_t* succ_ids, float* succ_scores, hipStream_t st) {
-  if (K < 1 || K > 16) return GOOSE_ERR_ARG;
-  hipLaunchKernelGGL(k_harvest_topk<16>, dim3(B), dim3(256), 0, st, logits, ld, V, tokens, B, K, table_rows, succ_ids,
-                     succ_scores);
-  return goose_launch_status();
+// One launch of k_harvest_part for all requests.  The tables of different requests are normally distinct and one
+// launch of k_harvest_merge fills them all; where two of them overlap (requests that share a table) they are filled one
+// request after the other, so that the later request wins.
+int launch_harvest_topk(const float* logits, size_t ld, int V, const HarvestReq* reqs, int n, void* ws, hipStream_t st) {
+  if (n < 1 || n > GOOSE_MAX_REQUESTS || ws == nullptr || V < 1) return GOOSE_ERR_ARG;
+  HarvestTable t{};
+  int k_max = 0, b_max = 0;
+  size_t rows = 0;
+  bool overlap = false;
+  for (int r = 0; r < n; ++r) {
+    const HarvestReq& q = reqs[r];
+    if (q.K < 1 || q.K > HARVEST_KMAX || q.B < 1 || q.row0 < 0) return GOOSE_ERR_ARG;
+    t.r[r] = q;
+    k_max = q.K > k_max ? q.K : k_max;
+    b_max = q.B > b_max ? q.B : b_max;
+    rows = (size_t)(q.row0 + q.B) > rows ? (size_t)(q.row0 + q.B) : rows;
+    for (int p = 0; p < r; ++p) {
+      const size_t a = (size_t)V * q.K, b = (size_t)V * reqs[p].K;
+      overlap = overlap || (q.ids < reqs[p].ids + b && reqs[p].ids < q.ids + a) ||
+                (q.scores < reqs[p].scores + b && reqs[p].scores < q.scores + a);
+    }
+  }
+  const int chunks = (V + HARVEST_CHUNK - 1) / HARVEST_CHUNK;
+  float2* lse = static_cast<float2*>(ws);
+  hkey* pairs = reinterpret_cast<hkey*>(lse + rows * chunks);
+  hipLaunchKernelGGL(k_harvest_part, dim3(chunks, b_max, n), dim3(256), 0, st, logits, ld, V, k_max, t, pairs, lse);
+  int rc = goose_launch_status();
+  if (rc != GOOSE_OK) return rc;
+  if (!overlap) {
+    hipLaunchKernelGGL(k_harvest_merge, dim3(b_max, n), dim3(256), 0, st, chunks, V, k_max, t, pairs, lse);
+    return goose_launch_status();
+  }
+  for (int r = 0; r < n; ++r) {
+    HarvestTable one{};
+    one.r[0] = reqs[r];
+    hipLaunchKernelGGL(k_harvest_merge, dim3(reqs[r].B, 1), dim3(256), 0, st, chunks, V, k_max, one, pairs, lse);
+    rc = goose_launch_status();
+    if (rc != GOOSE_OK) return rc;
+  }
+  return GOOSE_OK;
 }
 
 static ReqTable req_table(const BatchReq* reqs, int n) {

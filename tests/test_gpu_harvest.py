@@ -68,6 +68,32 @@ def test_harvest_row_that_defeats_the_prefilter():
     c.close()
 
 
+@pytest.mark.parametrize("V,K", [(16, 16), (8191, 10), (8192, 16), (8193, 16), (24577, 3), (600000, 16)])
+def test_harvest_chunk_edges(V, K):
+    """A row is cut into chunks of 8192 columns: vocabularies around the cut (the last chunk may hold one column), and one whose
+    chunks give more pairs than one merge round ranks.  Rows: ordinary; every large logit in the share of four neighbouring
+    threads; all -inf but a few; the winners spread over the chunk borders; equal everywhere."""
+    dev = "cuda:0"
+    c = _ctx(V)
+    rng = np.random.default_rng(V)
+    logits = (rng.normal(size=(5, V)) * 3).astype(np.float32)
+    cols = np.arange(V)
+    logits[1, (cols % 256) < 4] += 40.0
+    logits[2] = -np.inf
+    logits[2, rng.permutation(V)[:5]] = [1.0, 2.0, 2.0, -3.0, 0.5]
+    logits[3, np.unique(np.clip([0, 8190, 8191, 8192, 8193, 16383, 16384, V - 2, V - 1], 0, V - 1))] = 30.0
+    logits[4] = -0.25
+    tokens = rng.permutation(V)[:5].astype(np.int32)
+    d_ids = torch.full((V, K), -1, dtype=torch.int32, device=dev)
+    d_sc = torch.zeros((V, K), dtype=torch.float32, device=dev)
+    c.goose_harvest_topk(torch.from_numpy(logits).to(dev), V, torch.from_numpy(tokens).to(dev), 5, K, d_ids, d_sc)
+    torch.cuda.synchronize()
+    ref_ids, ref_sc = orc.harvest_topk(logits.astype(np.float64), tokens, K)
+    assert np.array_equal(d_ids.cpu().numpy(), ref_ids)
+    np.testing.assert_allclose(d_sc.cpu().numpy(), ref_sc, rtol=2e-5, atol=1e-12)
+    c.close()
+
+
 def test_harvest_inside_the_fused_step():
     shape = gi.SHAPES["small_bf16"]
     tm = torch_model(shape, seed=2, gain_jitter=0.1)
