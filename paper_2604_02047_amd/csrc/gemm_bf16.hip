@@ -119,22 +119,20 @@ __global__ __launch_bounds__(256) void k_pack_bf16(int mode, const bf16_t* __res
 // 172 with four.
 // EPI_TOP2: besides the optional plain output, every workgroup reduces its columns to one
 // (largest, second largest, index of largest) triple per row, for the greedy argmax.
-// CHUNKED: more than MT*32 rows, computed as several row chunks that read the same weights (1-D
-// grid in an XCD-aware order, ordinary loads so that the chunks share the L2); otherwise the
-// weights are read once by the whole grid, with non-temporal loads that keep them from displacing
+// The weights are read once by the whole grid, with non-temporal loads that keep them from displacing
 // the L2's other lines.  F16: fp16 instead of bf16 operands (and SwiGLU output).
 // word 3 of a raw buffer descriptor on this target (32-bit untyped data, range checking on the byte offset)
 #define GOOSE_BUFFER_WORD3 0x00020000
 #define GOOSE_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }  // s_waitcnt vmcnt(n) only
 
-template <int MT, int NW, int TERMS, int EPI, bool CHUNKED = false, bool F16 = false>
+template <int MT, int NW, int TERMS, int EPI, bool F16>
 __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>::T* __restrict__ A, int lda,
                                                             const u32x4* __restrict__ Wp, int ntiles, int ksteps_total,
                                                             int stages_per_split, int B, void* __restrict__ out,
                                                             size_t ldo, size_t split_stride,
-                                                            float4* __restrict__ top2, int n_valid, int gx, int nsplit,
-                                                            int nchunk, float out_scale, int32_t* __restrict__ flags) {
+                                                            float4* __restrict__ top2, int n_valid, float out_scale,
+                                                            int32_t* __restrict__ flags) {
   typedef typename Mma16<F16>::T T;
   typedef typename Mma16<F16>::v8 op8;
   constexpr int KC = 128, STEPS = KC / 16;
@@ -178,22 +176,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (in a scalar register: it selects buffer descriptors)
   const int wt = wave;  // this wavefront's column tile
-  // Work item = (column-tile group bx, split-K range by, row chunk of MT*32 rows).  One chunk: the
-  // plain 2-D grid.  Several chunks: a 1-D grid; workgroups are dealt to the 8 XCDs round-robin in
-  // launch order and the chunks of one (bx, by) read the same weights, so they take consecutive
-  // slots of ONE XCD: its L2 then serves all but the first.
-  constexpr bool STREAM = !CHUNKED;
-  int bx = blockIdx.x, by = blockIdx.y, row_base = 0, ngroups = gridDim.x;
-  if (CHUNKED) {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int j = slot / nchunk, chunk = slot - j * nchunk;
-    const int t = j * 8 + xcd;
-    if (t >= gx * nsplit) return;  // the grid is rounded up to whole groups of 8
-    by = t / gx;
-    bx = t - by * gx;
-    row_base = chunk * MT * 32;
-    ngroups = gx;
-  }
+  const int bx = blockIdx.x, by = blockIdx.y, ngroups = gridDim.x;  // column-tile group, split-K range
   const int tile = EPI == EPI_TOP2 ? bx * NW + wt : bx + ngroups * wt;
   const bool active = tile < ntiles;
   // a wavefront without a tile runs the same pipeline (no divergent control flow: the compiler can
@@ -229,7 +212,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
     const int c = min(wave * CPW + q, COPIES - 1);
     const int row = c * ROWS_PER_COPY + lane / SU, pos = lane % SU;
     const int unit = (pos & ~15) | ((pos ^ row) & 15);
-    a_src[q] = reinterpret_cast<const u32x4*>(A) + (size_t)(row_base + row) * row_units +
+    a_src[q] = reinterpret_cast<const u32x4*>(A) + (size_t)row * row_units +
                (size_t)s_begin * SU + unit;
   }
   auto copy_a = [&](int i, auto buf_c) {  // stage i -> LDS buffer buf
@@ -257,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
     for (int s = 0; s < STEPS; ++s)
-      wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, w_lane, (i * STEPS + s) * 1024, STREAM ? 2 : 0);
+      wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, w_lane, (i * STEPS + s) * 1024, 2);
 #endif
   };
   // operand reads: lane l holds row l % 32 (of row tile mt) and the eight inputs 8*(l/32).. of a k-step
@@ -309,7 +292,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = Mma16<F16>::mfma(af[s % NB][t][mt], b, acc[mt]);
 #if defined(__HIP_DEVICE_COMPILE__)
-      wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, w_lane, ((i + D) * STEPS + s) * 1024, STREAM ? 2 : 0);
+      wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, w_lane, ((i + D) * STEPS + s) * 1024, 2);
 #endif
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -358,7 +341,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
     const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
         reinterpret_cast<float*>(out) + by * split_stride, 0, (int)((size_t)B * ldo * 4), GOOSE_BUFFER_WORD3);
     const int ldo4 = (int)ldo * 4;
-    const int voff = (row_base + 4 * (lane >> 5)) * ldo4 + col * 4;
+    const int voff = 4 * (lane >> 5) * ldo4 + col * 4;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -378,7 +361,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
       for (int r = 0; r < 16; ++r) {
         const int row = mt * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
         const float v = acc[mt][r] * out_scale;
-        if (o != nullptr && active && row_base + row < B) o[(size_t)(row_base + row) * ldo + col] = v;
+        if (o != nullptr && active && row < B) o[(size_t)row * ldo + col] = v;
         ct[row * CT_ROW + (lane & 31)] = v;
       }
     __syncthreads();
@@ -406,7 +389,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
           if (e.x > t.x) { t.y = fmaxf(t.x, e.y); t.x = e.x; t.z = e.z; }
           else t.y = fmaxf(t.y, e.x);
         }
-        if (row_base + row < B) top2[(size_t)(row_base + row) * ngroups + bx] = t;
+        if (row < B) top2[(size_t)row * ngroups + bx] = t;
       }
     }
   } else {  // EPI_SWIGLU
@@ -426,7 +409,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
       bool clamped = false;
       for (int e = lane; e < MT * 16 * 16; e += 64) {
         const int pr = e & 7, half = (e >> 3) & 1, rr = (e >> 4) & 15, mt = e >> 8;  // column pair, lane half, register, row tile
-        const int row = row_base + mt * 32 + 8 * (rr >> 2) + 4 * half + (rr & 3);
+        const int row = mt * 32 + 8 * (rr >> 2) + 4 * half + (rr & 3);
         const int col = tile * 16 + 2 * pr;
         const float* src = &mine[(mt * 16 + rr) * 64 + half * 32 + 2 * pr];
         const float2 g = *reinterpret_cast<const float2*>(src);
@@ -461,21 +444,18 @@ struct GemmCall {
   int gx = 0;  // grid width in workgroups per K range (0: chosen by launch_one)
 };
 
-template <int MT, int NW, int TERMS, int EPI, bool CHUNKED, bool F16>
-int launch_k(const GemmCall& g, dim3 grid, int gx, int gps, int nchunk) {
-  hipLaunchKernelGGL((k_gemm_bf16<MT, NW, TERMS, EPI, CHUNKED, F16>), grid, dim3(64 * NW), 0, g.st,
+template <int MT, int NW, int TERMS, int EPI, bool F16>
+int launch_k(const GemmCall& g, dim3 grid, int gps) {
+  hipLaunchKernelGGL((k_gemm_bf16<MT, NW, TERMS, EPI, F16>), grid, dim3(64 * NW), 0, g.st,
                      (const typename Mma16<F16>::T*)g.A, g.lda, (const u32x4*)g.Wp, g.Npad / 32, g.Kpad / 16, gps, g.B,
-                     g.out, g.ldo, g.split_stride, (float4*)g.top2, g.n_valid, gx, g.ksplit, nchunk, g.out_scale, g.flags);
+                     g.out, g.ldo, g.split_stride, (float4*)g.top2, g.n_valid, g.out_scale, g.flags);
   return goose_launch_status();
 }
 
-template <int MT, int NW, int EPI, bool CHUNKED>
-int launch_terms(const GemmCall& g, dim3 grid, int gx, int gps, int nchunk) {
-  if (g.terms == 2)
-    return g.f16 ? launch_k<MT, NW, 2, EPI, CHUNKED, true>(g, grid, gx, gps, nchunk)
-                 : launch_k<MT, NW, 2, EPI, CHUNKED, false>(g, grid, gx, gps, nchunk);
-  return g.f16 ? launch_k<MT, NW, 1, EPI, CHUNKED, true>(g, grid, gx, gps, nchunk)
-               : launch_k<MT, NW, 1, EPI, CHUNKED, false>(g, grid, gx, gps, nchunk);
+template <int MT, int NW, int EPI>
+int launch_terms(const GemmCall& g, dim3 grid, int gps) {
+  if (g.terms == 2) return g.f16 ? launch_k<MT, NW, 2, EPI, true>(g, grid, gps) : launch_k<MT, NW, 2, EPI, false>(g, grid, gps);
+  return g.f16 ? launch_k<MT, NW, 1, EPI, true>(g, grid, gps) : launch_k<MT, NW, 1, EPI, false>(g, grid, gps);
 }
 
 template <int MT, int NW, int EPI>
@@ -492,22 +472,17 @@ int launch_one(const GemmCall& g) {
     const int want = (256 + g.ksplit - 1) / g.ksplit;
     gx = want < ntiles ? (want > gx ? want : gx) : ntiles;
   }
-  const int nchunk = (g.B + MT * 32 - 1) / (MT * 32);  // more than 128 rows: chunks of 4 row tiles
-  const dim3 grid = nchunk == 1 ? dim3(gx, g.ksplit) : dim3((gx * g.ksplit + 7) / 8 * 8 * nchunk);
   const int granules = g.Kpad / KGRAN;                      // split-K ranges are multiples of 128 inputs
   const int gps = (granules + g.ksplit - 1) / g.ksplit;     // granules (= stages) per split
-  if constexpr (MT == 4) {
-    if (nchunk > 1) return launch_terms<MT, NW, EPI, true>(g, grid, gx, gps, nchunk);
-  }
-  return launch_terms<MT, NW, EPI, false>(g, grid, gx, gps, nchunk);
+  return launch_terms<MT, NW, EPI>(g, dim3(gx, g.ksplit), gps);
 }
 
-// five-wavefront workgroups (single row chunk only): see launch_gemm_16
+// five-wavefront workgroups: see launch_gemm_16
 template <int MT, int EPI>
 int launch_five(const GemmCall& g) {
   const int granules = g.Kpad / KGRAN;
   const int gps = (granules + g.ksplit - 1) / g.ksplit;
-  return launch_terms<MT, 5, EPI, false>(g, dim3(g.gx, g.ksplit), g.gx, gps, 1);
+  return launch_terms<MT, 5, EPI>(g, dim3(g.gx, g.ksplit), gps);
 }
 template <int EPI>
 int launch_mt5(int MT, const GemmCall& g) {
@@ -582,7 +557,11 @@ int launch_gemm_top2_16(int dtype, const void* A, int lda, int terms, const void
   if (B < 1 || B > GOOSE_MAX_ROWS || (Npad & 31) || (Kpad % KGRAN) || !top2 || n_valid < 1 || n_valid > Npad)
     return GOOSE_ERR_ARG;
   if ((terms != 1 && terms != 2) || lda < Kpad * terms || (lda & 7)) return GOOSE_ERR_ARG;
-  const int MT = B > 128 ? 4 : (B + 31) / 32;
+  if (B > 128)  // the kernel blocked for the matrix cores
+    return nw != GOOSE_ROWS_TILES ? GOOSE_ERR_ARG
+                                  : launch_gemm_rows_16(dtype, EPI_TOP2, A, lda, terms, Wp, Npad, Kpad, B, 1, out, ldo, 0, top2,
+                                                        n_valid, out_scale, nullptr, st);
+  const int MT = (B + 31) / 32;
   const GemmCall g{A, lda, Wp, Npad, Kpad, B, 1, out, ldo, 0, st, top2, n_valid, f16, terms, out_scale, nullptr};
   return nw == 4 ? launch_mt<4, EPI_TOP2>(MT, g) : launch_mt<2, EPI_TOP2>(MT, g);
 }
@@ -597,8 +576,8 @@ int launch_gemm_16(int dtype, int epi, const void* A, int lda, int terms, const 
   if (epi != EPI_PARTIAL && epi != EPI_SWIGLU) return GOOSE_ERR_ARG;
   if (epi == EPI_SWIGLU && (ksplit != 1 || (Npad & 63))) return GOOSE_ERR_ARG;
   if (B > 128)  // the kernel blocked for the matrix cores
-    return launch_gemm_rows_16(dtype, epi, A, lda, terms, Wp, Npad, Kpad, B, ksplit, out, ldo, out_split_stride, out_scale,
-                               flags, st);
+    return launch_gemm_rows_16(dtype, epi, A, lda, terms, Wp, Npad, Kpad, B, ksplit, out, ldo, out_split_stride, nullptr, 0,
+                               out_scale, flags, st);
   const int MT = (B + 31) / 32;
   // More four-tile workgroups than compute units would run as one round plus a few stragglers (or
   // with some units loaded twice, which then take twice as long: a unit pulls only so many bytes

@@ -215,6 +215,14 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
       if (d.dtype == GOOSE_DTYPE_BF16) { c->w_exp = 8; c->out_scale = 1.0f / 256.0f; }
     }
   }
+  // Rows of the operands at a stride of a power of two (Kh = 4096: 8 KiB) fall on the same L2 channel, and
+  // the projections copy many rows of one column range at a time.  With up to 256 rows that costs
+  // nothing measurable; 512 rows of the 28672 x 4096 gate/up product take 148 us at a stride of 8192
+  // bytes and 122 us with 256 bytes more (256 rows: 80 and 82 us).
+  const int pad = is16(d.dtype) && c->Bpad > 256 ? 128 : 0;
+  c->ld_xn = c->Kh * c->terms + pad;
+  c->ld_o = c->Kq * c->terms + pad;
+  c->ld_h = c->Fpad * c->terms + pad;
   compute_layouts(c);
 
   const size_t es = elem_size(d.dtype);
@@ -224,11 +232,11 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
   c->part_ld = widest;
   int rc = GOOSE_OK;
   auto A = [&](void** p, size_t bytes) { if (rc == GOOSE_OK) rc = dev_alloc(p, bytes); };
-  A(&c->xn, (size_t)c->Bpad * c->Kh * es * c->terms);
+  A(&c->xn, (size_t)c->Bpad * c->ld_xn * es);
   A((void**)&c->part, (size_t)c->max_ksplit * c->Bpad * c->part_ld * sizeof(float));
   A(&c->q, (size_t)c->Bpad * c->Kq * es);
-  A(&c->o, (size_t)c->Bpad * c->Kq * es * c->terms);
-  A(&c->h, (size_t)c->Bpad * c->Fpad * es * c->terms);
+  A(&c->o, (size_t)c->Bpad * c->ld_o * es);
+  A(&c->h, (size_t)c->Bpad * c->ld_h * es);
   A((void**)&c->att_o, (size_t)d.n_heads * c->max_splits * c->Bpad * d.head_dim * sizeof(float));
   A((void**)&c->att_ml, (size_t)d.n_heads * c->max_splits * c->Bpad * 2 * sizeof(float));
   A((void**)&c->logits, (size_t)c->Bpad * c->Vpad * sizeof(float));
@@ -365,7 +373,7 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   if (!xhat_ready) {
     PROF(PK_NORM);
     rc = launch_resid_norm(d.dtype, c->act_dtype, d_x, H, nullptr, 0, 0, 0, w + c->pl.g1, d.rms_eps, c->xn,
-                           c->Kh * c->terms, c->terms, B, st);
+                           c->ld_xn, c->terms, B, st);
   }
   if (rc) return rc;
 
@@ -376,7 +384,7 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
     const GemmCfg cq = gemm_cfg(c, "GOOSE_CFG_QKV", Nqkv, c->Kh);
     int ks = cq.ks;
     { PROF(PK_GEMM_QKV);
-      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->xn, c->Kh * T, T, w + c->pl.wqkv, Nqkv, c->Kh, B, cq.nw, ks,
+      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->xn, c->ld_xn, T, w + c->pl.wqkv, Nqkv, c->Kh, B, cq.nw, ks,
                           c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
     if (rc) return rc;
     // rotary embedding of q and k, KV rows of the tree into the cache, tree attention: one kernel
@@ -386,35 +394,35 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
     { PROF(PK_ATTN);
       rc = launch_attn_16(d.dtype, c->part, ks, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, segs,
                             nseg, splits_env, c->max_splits, ng_env, d.qk_norm ? w + c->pl.gq : nullptr,
-                            d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->Kq * T,
+                            d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o,
                             T, c->act_dtype, c->flags, st); }
     if (rc) return rc;
     const GemmCfg co = gemm_cfg(c, "GOOSE_CFG_O", Nh, c->Kq);
     ks = co.ks;
     { PROF(PK_GEMM_O);
-      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->o, c->Kq * T, T, w + c->pl.wo, Nh, c->Kq, B, co.nw, ks, c->part,
+      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->o, c->ld_o, T, w + c->pl.wo, Nh, c->Kq, B, co.nw, ks, c->part,
                           c->part_ld, pstride, c->out_scale, c->flags, st); }
     if (rc) return rc;
     // x += attention projection; x_hat = RMSNorm(x) * g2
     { PROF(PK_NORM);
       rc = launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks, pstride, c->part_ld, w + c->pl.g2, d.rms_eps,
-                             c->xn, c->Kh * T, T, B, st); }
+                             c->xn, c->ld_xn, T, B, st); }
     if (rc) return rc;
     static const int gu_nw = env_int("GOOSE_GU_NW", 4) == 2 ? 2 : 4;
     { PROF(PK_GEMM_GATE_UP);
-      rc = launch_gemm_16(c->act_dtype, EPI_SWIGLU, c->xn, c->Kh * T, T, w + c->pl.wgu, Ngu, c->Kh, B, gu_nw, 1, c->h,
-                          (size_t)c->Fpad * T, 0, c->out_scale, c->flags, st); }
+      rc = launch_gemm_16(c->act_dtype, EPI_SWIGLU, c->xn, c->ld_xn, T, w + c->pl.wgu, Ngu, c->Kh, B, gu_nw, 1, c->h,
+                          (size_t)c->ld_h, 0, c->out_scale, c->flags, st); }
     if (rc) return rc;
     const GemmCfg cd = gemm_cfg(c, "GOOSE_CFG_DOWN", Nh, c->Fpad);
     ks = cd.ks;
     { PROF(PK_GEMM_DOWN);
-      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->h, c->Fpad * T, T, w + c->pl.wd, Nh, c->Fpad, B, cd.nw, ks,
+      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->h, c->ld_h, T, w + c->pl.wd, Nh, c->Fpad, B, cd.nw, ks,
                           c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
     if (rc) return rc;
     // x += MLP output (and the following normalisation when its gain is known)
     PROF(PK_NORM);
     return launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks, pstride, c->part_ld, g_next, d.rms_eps,
-                             g_next ? c->xn : nullptr, g_next ? c->Kh * T : 0, T, B, st);
+                             g_next ? c->xn : nullptr, g_next ? c->ld_xn : 0, T, B, st);
   }
 
   // fp32 storage: plain kernels (one request)
@@ -488,19 +496,20 @@ static int lm_head_impl(goose_ctx* c, const void* d_packed_head, const float* d_
   int rc = GOOSE_OK;
   if (!xhat_ready)
     rc = launch_resid_norm(d.dtype, c->act_dtype, const_cast<float*>(d_x), d.hidden, nullptr, 0, 0, 0, w + c->ph.gf,
-                           d.rms_eps, c->xn, c->Kh * c->terms, c->terms, B, st);
+                           d.rms_eps, c->xn, c->ld_xn, c->terms, B, st);
   if (rc) return rc;
   if (is16(d.dtype)) {
     // the projection kernel reduces its own columns to (max, second, index) per row; logits are
     // written only on request (through the padded workspace when rows are no multiple of a tile)
-    static const int lm_nw = env_int("GOOSE_LM_NW", 4) == 2 ? 2 : 4;
+    static const int lm_env = env_int("GOOSE_LM_NW", 4) == 2 ? 2 : 4;
+    const int lm_nw = B > 128 ? (int)GOOSE_ROWS_TILES : lm_env;  // column tiles per workgroup of the kernel that runs
     // (the harvest needs them too: into the workspace then)
     const bool bounce = d_logits_or_null && (d.vocab % 32) != 0;
     float* out = (bounce || (!d_logits_or_null && hv.n > 0)) ? c->logits : d_logits_or_null;
     const size_t ld = out == c->logits ? (size_t)c->Vpad : (size_t)d.vocab;
     const int groups = (c->Vpad / 32 + lm_nw - 1) / lm_nw;
     { PROF(PK_LM_HEAD);
-      rc = launch_gemm_top2_16(c->act_dtype, c->xn, c->Kh * c->terms, c->terms, w + c->ph.wlm, c->Vpad, c->Kh, B, lm_nw, out,
+      rc = launch_gemm_top2_16(c->act_dtype, c->xn, c->ld_xn, c->terms, w + c->ph.wlm, c->Vpad, c->Kh, B, lm_nw, out,
                                ld, c->top2, d.vocab, c->out_scale, st); }
     if (rc) return rc;
     if (bounce)

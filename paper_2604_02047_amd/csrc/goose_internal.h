@@ -62,12 +62,13 @@ struct goose_ctx {
   PackedHeadLayout ph;
 
   // device workspace
-  void* xn;        // T [Bpad][Kh]   normalised activations (GEMM operand)
+  int ld_xn, ld_o, ld_h;  // row lengths (elements) of the GEMM operands below: K * terms, padded in large contexts
+  void* xn;        // T [Bpad][ld_xn] normalised activations (GEMM operand)
   float* part;     // f32 [max_ksplit][Bpad][part_ld]   GEMM outputs / split-K partials
   size_t part_ld;  // row length of `part`
   void* q;         // T [Bpad][Kq]   rotated queries
-  void* o;         // T [Bpad][Kq]   attention output (GEMM operand)
-  void* h;         // T [Bpad][Fpad] SwiGLU output (GEMM operand)
+  void* o;         // T [Bpad][ld_o] attention output (GEMM operand)
+  void* h;         // T [Bpad][ld_h] SwiGLU output (GEMM operand)
   float* att_o;    // f32 [n_heads][max_splits][Bpad][head_dim]
   float* att_ml;   // f32 [n_heads][max_splits][Bpad][2]
   float* logits;   // f32 [Bpad][Vpad]  (fp32 models; vocabularies that are no multiple of 32)
@@ -165,14 +166,15 @@ static __device__ __forceinline__ float swiglu_f32(float g, float u) {
 int launch_gemm_16(int dtype, int epi, const void* A, int lda, int terms, const void* Wp, int Npad, int Kpad, int B,
                    int nw, int ksplit, void* out, size_t ldo, size_t out_split_stride, float out_scale, int32_t* flags,
                    hipStream_t st);
-// The same products for 128 < B <= GOOSE_MAX_ROWS stacked rows, blocked for the matrix cores
-// (gemm_rows_bf16.hip); A must hold whole chunks of 128 readable rows.
+// The same products, and launch_gemm_top2_16's, for 128 < B <= GOOSE_MAX_ROWS stacked rows, blocked for the matrix cores
+// (gemm_rows_bf16.hip); EPI_TOP2: top2 is float4 [B][ceil(Npad/32/GOOSE_ROWS_TILES)].
+enum { GOOSE_ROWS_TILES = 8 };
 int launch_gemm_rows_16(int dtype, int epi, const void* A, int lda, int terms, const void* Wp, int Npad, int Kpad, int B,
-                        int ksplit, void* out, size_t ldo, size_t out_split_stride, float out_scale, int32_t* flags,
-                        hipStream_t st);
+                        int ksplit, void* out, size_t ldo, size_t out_split_stride, void* top2, int n_valid, float out_scale,
+                        int32_t* flags, hipStream_t st);
 // Projection whose workgroups (nw column tiles each) also emit per-row (max, second max, index of
 // max) over their valid columns (< n_valid): top2 is float4 [B][ceil(Npad/32/nw)], index bits in .z.
-// `out` (f32 [B][ldo]) may be null when only the reduction is wanted.
+// `out` (f32 [B][ldo]) may be null when only the reduction is wanted.  nw is 2 or 4, and GOOSE_ROWS_TILES beyond 128 rows.
 int launch_gemm_top2_16(int dtype, const void* A, int lda, int terms, const void* Wp, int Npad, int Kpad, int B, int nw,
                         float* out, size_t ldo, void* top2, int n_valid, float out_scale, hipStream_t st);
 // Logit harvest of up to GOOSE_MAX_REQUESTS requests (goose_harvest_topk's semantics each): request r's nodes are rows

@@ -71,6 +71,17 @@ def test_gemm_row_chunks(B):
     _run(B, 4096, 2048, 4, 4)
 
 
+@pytest.mark.parametrize("B", [129, 191, 193, 256, 257, 384, 385, 449])
+def test_gemm_many_rows_edges(B):
+    """The many-row kernel picks workgroups of 128, 192 or 256 rows x 256 columns: row counts on both sides of
+    each, fewer columns than one workgroup, a ragged last one, and ranges of 2 to 6 stages through a ring of two or three slots."""
+    for K in (128, 256, 384):
+        _run(B, 40, K, 4, 1, dt=torch.float16)
+        _run(B, 288, K, 4, 1, terms=2)
+    _run(B, 2080, 640, 4, 5)
+    _run(B, 2080, 896, 2, 3, dt=torch.float16)
+
+
 @pytest.mark.parametrize("stages,ks", [(1, 1), (2, 1), (2, 2), (3, 1), (3, 3), (4, 2), (5, 1), (5, 2), (6, 3),
                                        (8, 2), (9, 2), (22, 5), (32, 1), (32, 4), (86, 8)])
 def test_gemm_stage_counts_and_splits(stages, ks):
