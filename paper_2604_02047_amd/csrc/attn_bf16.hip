@@ -136,7 +136,7 @@ __global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
   const int Hq = n_heads * D, Hkv = n_kv_heads * D;
   const int kcol = Hq + kvh * D - h * D, vcol = kcol + Hkv;  // relative to this head's q columns
   const bool tail_writer = h == kvh * group;                 // one head of the group stores the tree's K/V
-  int P = *sg.dP;   // (used further down: the loads below do not wait for it)
+  int P = sg.dP != nullptr ? *sg.dP : sg.P_max;   // (used further down: the loads below do not wait for it)
   const bool last = blockIdx.y == gridDim.y - 1;
   // ---- q of all query tiles (every split), k and v of the tree (last split): sum the split-K
   // slices, rotate q and k, bf16 into LDS.  One item = 4 columns j0.. and their rotation partners
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(128 * NQH) void k_attn_wide(
   const int Hq = n_heads * D, Hkv = n_kv_heads * D;
   const int kcol = Hq + kvh * D - h * D, vcol = kcol + Hkv;
   const bool tail_writer = h == kvh * group;
-  int P = *sg.dP;
+  int P = sg.dP != nullptr ? *sg.dP : sg.P_max;
   const bool last = blockIdx.y == gridDim.y - 1;
   const int nbt = (B + 31) >> 5;
   const int rows = nbt * 32;
@@ -1141,19 +1141,6 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ at
   if (oterms == 2) *reinterpret_cast<u16x4*>(dst + 8) = v2;
 }
 
-// (cos, sin) of pos[m] * base^(-2j/d) for every node m and pair j: the angle is reduced in double,
-// then evaluated in float (|error| ~ 1e-7 rad at any position).
-__global__ void k_rope_table(const int32_t* __restrict__ pos, const double* __restrict__ inv_freq, int half,
-                             float2* __restrict__ cs) {
-  const int m = blockIdx.x, j = threadIdx.x;
-  double ang = (double)pos[m] * inv_freq[j];
-  const double two_pi = 6.283185307179586476925286766559;
-  ang -= two_pi * rint(ang / two_pi);
-  float sn, c;
-  sincosf((float)ang, &sn, &c);
-  cs[(size_t)m * half + j] = make_float2(c, sn);
-}
-
 struct AttnArgs {
   const float* part; int ks; size_t part_stride, part_ld; int n_heads, n_kv;
   const float2* cs; int cap; const void* gq; const void* gk; float eps;
@@ -1232,11 +1219,6 @@ int launch_merge(dim3 grid, int head_dim, hipStream_t st, const AttnArgs& a, int
 
 }  // namespace
 
-int launch_rope_table(const int32_t* pos, const double* inv_freq, int B, int head_dim, void* cs, hipStream_t st) {
-  hipLaunchKernelGGL(k_rope_table, dim3(B), dim3(head_dim / 2), 0, st, pos, inv_freq, head_dim / 2, (float2*)cs);
-  return goose_launch_status();
-}
-
 // Key splits per head for a pass over `keys_max` keys: about two 32-key blocks per wavefront
 // (4 key groups per workgroup), but never more workgroups than compute units.  Measured: a
 // workgroup's fixed cost (projection slices, rotation, merge) and its LDS footprint (one or two
@@ -1268,7 +1250,7 @@ int launch_attn_16(int dtype, const float* part, int ks, size_t part_stride, siz
   for (int r = 0; r < nseg; ++r) {
     const AttnSeg& g = segs[r];
     if (g.B < 1 || g.B > GOOSE_MAX_B || g.row0 < 0 || (g.row0 & 31) || g.row0 + tiles_of(g.B) * 32 > Bpad ||
-        g.P_max < 0 || g.P_max + g.B > cap || !g.kc || !g.vc || !g.dP || !g.mask)
+        g.P_max < 0 || g.P_max + g.B > cap || !g.kc || !g.vc || !g.mask)
       return GOOSE_ERR_ARG;
   }
   // one launch per class of tree size (1 to 4 query tiles): the class fixes the workgroup shape

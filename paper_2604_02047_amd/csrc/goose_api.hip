@@ -341,10 +341,7 @@ int goose_build_mask(goose_ctx* c, const int32_t* d_parent, int B, int P, const 
   if (rc) return rc;
   if (!d_parent || !d_mask || !d_depth || !d_pos) return GOOSE_ERR_ARG;
   hipStream_t st = as_stream(stream);
-  const int32_t* dP;
-  rc = resolve_P(c, P, d_P, st, &dP);
-  if (rc) return rc;
-  return launch_build_mask(d_parent, B, dP, d_mask, d_depth, d_pos, c->flags, c->cap, d_P ? c->cap - B : P, st);
+  return launch_build_mask(d_parent, B, d_P, d_mask, d_depth, d_pos, c->flags, c->cap, d_P ? c->cap - B : P, st);
 }
 
 int goose_embed(goose_ctx* c, const void* d_embed, const int32_t* d_tokens, int B, float* d_x, void* stream) {
@@ -354,8 +351,13 @@ int goose_embed(goose_ctx* c, const void* d_embed, const int32_t* d_tokens, int 
   return launch_embed(c->d.dtype, d_embed, d_tokens, B, c->d.hidden, c->d.vocab, d_x, as_stream(stream));
 }
 
+static RopeArgs rope_args(const goose_ctx* c, const int32_t* pos, int rows) {
+  return RopeArgs{pos, c->inv_freq, (float2*)c->rope_cs, rows, c->d.head_dim / 2};
+}
+
 // One decoder layer.  `xhat_ready`: the operand buffer already holds RMSNorm(x)*g1 (the previous
-// layer's closing kernel wrote it).  `g_next`: gain of the normalisation that follows this layer
+// layer's closing kernel wrote it); `rope`, with xhat_ready false only: the rotary angles of the
+// tree, written by the launch that normalises.  dP null (16-bit storage): the cache length is P.  `g_next`: gain of the normalisation that follows this layer
 // (the next layer's g1 or the final norm), folded into the closing residual add; null to skip.
 // A batch of requests shares every projection (their rows are stacked, each request starting at a
 // multiple of 32 rows); in the attention every request is a slice of the grid with its own caches,
@@ -363,7 +365,8 @@ int goose_embed(goose_ctx* c, const void* d_embed, const int32_t* d_tokens, int 
 static_assert(GOOSE_MAX_REQUESTS <= ATTN_MAX_SEGS, "a batch must fit the attention's request table");
 static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, void* d_vcache, int P,
                       const int32_t* dP, int B, const uint64_t* d_mask, const int32_t* d_pos, hipStream_t st,
-                      bool xhat_ready, const void* g_next, const AttnSeg* segs = nullptr, int nseg = 0) {
+                      bool xhat_ready, const void* g_next, const RopeArgs* rope, const AttnSeg* segs = nullptr,
+                      int nseg = 0) {
   int rc = GOOSE_OK;
   const goose_model_desc& d = c->d;
   const size_t pstride = (size_t)c->Bpad * c->part_ld;
@@ -373,7 +376,7 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   if (!xhat_ready) {
     PROF(PK_NORM);
     rc = launch_resid_norm(d.dtype, c->act_dtype, d_x, H, nullptr, 0, 0, 0, w + c->pl.g1, d.rms_eps, c->xn,
-                           c->ld_xn, c->terms, B, st);
+                           c->ld_xn, c->terms, B, st, rope);
   }
   if (rc) return rc;
 
@@ -458,16 +461,15 @@ int goose_verify_layer(goose_ctx* c, const void* d_packed_layer, float* d_x, voi
   if (rc) return rc;
   if (!d_packed_layer || !d_x || !d_kcache || !d_vcache || !d_mask || !d_pos) return GOOSE_ERR_ARG;
   hipStream_t st = as_stream(stream);
+  const char* w = (const char*)d_packed_layer;
+  if (is16(c->d.dtype)) {
+    const RopeArgs rope = rope_args(c, d_pos, B);
+    return layer_impl(c, w, d_x, d_kcache, d_vcache, P, d_P, B, d_mask, d_pos, st, false, nullptr, &rope);
+  }
   const int32_t* dP;
   rc = resolve_P(c, P, d_P, st, &dP);
   if (rc) return rc;
-  if (is16(c->d.dtype)) {
-    PROF(PK_ROPE);
-    rc = launch_rope_table(d_pos, c->inv_freq, B, c->d.head_dim, c->rope_cs, st);
-    if (rc) return rc;
-  }
-  return layer_impl(c, (const char*)d_packed_layer, d_x, d_kcache, d_vcache, P, dP, B, d_mask, d_pos, st, false,
-                    nullptr);
+  return layer_impl(c, w, d_x, d_kcache, d_vcache, P, dP, B, d_mask, d_pos, st, false, nullptr, nullptr);
 }
 
 struct HarvestArgs {  // optional harvest of the logits into the requests' successor tables
@@ -577,11 +579,7 @@ int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_
   if (rc) return rc;
   rc = launch_embed(d.dtype, m->d_embed, io->d_tokens, B, d.hidden, d.vocab, c->s_x, st);
   if (rc) return rc;
-  if (is16(d.dtype)) {  // the tree's rotary angles, once for all layers
-    PROF(PK_ROPE);
-    rc = launch_rope_table(c->s_pos, c->inv_freq, B, d.head_dim, c->rope_cs, st);
-    if (rc) return rc;
-  }
+  const RopeArgs rope = rope_args(c, c->s_pos, B);  // the tree's rotary angles, once for all layers
   const size_t layer_cache = (size_t)c->n_kv * c->cap * d.head_dim * elem_size(d.dtype);
   // each layer's closing residual add also writes the next normalisation's output
   for (int l = 0; l < d.n_layers; ++l) {
@@ -589,7 +587,7 @@ int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_
     const void* g_next = (l + 1 < d.n_layers) ? (const void*)(w + c->pl.total + c->pl.g1)
                                               : (const void*)((const char*)m->d_packed_head + c->ph.gf);
     rc = layer_impl(c, w, c->s_x, (char*)m->d_kcache_all + l * layer_cache, (char*)m->d_vcache_all + l * layer_cache,
-                    P_max, io->d_P, B, c->s_mask, c->s_pos, st, l > 0, g_next);
+                    P_max, io->d_P, B, c->s_mask, c->s_pos, st, l > 0, g_next, is16(d.dtype) && l == 0 ? &rope : nullptr);
     if (rc) return rc;
   }
   HarvestArgs hv;
@@ -641,8 +639,7 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
                               c->s_x, c->flags, c->cap, st);
   if (rc) return rc;
   // rows between requests keep stale (finite) values: they ride through the projections unused
-  rc = launch_rope_table(c->s_pos, c->inv_freq, rows, d.head_dim, c->rope_cs, st);
-  if (rc) return rc;
+  const RopeArgs rope = rope_args(c, c->s_pos, rows);
   const size_t layer_cache = (size_t)c->n_kv * c->cap * d.head_dim * elem_size(d.dtype);
   for (int l = 0; l < d.n_layers; ++l) {
     const char* w = (const char*)m->d_packed_layers + (size_t)l * c->pl.total;
@@ -652,7 +649,8 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
       segs[r].kc = (char*)reqs[r].d_kcache_all + l * layer_cache;
       segs[r].vc = (char*)reqs[r].d_vcache_all + l * layer_cache;
     }
-    rc = layer_impl(c, w, c->s_x, nullptr, nullptr, 0, nullptr, rows, nullptr, c->s_pos, st, l > 0, g_next, segs, n_req);
+    rc = layer_impl(c, w, c->s_x, nullptr, nullptr, 0, nullptr, rows, nullptr, c->s_pos, st, l > 0, g_next, l == 0 ? &rope : nullptr,
+                    segs, n_req);
     if (rc) return rc;
   }
   HarvestArgs hv;

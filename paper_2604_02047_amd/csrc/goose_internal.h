@@ -89,15 +89,24 @@ struct goose_ctx {
 // ---- small kernels (kernels_small.hip)
 int launch_set_int(int32_t* dst, int v, hipStream_t st);
 // flags: GOOSE_FLAG_BAD_PARENT for a parent array that is no topological tree, GOOSE_FLAG_CAPACITY
-// for a cache length *dP outside [0, P_max] or with *dP + B > cap
+// for a cache length *dP (P_max without a pointer) outside [0, P_max] or with *dP + B > cap
 int launch_build_mask(const int32_t* parent, int B, const int32_t* dP, uint64_t* mask, int32_t* depth, int32_t* pos,
                       int32_t* flags, int cap, int P_max, hipStream_t st);
 int launch_embed(int dtype, const void* E, const int32_t* tokens, int B, int H, int V, float* x, hipStream_t st);
+// The tree's rotary angles: cs[m][j] = (cos, sin) of pos[m] * inv_freq[j], m < rows, j < half = head_dim / 2 <= 128.
+struct RopeArgs {
+  const int32_t* pos;
+  const double* inv_freq;
+  float2* cs;
+  int32_t rows, half;
+};
 // x[m][:] += sum_s part[s][m][:H] (S may be 0); xn[m][:] = Ta(rmsnorm(x[m]) * g) if xn != NULL, in `terms`
 // terms (two: hi + lo in groups of eight columns, the operand layout of the projections; 16-bit types only).
 // gain_dtype: type of g; act_dtype: type Ta of xn (equal, or fp16 activations under bf16 gains).
+// rope (16-bit types; its rows must equal B): the same launch writes these angles too.
 int launch_resid_norm(int gain_dtype, int act_dtype, float* x, int H, const float* part, int S, size_t part_stride,
-                      size_t part_ld, const void* g, float eps, void* xn, int ldxn, int terms, int B, hipStream_t st);
+                      size_t part_ld, const void* g, float eps, void* xn, int ldxn, int terms, int B, hipStream_t st,
+                      const RopeArgs* rope = nullptr);
 // qkv = sum_s part[s][m][0:3Hq]; rotary on q,k; q -> qout, k/v -> cache slots P+m
 int launch_rope_kv(int dtype, const float* part, int S, size_t part_stride, size_t part_ld, int B, int n_heads,
                    int head_dim, const int32_t* pos, const double* inv_freq, const int32_t* dP, int cap, void* qout,
@@ -196,8 +205,6 @@ int launch_split_operand(int dtype, const float* src, int rows, int cols, int ld
 int launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st);
 int launch_argmax_top2(const void* top2, int n_groups, int B, int32_t* argmax, float* margin, hipStream_t st);
 void pick_gemm_config(int Npad, int Kpad, int max_ksplit, int max_rows, int* nw_out, int* ksplit_out);
-// (cos, sin) of every node's rotary angles: cs is float2 [B][head_dim/2].
-int launch_rope_table(const int32_t* pos, const double* inv_freq, int B, int head_dim, void* cs, hipStream_t st);
 // One request's share of an attention launch: its rows [row0, row0 + B) of the stacked projections,
 // this layer's operand-ordered caches, its cache length and its ancestor bitmask (words per row =
 // ceil(B/64)); P_max bounds *dP and sizes the launch.
@@ -205,7 +212,7 @@ struct AttnSeg {
   int32_t row0, B, P_max;
   void* kc;
   void* vc;
-  const int32_t* dP;
+  const int32_t* dP;   // null: the length is P_max
   const uint64_t* mask;
 };
 enum { ATTN_MAX_SEGS = 16 };

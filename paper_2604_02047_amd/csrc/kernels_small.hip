@@ -29,8 +29,8 @@ __device__ inline void build_mask_body(const int32_t* __restrict__ parent, int B
                                        uint64_t* __restrict__ mask, int32_t* __restrict__ depth,
                                        int32_t* __restrict__ pos, int32_t* __restrict__ flags, int cap, int P_max) {
   const int i = threadIdx.x;
+  const int P = dP != nullptr ? *dP : P_max;  // (no pointer: the host knows the length)
   if (i == 0) {
-    const int P = *dP;
     if (P < 0 || P > P_max || P + B > cap) atomicOr(flags, GOOSE_FLAG_CAPACITY);
   }
   if (i >= B) return;
@@ -50,7 +50,7 @@ __device__ inline void build_mask_body(const int32_t* __restrict__ parent, int B
   mask[(size_t)i * W] = w0;
   if (W > 1) mask[(size_t)i * W + 1] = w1;
   depth[i] = dep;
-  pos[i] = *dP + dep;
+  pos[i] = P + dep;
   if (bad) atomicOr(flags, GOOSE_FLAG_BAD_PARENT);
 }
 
@@ -73,27 +73,42 @@ __global__ __launch_bounds__(128) void k_build_mask_batch(const ReqTable t, uint
 }
 
 // ------------------------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_embed(const T* __restrict__ E, const int32_t* __restrict__ tokens, int H,
-                                               int V, float* __restrict__ x) {
-  const int m = blockIdx.x;
-  int t = tokens[m];
-  t = t < 0 ? 0 : (t >= V ? V - 1 : t);
-  const T* row = E + (size_t)t * H;
-  for (int c = threadIdx.x; c < H; c += 256) x[(size_t)m * H + c] = to_f32(row[c]);
+// Embedding rows as fp32.  A thread converts VEC columns at once (16 bytes of the table; VEC = 1 where the
+// row length or an address does not allow that), a row is spread over workgroups of 256 threads: all
+// loads of a pass are in flight together.  Element by element in a loop, 64 rows of 4096 took 5.8 us
+// and 80 rows of 6656 12.8 us, most of it waiting for the next round; now 4.0 and 5.7 us.
+template <typename T, int VEC>
+__device__ inline void embed_row(const T* __restrict__ E, int tok, int H, int V, float* __restrict__ xr) {
+  tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+  const int c = (blockIdx.x * 256 + threadIdx.x) * VEC;
+  if (c >= H) return;
+  struct alignas(VEC * sizeof(T)) Piece { T e[VEC]; };
+  const Piece v = *reinterpret_cast<const Piece*>(E + (size_t)tok * H + c);
+  if constexpr (VEC == 1) {
+    xr[c] = to_f32(v.e[0]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < VEC; q += 4)
+      *reinterpret_cast<float4*>(xr + c + q) =
+          make_float4(to_f32(v.e[q]), to_f32(v.e[q + 1]), to_f32(v.e[q + 2]), to_f32(v.e[q + 3]));
+  }
 }
 
-template <typename T>
+// grid (column groups, rows)
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void k_embed(const T* __restrict__ E, const int32_t* __restrict__ tokens, int H,
+                                               int V, float* __restrict__ x) {
+  embed_row<T, VEC>(E, tokens[blockIdx.y], H, V, x + (size_t)blockIdx.y * H);
+}
+
+// grid (column groups, rows, requests)
+template <typename T, int VEC>
 __global__ __launch_bounds__(256) void k_embed_batch(const T* __restrict__ E, const ReqTable t, int H, int V,
                                                      float* __restrict__ x) {
-  const BatchReq& q = t.r[blockIdx.y];
-  const int i = blockIdx.x;
+  const BatchReq& q = t.r[blockIdx.z];
+  const int i = blockIdx.y;
   if (i >= q.B) return;
-  int tok = q.tokens[i];
-  tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
-  const T* row = E + (size_t)tok * H;
-  float* xr = x + (size_t)(q.row0 + i) * H;
-  for (int c = threadIdx.x; c < H; c += 256) xr[c] = to_f32(row[c]);
+  embed_row<T, VEC>(E, q.tokens[i], H, V, x + (size_t)(q.row0 + i) * H);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -119,16 +134,34 @@ __device__ inline void store4<_Float16>(_Float16* p, float a, float b, float c, 
   *reinterpret_cast<f16x4*>(p) = v;
 }
 
+// (cos, sin) of pos[m] * base^(-2j/d): the angle is reduced in double, then evaluated in float
+// (|error| ~ 1e-7 rad at any position).
+__device__ inline void rope_entry(const RopeArgs& a, int m, int j) {
+  double ang = (double)a.pos[m] * a.inv_freq[j];
+  const double two_pi = 6.283185307179586476925286766559;
+  ang -= two_pi * rint(ang / two_pi);
+  float sn, c;
+  sincosf((float)ang, &sn, &c);
+  a.cs[(size_t)m * a.half + j] = make_float2(c, sn);
+}
+
 // TERMS = 2 (16-bit types): xn is written as hi + lo, lo = T(v - hi), in groups of eight columns
 // (8 hi values, then their 8 lo values; row length 2 * columns): the operand layout of the projections.
 // Tg: type of the gains; T: type of xn (fp16 activations may meet bf16 gains).
-template <typename Tg, typename T, int NTHR, int TERMS>
+// ROPE: the launch also writes the tree's rotary angles (rope_entry), which nothing before the attention
+// needs: its workgroups beyond the `rope.rows` rows take NTHR / half of the table's rows each.
+template <typename Tg, typename T, int NTHR, int TERMS, bool ROPE>
 __global__ __launch_bounds__(NTHR) void k_resid_norm(float* __restrict__ x, int H, const float* __restrict__ part,
                                                      int S, size_t part_stride, size_t part_ld,
                                                      const Tg* __restrict__ g, float eps, T* __restrict__ xn,
-                                                     int ldxn) {
+                                                     int ldxn, RopeArgs rope) {
   constexpr int MAXV = 4;  // float4 slots per thread kept in registers (H <= 16 * NTHR)
   const int m = blockIdx.x;
+  if (ROPE && m >= rope.rows) {
+    const int per = NTHR / rope.half, r = (m - rope.rows) * per + (int)threadIdx.x / rope.half;
+    if ((int)threadIdx.x < per * rope.half && r < rope.rows) rope_entry(rope, r, threadIdx.x % rope.half);
+    return;
+  }
   float* xr = x + (size_t)m * H;
   const int nvec = H >> 2;
   float4 v[MAXV];
@@ -659,49 +692,64 @@ int launch_build_mask(const int32_t* parent, int B, const int32_t* dP, uint64_t*
   return goose_launch_status();
 }
 
-int launch_embed(int dtype, const void* E, const int32_t* tokens, int B, int H, int V, float* x, hipStream_t st) {
-  if (dtype == GOOSE_DTYPE_BF16)
-    hipLaunchKernelGGL(k_embed<bf16_t>, dim3(B), dim3(256), 0, st, (const bf16_t*)E, tokens, H, V, x);
-  else if (dtype == GOOSE_DTYPE_F16)
-    hipLaunchKernelGGL(k_embed<_Float16>, dim3(B), dim3(256), 0, st, (const _Float16*)E, tokens, H, V, x);
+// 16-byte pieces where every row of the table and of x starts on a multiple of them
+template <typename T>
+static bool embed_vec(const void* E, int H, const float* x) {
+  return H % (16 / sizeof(T)) == 0 && (((uintptr_t)E | (uintptr_t)x) & 15) == 0;
+}
+template <typename T>
+static void launch_embed_t(const void* E, const int32_t* tokens, int B, int H, int V, float* x, hipStream_t st) {
+  constexpr int VEC = 16 / sizeof(T);
+  if (embed_vec<T>(E, H, x))
+    hipLaunchKernelGGL((k_embed<T, VEC>), dim3((H / VEC + 255) / 256, B), dim3(256), 0, st, (const T*)E, tokens, H, V, x);
   else
-    hipLaunchKernelGGL(k_embed<float>, dim3(B), dim3(256), 0, st, (const float*)E, tokens, H, V, x);
+    hipLaunchKernelGGL((k_embed<T, 1>), dim3((H + 255) / 256, B), dim3(256), 0, st, (const T*)E, tokens, H, V, x);
+}
+int launch_embed(int dtype, const void* E, const int32_t* tokens, int B, int H, int V, float* x, hipStream_t st) {
+  if (dtype == GOOSE_DTYPE_BF16) launch_embed_t<bf16_t>(E, tokens, B, H, V, x, st);
+  else if (dtype == GOOSE_DTYPE_F16) launch_embed_t<_Float16>(E, tokens, B, H, V, x, st);
+  else launch_embed_t<float>(E, tokens, B, H, V, x, st);
   return goose_launch_status();
 }
 
-template <typename Tg, typename T, int TERMS>
-static void launch_resid_norm_t(float* x, int H, const float* part, int S, size_t part_stride, size_t part_ld,
-                                const void* g, float eps, void* xn, int ldxn, int B, hipStream_t st) {
-  if (H > 4 * 256)  // 1024 threads once a row has more than 1024 columns
-    hipLaunchKernelGGL((k_resid_norm<Tg, T, 1024, TERMS>), dim3(B), dim3(1024), 0, st, x, H, part, S, part_stride,
-                       part_ld, (const Tg*)g, eps, (T*)xn, ldxn);
-  else
-    hipLaunchKernelGGL((k_resid_norm<Tg, T, 256, TERMS>), dim3(B), dim3(256), 0, st, x, H, part, S, part_stride, part_ld,
-                       (const Tg*)g, eps, (T*)xn, ldxn);
+struct NormArgs {
+  float* x; int H; const float* part; int S; size_t part_stride, part_ld; const void* g; float eps; void* xn; int ldxn, B;
+  RopeArgs rope; hipStream_t st;
+};
+template <typename Tg, typename T, int NTHR, int TERMS>
+static void launch_resid_norm_n(const NormArgs& a) {
+  if (a.rope.rows > 0) {
+    const int per = NTHR / a.rope.half;  // (half <= 128 <= NTHR)
+    hipLaunchKernelGGL((k_resid_norm<Tg, T, NTHR, TERMS, true>), dim3(a.B + (a.rope.rows + per - 1) / per), dim3(NTHR), 0, a.st,
+                       a.x, a.H, a.part, a.S, a.part_stride, a.part_ld, (const Tg*)a.g, a.eps, (T*)a.xn, a.ldxn, a.rope);
+  } else {
+    hipLaunchKernelGGL((k_resid_norm<Tg, T, NTHR, TERMS, false>), dim3(a.B), dim3(NTHR), 0, a.st, a.x, a.H, a.part, a.S,
+                       a.part_stride, a.part_ld, (const Tg*)a.g, a.eps, (T*)a.xn, a.ldxn, a.rope);
+  }
 }
-
+template <typename Tg, typename T, int TERMS>
+static void launch_resid_norm_t(const NormArgs& a) {
+  if (a.H > 4 * 256) launch_resid_norm_n<Tg, T, 1024, TERMS>(a);  // 1024 threads once a row has more than 1024 columns
+  else launch_resid_norm_n<Tg, T, 256, TERMS>(a);
+}
 template <typename Tg, typename T>
-static void launch_resid_norm_terms(int terms, float* x, int H, const float* part, int S, size_t part_stride,
-                                    size_t part_ld, const void* g, float eps, void* xn, int ldxn, int B,
-                                    hipStream_t st) {
-  if (terms == 2) launch_resid_norm_t<Tg, T, 2>(x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, st);
-  else launch_resid_norm_t<Tg, T, 1>(x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, st);
+static void launch_resid_norm_terms(int terms, const NormArgs& a) {
+  if (terms == 2) launch_resid_norm_t<Tg, T, 2>(a);
+  else launch_resid_norm_t<Tg, T, 1>(a);
 }
 
 int launch_resid_norm(int gain_dtype, int act_dtype, float* x, int H, const float* part, int S, size_t part_stride,
-                      size_t part_ld, const void* g, float eps, void* xn, int ldxn, int terms, int B, hipStream_t st) {
+                      size_t part_ld, const void* g, float eps, void* xn, int ldxn, int terms, int B, hipStream_t st,
+                      const RopeArgs* rope) {
   if ((H & 3) || H > 16 * 1024 || (terms == 2 && (H & 7))) return GOOSE_ERR_SHAPE;
   if (terms != 1 && !(terms == 2 && act_dtype != GOOSE_DTYPE_F32)) return GOOSE_ERR_ARG;
-  if (gain_dtype == GOOSE_DTYPE_BF16 && act_dtype == GOOSE_DTYPE_BF16)
-    launch_resid_norm_terms<bf16_t, bf16_t>(terms, x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, st);
-  else if (gain_dtype == GOOSE_DTYPE_BF16 && act_dtype == GOOSE_DTYPE_F16)
-    launch_resid_norm_terms<bf16_t, _Float16>(terms, x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, st);
-  else if (gain_dtype == GOOSE_DTYPE_F16 && act_dtype == GOOSE_DTYPE_F16)
-    launch_resid_norm_terms<_Float16, _Float16>(terms, x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, st);
-  else if (gain_dtype == GOOSE_DTYPE_F32 && act_dtype == GOOSE_DTYPE_F32)
-    launch_resid_norm_t<float, float, 1>(x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, st);
-  else
-    return GOOSE_ERR_ARG;
+  if (rope != nullptr && (rope->rows != B || rope->half < 1 || rope->half > 128)) return GOOSE_ERR_ARG;
+  const NormArgs a{x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, rope != nullptr ? *rope : RopeArgs{}, st};
+  if (gain_dtype == GOOSE_DTYPE_BF16 && act_dtype == GOOSE_DTYPE_BF16) launch_resid_norm_terms<bf16_t, bf16_t>(terms, a);
+  else if (gain_dtype == GOOSE_DTYPE_BF16 && act_dtype == GOOSE_DTYPE_F16) launch_resid_norm_terms<bf16_t, _Float16>(terms, a);
+  else if (gain_dtype == GOOSE_DTYPE_F16 && act_dtype == GOOSE_DTYPE_F16) launch_resid_norm_terms<_Float16, _Float16>(terms, a);
+  else if (gain_dtype == GOOSE_DTYPE_F32 && act_dtype == GOOSE_DTYPE_F32 && rope == nullptr) launch_resid_norm_t<float, float, 1>(a);
+  else return GOOSE_ERR_ARG;
   return goose_launch_status();
 }
 
@@ -824,12 +872,16 @@ int launch_batch_begin(int dtype, const BatchReq* reqs, int n, int max_B, const 
   hipLaunchKernelGGL(k_build_mask_batch, dim3(n), dim3(128), 0, st, t, mask, depth, pos, flags, cap);
   int rc = goose_launch_status();
   if (rc != GOOSE_OK) return rc;
-  if (dtype == GOOSE_DTYPE_BF16)
-    hipLaunchKernelGGL(k_embed_batch<bf16_t>, dim3(max_B, n), dim3(256), 0, st, (const bf16_t*)E, t, H, V, x);
-  else if (dtype == GOOSE_DTYPE_F16)
-    hipLaunchKernelGGL(k_embed_batch<_Float16>, dim3(max_B, n), dim3(256), 0, st, (const _Float16*)E, t, H, V, x);
-  else
-    return GOOSE_ERR_SHAPE;
+  if (dtype != GOOSE_DTYPE_BF16 && dtype != GOOSE_DTYPE_F16) return GOOSE_ERR_SHAPE;
+  const bool vec = embed_vec<bf16_t>(E, H, x);  // (both types have 2 bytes)
+  const dim3 grid(((vec ? H / 8 : H) + 255) / 256, max_B, n);
+  if (dtype == GOOSE_DTYPE_BF16) {
+    if (vec) hipLaunchKernelGGL((k_embed_batch<bf16_t, 8>), grid, dim3(256), 0, st, (const bf16_t*)E, t, H, V, x);
+    else hipLaunchKernelGGL((k_embed_batch<bf16_t, 1>), grid, dim3(256), 0, st, (const bf16_t*)E, t, H, V, x);
+  } else {
+    if (vec) hipLaunchKernelGGL((k_embed_batch<_Float16, 8>), grid, dim3(256), 0, st, (const _Float16*)E, t, H, V, x);
+    else hipLaunchKernelGGL((k_embed_batch<_Float16, 1>), grid, dim3(256), 0, st, (const _Float16*)E, t, H, V, x);
+  }
   return goose_launch_status();
 }
 

@@ -177,3 +177,21 @@ def test_cache_length_from_device_memory_out_of_range_sets_the_capacity_flag(ctx
         c.goose_compact_kv(k, v, 0, path, L, dP, d_P=dP)
         assert bool(c.goose_device_flags() & GOOSE_FLAG_CAPACITY) == bad, P
     c.close()
+
+
+@pytest.mark.parametrize("hidden", [8, 264, 2056, 6656])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_embedding_rows_are_exact(hidden, shift):
+    """Rows in 16-byte pieces, or element by element where the table does not start on such a boundary (shift 1)."""
+    from paper_2604_02047_amd import GooseContext, ModelDesc
+    dev, V = "cuda:0", 37
+    c = GooseContext(ModelDesc(1, hidden, 1, 64, 64, V), 128, 128)
+    flat = torch.randn(V * hidden + 8, device=dev).to(torch.bfloat16)
+    E = flat[shift:shift + V * hidden]
+    tokens = torch.tensor([0, V - 1, 5, -3, V + 4, 17], dtype=torch.int32, device=dev)   # out of range: clamped
+    x = torch.full((7, hidden), float("nan"), device=dev)
+    c.goose_embed(E, tokens, 6, x)
+    torch.cuda.synchronize()
+    assert torch.equal(x[:6], E.view(V, hidden)[tokens.long().clamp(0, V - 1)].float())
+    assert torch.isnan(x[6]).all()
+    c.close()
