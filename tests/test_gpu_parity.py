@@ -159,6 +159,25 @@ def test_tiny_fp32_empty_prefix_and_big_trees():
     gm.ctx.close()
 
 
+@pytest.mark.parametrize("hidden,heads,head_dim,ffn,vocab", [(36, 1, 40, 45, 77), (512, 2, 256, 130, 301), (8, 3, 8, 9, 50)])
+def test_fp32_odd_shapes(hidden, heads, head_dim, ffn, vocab):
+    """Inner dimensions that are no multiple of a 16-byte piece or of a wavefront, the smallest and the largest head size,
+    a prefix that is no multiple of anything, row counts around the groups of eight."""
+    shape = gi.ModelShape("f32odd", 2, hidden, heads, head_dim, ffn, vocab, dtype="f32")
+    tm = torch_model(shape, seed=3, gain_jitter=0.1)
+    om = oracle_model(shape, tm)
+    gm = gpu_model(shape, tm, max_B=128, cap=576)
+    last = _gpu_prefill(gm, gi.prefix_tokens(4, 333, shape.vocab), 64)
+    root = int(last["argmax"][-1].item())
+    for n, tree in enumerate([gi.tree_single(), gi.tree_random(9, 1, spine_len=3), gi.tree_random(33, 2, spine_len=8)]):
+        tokens = np.arange(tree.B, dtype=np.int32) * 7 % shape.vocab
+        tokens[0] = root
+        cache = device_cache_as_oracle(gm, gm.P)
+        g, o, decisive = _compare_step(shape, gm, om, cache, tokens, tree, TOL["f32"])
+        root = g["bonus"]
+    gm.ctx.close()
+
+
 @pytest.mark.parametrize("shape_name", ["tiny_bf16", "small_gqa_qknorm_f16"])
 def test_16bit_empty_prefix_and_big_trees(shape_name):
     """MFMA path from an empty cache (no prefix blocks at all, then a ragged first block): every tree shape."""
