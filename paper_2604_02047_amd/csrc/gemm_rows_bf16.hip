@@ -299,10 +299,16 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const typename Mma16<F16>:
       const float* crow = ct + (lane & 31) * CT_ROW + hh * 32;
       float v1 = -INFINITY, v2 = -INFINITY;
       int i1 = INT_MAX;
-      for (int cc = 0; cc < c_end; ++cc) {
-        const float v = crow[cc];
-        if (v > v1) { v2 = v1; v1 = v; i1 = col0 + cc; }
-        else v2 = fmaxf(v2, v);
+      for (int c0 = 0; c0 < c_end; c0 += 8) {  // (eight reads in flight: 512 x 128256 542 -> 534 us)
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = crow[c0 + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float x = c0 + e < c_end ? v[e] : -INFINITY;
+          if (x > v1) { v2 = v1; v1 = x; i1 = col0 + c0 + e; }
+          else v2 = fmaxf(v2, x);
+        }
       }
       // the second tile's columns follow the first's
       const float ov1 = __shfl_xor(v1, 32, 64), ov2 = __shfl_xor(v2, 32, 64);

@@ -318,14 +318,21 @@ __global__ __launch_bounds__(256) void k_argmax(const float* __restrict__ logits
 }
 
 // Same from the per-workgroup reductions of the LM-head kernel (groups cover ascending column ranges).
-__global__ __launch_bounds__(64) void k_argmax_top2(const float4* __restrict__ top2, int n_groups,
-                                                    int32_t* __restrict__ argmax, float* __restrict__ margin) {
+// Four wavefronts, four records of a thread in flight at a time: 64 rows of 1002 records were walked by one
+// wavefront and one record after the other (7.7 us for 128256 columns; now 5.0).
+__global__ __launch_bounds__(256) void k_argmax_top2(const float4* __restrict__ top2, int n_groups,
+                                                     int32_t* __restrict__ argmax, float* __restrict__ margin) {
+  constexpr int U = 4;
   const int m = blockIdx.x;
+  const float4* row = top2 + (size_t)m * n_groups;
   Top2 t = {-INFINITY, -INFINITY, INT_MAX};
-  for (int g = threadIdx.x; g < n_groups; g += 64) {
-    const float4 e = top2[(size_t)m * n_groups + g];
-    Top2 o = {e.x, e.y, __float_as_int(e.z)};
-    t = top2_merge(t, o);
+  for (int g0 = threadIdx.x; g0 < n_groups; g0 += 256 * U) {
+    float4 e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = row[min(g0 + 256 * u, n_groups - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (g0 + 256 * u < n_groups) t = top2_merge(t, Top2{e[u].x, e[u].y, __float_as_int(e[u].z)});
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -335,9 +342,13 @@ __global__ __launch_bounds__(64) void k_argmax_top2(const float4* __restrict__ t
     o.i1 = __shfl_xor(t.i1, off, 64);
     t = top2_merge(t, o);
   }
+  __shared__ Top2 red[4];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    argmax[m] = t.i1;
-    if (margin) margin[m] = t.v1 - t.v2;
+    const Top2 r = top2_merge(top2_merge(red[0], red[1]), top2_merge(red[2], red[3]));
+    argmax[m] = r.i1;
+    if (margin) margin[m] = r.v1 - r.v2;
   }
 }
 
@@ -813,7 +824,7 @@ int launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st) 
 }
 
 int launch_argmax_top2(const void* top2, int n_groups, int B, int32_t* argmax, float* margin, hipStream_t st) {
-  hipLaunchKernelGGL(k_argmax_top2, dim3(B), dim3(64), 0, st, (const float4*)top2, n_groups, argmax, margin);
+  hipLaunchKernelGGL(k_argmax_top2, dim3(B), dim3(256), 0, st, (const float4*)top2, n_groups, argmax, margin);
   return goose_launch_status();
 }
 

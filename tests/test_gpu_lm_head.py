@@ -77,3 +77,29 @@ def test_ties_go_to_the_lowest_token_id():
     assert np.array_equal(am[pos], np.full(pos.sum(), 400)) and np.array_equal(am[~pos], np.zeros((~pos).sum()))
     assert (mg == 0).all()
     gm.ctx.close()
+
+
+@pytest.mark.parametrize("vocab", [32, 131104, 140000])
+@pytest.mark.parametrize("B", [1, 40])
+def test_argmax_over_many_column_groups(vocab, B):
+    """The per-row reduction takes 1024 of the workgroups' records a round: one record, 1025, and 1094 (a ragged second round);
+    predictions and margins must be those of the logits that the same call returns, ties included."""
+    from paper_2604_02047_amd import GooseContext, ModelDesc
+    dev = "cuda:0"
+    c = GooseContext(ModelDesc(1, 64, 1, 64, 64, vocab), 64, 128)
+    g = torch.Generator(device=dev).manual_seed(vocab + B)
+    head = torch.randn((vocab, 64), generator=g, device=dev).to(torch.bfloat16)
+    head[vocab - 1] = head[vocab // 2]                        # two equal columns far apart
+    packed = torch.zeros(c.goose_packed_lm_head_bytes(), dtype=torch.uint8, device=dev)
+    c.goose_pack_lm_head(torch.ones(64, dtype=torch.bfloat16, device=dev), head, packed)
+    x = torch.randn((B, 64), generator=g, device=dev)
+    x[0] = head[vocab // 2].float()                           # row 0 decides between them: the lower index wins
+    argmax = torch.full((B,), -1, dtype=torch.int32, device=dev)
+    margin, logits = torch.zeros(B, device=dev), torch.zeros((B, vocab), device=dev)
+    c.goose_lm_head_argmax(packed, x, B, argmax, logits, margin)
+    torch.cuda.synchronize()
+    lg = logits.cpu().numpy()
+    assert np.array_equal(argmax.cpu().numpy(), lg.argmax(axis=1)) and int(argmax[0]) == vocab // 2
+    top = np.sort(lg, axis=1)[:, -2:]
+    assert np.array_equal(margin.cpu().numpy(), top[:, 1] - top[:, 0])
+    c.close()
