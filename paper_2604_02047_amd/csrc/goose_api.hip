@@ -250,7 +250,7 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
   A((void**)&c->s_pos, (size_t)c->Bpad * sizeof(int32_t));
   A((void**)&c->s_x, (size_t)c->Bpad * d.hidden * sizeof(float));
   A((void**)&c->flags, sizeof(int32_t));
-  A((void**)&c->s_P, sizeof(int32_t));
+  A((void**)&c->s_P, GOOSE_MAX_REQUESTS * sizeof(int32_t));
   if (rc == GOOSE_OK) {
     std::vector<double> f(d.head_dim / 2);
     for (int j = 0; j < d.head_dim / 2; ++j) f[j] = pow((double)d.rope_base, -2.0 * j / d.head_dim);
@@ -548,7 +548,7 @@ int goose_accept(goose_ctx* c, const int32_t* d_parent, const int32_t* d_tokens,
   if (B < 1) return GOOSE_ERR_ARG;
   if (B > GOOSE_MAX_B) return GOOSE_ERR_CAPACITY;
   return launch_accept(d_parent, d_tokens, d_is_spine_or_null, d_argmax, B, d_accept_len, d_path, d_bonus, nullptr,
-                       as_stream(stream));
+                       nullptr, nullptr, 0, nullptr, as_stream(stream));
 }
 
 int goose_compact_kv(goose_ctx* c, void* d_kcache_all, void* d_vcache_all, int P, const int32_t* d_P,
@@ -599,10 +599,10 @@ int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_
                     true, hv);
   if (rc) return rc;
   rc = launch_accept(io->d_parent, io->d_tokens, io->d_is_spine, io->d_argmax, B, io->d_accept_len, io->d_path,
-                     io->d_bonus, io->d_next_root_or_null, st);
+                     io->d_bonus, io->d_next_root_or_null, io->d_P, c->s_P, c->cap, c->flags, st);
   if (rc) return rc;
   return launch_compact((int)elem_size(d.dtype), m->d_kcache_all, m->d_vcache_all, d.n_layers, c->n_kv, c->cap,
-                        d.head_dim, io->d_P, io->d_path, io->d_accept_len, io->d_P, c->flags, st);
+                        d.head_dim, c->s_P, io->d_path, io->d_accept_len, nullptr, c->flags, st);
 }
 
 int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goose_request* reqs, int n_req,
@@ -661,7 +661,7 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
   }
   rc = lm_head_impl(c, m->d_packed_head, c->s_x, rows, d_argmax_all, nullptr, nullptr, st, true, hv);
   if (rc) return rc;
-  return launch_batch_end(br, n_req, d_argmax_all, d.n_layers, c->n_kv, c->cap, d.head_dim, c->flags, st);
+  return launch_batch_end(br, n_req, d_argmax_all, d.n_layers, c->n_kv, c->cap, d.head_dim, c->s_P, c->flags, st);
 }
 
 // ---- the LM head without a context: its workspace is a static device array --------------------

@@ -82,7 +82,7 @@ struct goose_ctx {
   int32_t* s_pos;    // [128]
   float* s_x;        // [Bpad][hidden]
   int32_t* flags;    // [1]
-  int32_t* s_P;      // [1] holds a host-supplied P for kernels that read it from memory
+  int32_t* s_P;      // [GOOSE_MAX_REQUESTS] a host-supplied P for kernels that read it from memory; the old lengths while a step commits
   goose_prof* prof;  // optional per-kernel event timing
 };
 
@@ -113,8 +113,10 @@ int launch_rope_kv(int dtype, const float* part, int S, size_t part_stride, size
                    int ldq, void* kcache, void* vcache, int32_t* flags, hipStream_t st);
 int launch_swiglu_f32(const float* gu, size_t ld, int F, float* h, int ldh, int B, hipStream_t st);
 int launch_argmax(const float* logits, size_t ld, int V, int B, int32_t* argmax, float* margin, hipStream_t st);
+// dP (or null): cache length, replaced by P + L + 1 after its old value went to *P_old
 int launch_accept(const int32_t* parent, const int32_t* tokens, const uint8_t* is_spine, const int32_t* argmax, int B,
-                  int32_t* accept_len, int32_t* path, int32_t* bonus, int32_t* next_root, hipStream_t st);
+                  int32_t* accept_len, int32_t* path, int32_t* bonus, int32_t* next_root, int32_t* dP, int32_t* P_old, int cap,
+                  int32_t* flags, hipStream_t st);
 // One request of a batched pass as the per-request kernels see it (16-bit storage only).
 struct BatchReq {
   const int32_t* tokens;
@@ -133,9 +135,9 @@ struct BatchReq {
 // mask/depth/positions and embedding rows of all requests (2 launches); E: embedding table.
 int launch_batch_begin(int dtype, const BatchReq* reqs, int n, int max_B, const void* E, int H, int V,
                        uint64_t* mask, int32_t* depth, int32_t* pos, float* x, int32_t* flags, int cap, hipStream_t st);
-// walk, compaction and new cache length of all requests (3 launches)
+// walk, new cache length and compaction of all requests (2 launches); P_old: scratch for the n old lengths
 int launch_batch_end(const BatchReq* reqs, int n, const int32_t* argmax_all, int n_layers, int n_kv_heads, int cap,
-                     int head_dim, int32_t* flags, hipStream_t st);
+                     int head_dim, int32_t* P_old, int32_t* flags, hipStream_t st);
 int launch_compact(int elem_bytes, void* kall, void* vall, int n_layers, int n_heads, int cap, int head_dim,
                    const int32_t* dP, const int32_t* path, const int32_t* accept_len, int32_t* new_P, int32_t* flags,
                    hipStream_t st);

@@ -541,10 +541,13 @@ __global__ __launch_bounds__(256) void k_harvest_merge(int chunks, int table_row
 // at its parent) bids for its parent with the key (branch?1:0, node index); the lowest key
 // wins, i.e. spine children before branch children, lower index first.  Thread 0 then follows
 // the winners from the root; node indices grow along any path, so the walk is finite.
+// dP (or null): the cache length becomes P + L + 1 here, and its old value goes to *P_old, which the commit that
+// follows reads (a kernel of its own for this one word was the last launch of every step).
 __device__ inline void accept_body(const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
                                    const uint8_t* __restrict__ is_spine, const int32_t* __restrict__ argmax, int B,
                                    int32_t* __restrict__ accept_len, int32_t* __restrict__ path,
-                                   int32_t* __restrict__ bonus, int32_t* __restrict__ next_root) {
+                                   int32_t* __restrict__ bonus, int32_t* __restrict__ next_root, int32_t* __restrict__ dP,
+                                   int32_t* __restrict__ P_old, int cap, int32_t* __restrict__ flags) {
   __shared__ int nxt[GOOSE_MAX_B];
   __shared__ int xh[GOOSE_MAX_B];
   __shared__ int L_sh;
@@ -572,6 +575,12 @@ __device__ inline void accept_body(const int32_t* __restrict__ parent, const int
     *accept_len = L;
     *bonus = xh[v];
     if (next_root) *next_root = xh[v];
+    if (dP) {
+      const int p = *dP;
+      if (p < 0 || p + L + 1 > cap) atomicOr(flags, GOOSE_FLAG_CAPACITY);
+      *P_old = p;
+      *dP = p + L + 1;
+    }
     L_sh = L;
   }
   __syncthreads();
@@ -582,33 +591,43 @@ __global__ __launch_bounds__(128) void k_accept(const int32_t* __restrict__ pare
                                                 const uint8_t* __restrict__ is_spine,
                                                 const int32_t* __restrict__ argmax, int B,
                                                 int32_t* __restrict__ accept_len, int32_t* __restrict__ path,
-                                                int32_t* __restrict__ bonus, int32_t* __restrict__ next_root) {
-  accept_body(parent, tokens, is_spine, argmax, B, accept_len, path, bonus, next_root);
+                                                int32_t* __restrict__ bonus, int32_t* __restrict__ next_root,
+                                                int32_t* __restrict__ dP, int32_t* __restrict__ P_old, int cap,
+                                                int32_t* __restrict__ flags) {
+  accept_body(parent, tokens, is_spine, argmax, B, accept_len, path, bonus, next_root, dP, P_old, cap, flags);
 }
 
-__global__ __launch_bounds__(128) void k_accept_batch(const ReqTable t, const int32_t* __restrict__ argmax_all) {
+__global__ __launch_bounds__(128) void k_accept_batch(const ReqTable t, const int32_t* __restrict__ argmax_all,
+                                                      int32_t* __restrict__ P_old, int cap, int32_t* __restrict__ flags) {
   const BatchReq& q = t.r[blockIdx.x];
-  accept_body(q.parent, q.tokens, q.is_spine, argmax_all + q.row0, q.B, q.accept_len, q.path, q.bonus, q.next_root);
+  accept_body(q.parent, q.tokens, q.is_spine, argmax_all + q.row0, q.B, q.accept_len, q.path, q.bonus, q.next_root, q.dP,
+              P_old + blockIdx.x, cap, flags);
 }
 
 // ------------------------------------------------------------------------------------------
 // Commit of the accepted path: cache slot P + path[j] -> slot P + j, j = 1..L, in every layer and head.
-// K[head][slot][d]: one thread owns one 16-byte column chunk of all rows.  Vt[head][d][slot]: one thread
-// owns one d-row and moves single elements along it.  Either way a thread walks j upward and
-// path[j] >= j, so a slot is always read before the same thread can overwrite it.
-__global__ __launch_bounds__(64) void k_compact_k(uint4* __restrict__ kall, int cap, int row_chunks,
-                                                  const int32_t* __restrict__ dP, const int32_t* __restrict__ path,
-                                                  const int32_t* __restrict__ accept_len) {
+// fp32 caches, one launch: workgroup 2i moves the rows of K[head i][slot][d], a thread one 16-byte column
+// chunk of all of them; workgroup 2i+1 the columns of Vt[head i][d][slot], a thread single elements along one
+// d-row.  Either way a thread walks j upward and path[j] >= j, so a slot is always read before the
+// same thread can overwrite it.
+__global__ __launch_bounds__(256) void k_compact_f32(float* __restrict__ kall, float* __restrict__ vall, int cap, int head_dim,
+                                                     const int32_t* __restrict__ dP, const int32_t* __restrict__ path,
+                                                     const int32_t* __restrict__ accept_len) {
   const int c = threadIdx.x;
-  if (c >= row_chunks) return;
-  uint4* base = kall + (size_t)blockIdx.x * cap * row_chunks;  // blockIdx.x = layer * n_heads + head
+  const bool is_v = blockIdx.x & 1;
+  if (c >= (is_v ? head_dim : head_dim / 4)) return;
+  const size_t base = (size_t)(blockIdx.x >> 1) * cap * head_dim;  // (layer * n_heads + head)
+  uint4* kb = reinterpret_cast<uint4*>(kall + base) + c;
+  float* vb = vall + base + (size_t)c * cap;
   const int P = *dP;
   int L = *accept_len;
   if (L > GOOSE_MAX_B - 1) L = GOOSE_MAX_B - 1;
   for (int j = 1; j <= L; ++j) {
     const int src = path[j];
     if (src < j || src >= GOOSE_MAX_B || P + src >= cap) break;  // malformed path: stop, stay in bounds
-    if (src != j) base[(size_t)(P + j) * row_chunks + c] = base[(size_t)(P + src) * row_chunks + c];
+    if (src == j) continue;
+    if (is_v) vb[P + j] = vb[P + src];
+    else kb[(size_t)(P + j) * (head_dim / 4)] = kb[(size_t)(P + src) * (head_dim / 4)];
   }
 }
 
@@ -657,35 +676,11 @@ __global__ __launch_bounds__(D) void k_compact_tiled_batch(const ReqTable t, int
   compact_tiled_body<D>((bf16_t*)q.kall, (bf16_t*)q.vall, cap, q.dP, q.path, q.accept_len);
 }
 
-template <typename T>
-__global__ void k_compact_vt(T* __restrict__ vall, int cap, int head_dim, const int32_t* __restrict__ dP,
-                             const int32_t* __restrict__ path, const int32_t* __restrict__ accept_len) {
-  const int c = threadIdx.x;  // d index
-  T* base = vall + ((size_t)blockIdx.x * head_dim + c) * cap;
-  const int P = *dP;
-  int L = *accept_len;
-  if (L > GOOSE_MAX_B - 1) L = GOOSE_MAX_B - 1;
-  for (int j = 1; j <= L; ++j) {
-    const int src = path[j];
-    if (src < j || src >= GOOSE_MAX_B || P + src >= cap) break;
-    if (src != j) base[P + j] = base[P + src];
-  }
-}
-
 __global__ void k_new_P(const int32_t* dP, const int32_t* accept_len, int32_t* new_P, int cap, int32_t* flags) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     const int p = *dP, l = *accept_len;
     if (p < 0 || l < 0 || p + l + 1 > cap) atomicOr(flags, GOOSE_FLAG_CAPACITY);
     *new_P = p + l + 1;
-  }
-}
-
-__global__ void k_new_P_batch(const ReqTable t, int cap, int32_t* flags) {  // in place: after the compaction has read the old lengths
-  if (threadIdx.x == 0) {
-    const BatchReq& q = t.r[blockIdx.x];
-    const int p = *q.dP, l = *q.accept_len;
-    if (p < 0 || l < 0 || p + l + 1 > cap) atomicOr(flags, GOOSE_FLAG_CAPACITY);
-    *q.dP = p + l + 1;
   }
 }
 
@@ -897,28 +892,27 @@ int launch_batch_begin(int dtype, const BatchReq* reqs, int n, int max_B, const 
 }
 
 int launch_batch_end(const BatchReq* reqs, int n, const int32_t* argmax_all, int n_layers, int n_kv_heads, int cap,
-                     int head_dim, int32_t* flags, hipStream_t st) {
+                     int head_dim, int32_t* P_old, int32_t* flags, hipStream_t st) {
   if (n < 1 || n > GOOSE_MAX_REQUESTS) return GOOSE_ERR_ARG;
-  const ReqTable t = req_table(reqs, n);
-  hipLaunchKernelGGL(k_accept_batch, dim3(n), dim3(128), 0, st, t, argmax_all);
+  ReqTable t = req_table(reqs, n);
+  hipLaunchKernelGGL(k_accept_batch, dim3(n), dim3(128), 0, st, t, argmax_all, P_old, cap, flags);
   int rc = goose_launch_status();
   if (rc != GOOSE_OK) return rc;
+  for (int r = 0; r < n; ++r) t.r[r].dP = P_old + r;  // the walk replaced the lengths
   if (head_dim == 128)
     hipLaunchKernelGGL(k_compact_tiled_batch<128>, dim3(n_layers * n_kv_heads, n), dim3(128), 0, st, t, cap);
   else if (head_dim == 64)
     hipLaunchKernelGGL(k_compact_tiled_batch<64>, dim3(n_layers * n_kv_heads, n), dim3(64), 0, st, t, cap);
   else
     return GOOSE_ERR_SHAPE;
-  rc = goose_launch_status();
-  if (rc != GOOSE_OK) return rc;
-  hipLaunchKernelGGL(k_new_P_batch, dim3(n), dim3(64), 0, st, t, cap, flags);
   return goose_launch_status();
 }
 
 int launch_accept(const int32_t* parent, const int32_t* tokens, const uint8_t* is_spine, const int32_t* argmax, int B,
-                  int32_t* accept_len, int32_t* path, int32_t* bonus, int32_t* next_root, hipStream_t st) {
+                  int32_t* accept_len, int32_t* path, int32_t* bonus, int32_t* next_root, int32_t* dP, int32_t* P_old, int cap,
+                  int32_t* flags, hipStream_t st) {
   hipLaunchKernelGGL(k_accept, dim3(1), dim3(128), 0, st, parent, tokens, is_spine, argmax, B, accept_len, path,
-                     bonus, next_root);
+                     bonus, next_root, dP, P_old, cap, flags);
   return goose_launch_status();
 }
 
@@ -936,14 +930,9 @@ int launch_compact(int elem_bytes, void* kall, void* vall, int n_layers, int n_h
     else
       return GOOSE_ERR_SHAPE;
     rc = goose_launch_status();
-  } else {  // fp32: K[head][slot][d], Vt[head][d][slot]
-    const int row_chunks = head_dim * elem_bytes / 16;  // <= 64 for head_dim <= 256
-    hipLaunchKernelGGL(k_compact_k, dim3(n_layers * n_heads), dim3(64), 0, st, (uint4*)kall, cap, row_chunks, dP, path,
-                       accept_len);
-    rc = goose_launch_status();
-    if (rc != GOOSE_OK) return rc;
-    hipLaunchKernelGGL(k_compact_vt<float>, dim3(n_layers * n_heads), dim3(head_dim), 0, st, (float*)vall, cap,
-                       head_dim, dP, path, accept_len);
+  } else {  // fp32: K[head][slot][d], Vt[head][d][slot]; head_dim <= 256, a multiple of 8
+    hipLaunchKernelGGL(k_compact_f32, dim3(2 * n_layers * n_heads), dim3(head_dim <= 64 ? 64 : 256), 0, st, (float*)kall,
+                       (float*)vall, cap, head_dim, dP, path, accept_len);
     rc = goose_launch_status();
   }
   if (rc != GOOSE_OK) return rc;
