@@ -154,6 +154,29 @@ def test_batched_step_with_long_prefixes_matches_the_oracle(shape_name, sizes, P
     gm.ctx.close()
 
 
+def test_requests_that_share_successor_tables():
+    """Overlapping tables are filled one request after the other: where two requests carry the same token the later one wins."""
+    shape = gi.SHAPES["tiny_bf16"]
+    gm = gpu_model(shape, torch_model(shape, seed=9, gain_jitter=0.1), max_B=64, cap=384, max_rows=128)
+    reqs = _requests(gm, shape, [20, 33], [40, 77], [236, 223])
+    reqs[1]["tokens"][:20] = reqs[0]["tokens"]                      # the same tokens in both
+    _batched(gm, reqs)
+    own = [(q["succ_ids"].clone(), q["succ_scores"].clone(), q["tokens"][:q["B"]].long()) for q in reqs]
+    want_ids, want_sc = own[0][0].clone(), own[0][1].clone()
+    want_ids[own[1][2]], want_sc[own[1][2]] = own[1][0][own[1][2]], own[1][1][own[1][2]]
+    for q in reqs:
+        q["kcache"].copy_(q["k0"])
+        q["vcache"].copy_(q["v0"])
+        q["P"].fill_(q["P0"])
+        q["succ_ids"], q["succ_scores"] = reqs[0]["succ_ids"], reqs[0]["succ_scores"]
+    reqs[0]["succ_ids"].fill_(-1)
+    reqs[0]["succ_scores"].zero_()
+    gm.ctx.goose_verify_step_batched(gm.model_ptrs(), reqs, torch.zeros(128, dtype=torch.int32, device=gm.device))
+    torch.cuda.synchronize()
+    assert torch.equal(reqs[0]["succ_ids"], want_ids) and torch.equal(reqs[0]["succ_scores"], want_sc)
+    gm.ctx.close()
+
+
 def test_batched_step_rejects_what_does_not_fit():
     from paper_2604_02047_amd.binding import GooseError
     shape = gi.SHAPES["tiny_bf16"]
