@@ -279,8 +279,9 @@ int goose_verify_step_batched(goose_ctx* ctx, const goose_model_ptrs* model, con
  * For every node i < B -- accepted or not -- row d_tokens[i] of the two dense successor tables
  * receives the K most likely next tokens under node i's logits: d_succ_ids int32 [vocab][K], ordered
  * by decreasing logit (equal logits: increasing id), and d_succ_scores f32 [vocab][K], their softmax
- * probabilities.  When several nodes carry the same token the highest node index wins; rows of other
- * tokens are untouched; a token outside [0, vocab) writes nothing.  d_logits: f32 [B][ld] DEVICE,
+ * probabilities (NaN where the row's largest logit is infinite; a NaN logit is no successor and counts
+ * in no sum; entries that a row cannot fill get id -1, score 0).  When several nodes carry the same token
+ * the highest node index wins; rows of other tokens are untouched; a token outside [0, vocab) writes nothing.  d_logits: f32 [B][ld] DEVICE,
  * ld >= vocab.  1 <= K <= 16 (the paper uses 10).  The tier-2 (two-token context) table is host-side
  * hashing and not part of this library. */
 int goose_harvest_topk(goose_ctx* ctx, const float* d_logits, size_t ld, const int32_t* d_tokens, int B, int K,

@@ -368,7 +368,8 @@ __global__ __launch_bounds__(256) void k_argmax_top2(const float4* __restrict__ 
 //   tau: every group of four threads knows its best pair; the K-th best of these 64 pairs is a lower
 //   bound of the chunk's K-th best.  At most K groups hold pairs at or above it, so the list of such
 //   pairs never exceeds K * 4 * 32 = 2048 entries whatever the data (it usually holds K and a few).
-// NaNs are no candidates and count in no sum.
+// NaNs are no candidates and count in no sum.  Where the largest logit of a row is infinite its softmax is undefined: the
+// scores are NaN (the ids are still ordered).
 //
 // A pair travels as one 64-bit key, larger = earlier: the value's bits made monotonic (-0 counts as +0) over the complement
 // of the id; 0 stands for "no pair".  Ranking the 160 pairs of a row by comparing (float, int) took three quarters of the merge.
@@ -526,7 +527,7 @@ __global__ __launch_bounds__(256) void k_harvest_merge(int chunks, int table_row
     at += take;
   }
   M = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  float S = 0.f;
+  float S = fabsf(M) == INFINITY ? NAN : 0.f;
 #pragma unroll
   for (int w = 0; w < 4; ++w) S += red[4 + w] * exp_below(red[w], M);
   if (tid < q.K && tok >= 0 && tok < table_rows && !dup) {

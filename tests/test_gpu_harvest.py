@@ -94,6 +94,32 @@ def test_harvest_chunk_edges(V, K):
     c.close()
 
 
+@pytest.mark.parametrize("V", [100, 8192, 20000])
+def test_harvest_of_infinite_logits(V):
+    """Softmax is undefined where a row's largest logit is infinite: its scores are NaN, as in the oracle, and its ids still
+    ordered.  Logits of -inf under a finite largest one have probability 0, also where they fill a whole chunk of the row."""
+    dev, K = "cuda:0", 10
+    c = _ctx(V)
+    logits = np.random.default_rng(V).normal(size=(5, V)).astype(np.float32)
+    logits[0, V - 3] = np.inf
+    logits[1, [2, V // 2, V - 1]] = np.inf
+    logits[2] = -np.inf
+    logits[3, :V // 2] = -np.inf
+    logits[4] = -np.inf
+    logits[4, [5, V - 2]] = [0.5, 1.5]
+    tokens = np.arange(5, dtype=np.int32)
+    d_ids = torch.full((V, K), -1, dtype=torch.int32, device=dev)
+    d_sc = torch.zeros((V, K), dtype=torch.float32, device=dev)
+    c.goose_harvest_topk(torch.from_numpy(logits).to(dev), V, torch.from_numpy(tokens).to(dev), 5, K, d_ids, d_sc)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        ref_ids, ref_sc = orc.harvest_topk(logits.astype(np.float64), tokens, K)
+    assert np.isnan(ref_sc[:3]).all() and np.isfinite(ref_sc[3:]).all()
+    assert np.array_equal(d_ids.cpu().numpy(), ref_ids)
+    np.testing.assert_allclose(d_sc.cpu().numpy(), ref_sc, rtol=2e-5, atol=1e-12)
+    c.close()
+
+
 def test_harvest_inside_the_fused_step():
     shape = gi.SHAPES["small_bf16"]
     tm = torch_model(shape, seed=2, gain_jitter=0.1)
