@@ -404,22 +404,30 @@ __device__ inline void rank_pairs(const hkey* list, int n, int keep, Out out) {
   }
 }
 
-// Grid (chunk, node, request).  pairs: keys [row][chunks][K]; lse: float2 (max, sum) [row][chunks].
-__global__ __launch_bounds__(256) void k_harvest_part(const float* __restrict__ logits, size_t ld, int V, int K,
+// Grid (chunk, node, request).  pairs: keys [row][chunks][k_pairs]; lse: float2 (max, sum) [row][chunks].
+// WHOLE: the row is one chunk (V <= HARVEST_CHUNK), its pairs go straight into the request's tables and nothing is left to merge.
+template <bool WHOLE, int VPT>
+__global__ __launch_bounds__(256) void k_harvest_part(const float* __restrict__ logits, size_t ld, int V, int k_pairs,
                                                       const HarvestTable t, hkey* __restrict__ pairs,
                                                       float2* __restrict__ lse) {
-  __shared__ hkey best[64], list[HARVEST_KMAX * 4 * HARVEST_VPT], tau_s;
+  __shared__ hkey best[64], list[HARVEST_KMAX * 4 * VPT], tau_s;
   __shared__ float red[8];
   __shared__ int n_s;
   const HarvestReq& q = t.r[blockIdx.z];
-  if ((int)blockIdx.y >= q.B) return;
-  const int tid = threadIdx.x, c0 = blockIdx.x * HARVEST_CHUNK;
-  const size_t row = (size_t)q.row0 + blockIdx.y;
+  const int m = blockIdx.y, K = WHOLE ? q.K : k_pairs;
+  if (m >= q.B) return;
+  const int tid = threadIdx.x, c0 = WHOLE ? 0 : blockIdx.x * HARVEST_CHUNK;
+  int tok = 0, tok_t = 0;
+  if (WHOLE) {
+    tok = q.tokens[m];
+    tok_t = tid < q.B ? q.tokens[tid] : 0;
+  }
+  const size_t row = (size_t)q.row0 + m;
   const float* src = logits + row * ld + c0;
   const int nc = min(HARVEST_CHUNK, V - c0);  // columns of this chunk (>= 1)
-  float v[HARVEST_VPT];
+  float v[VPT];
 #pragma unroll
-  for (int u = 0; u < HARVEST_VPT; ++u) v[u] = (tid + u * 256 < nc) ? src[tid + u * 256] : NAN;
+  for (int u = 0; u < VPT; ++u) v[u] = (tid + u * 256 < nc) ? src[tid + u * 256] : NAN;
   if (tid == 0) {
     n_s = 0;
     tau_s = 0;  // (kept if fewer than K groups hold a value: every pair qualifies)
@@ -427,7 +435,7 @@ __global__ __launch_bounds__(256) void k_harvest_part(const float* __restrict__ 
   float bv = -INFINITY;
   int bi = -1;
 #pragma unroll
-  for (int u = 0; u < HARVEST_VPT; ++u)
+  for (int u = 0; u < VPT; ++u)
     if (v[u] > bv || (v[u] == bv && bi < 0)) { bv = v[u]; bi = c0 + tid + u * 256; }  // (ids ascend: '>' keeps the lowest)
   hkey bk = bi < 0 ? 0 : harvest_key(bv, bi);
 #pragma unroll
@@ -451,7 +459,7 @@ __global__ __launch_bounds__(256) void k_harvest_part(const float* __restrict__ 
   }
   float sm = 0.f;
 #pragma unroll
-  for (int u = 0; u < HARVEST_VPT; ++u) sm += v[u] == v[u] ? exp_below(v[u], M) : 0.f;
+  for (int u = 0; u < VPT; ++u) sm += v[u] == v[u] ? exp_below(v[u], M) : 0.f;
   sm = wave_sum(sm);
   if ((tid & 63) == 0) red[4 + (tid >> 6)] = sm;
   __syncthreads();
@@ -460,9 +468,20 @@ __global__ __launch_bounds__(256) void k_harvest_part(const float* __restrict__ 
   const float tv = harvest_value(tau);
   const int ti = harvest_id(tau);
 #pragma unroll
-  for (int u = 0; u < HARVEST_VPT; ++u) {
+  for (int u = 0; u < VPT; ++u) {
     const int c = c0 + tid + u * 256;
     if (v[u] == v[u] && (all || v[u] > tv || (v[u] == tv && c <= ti))) list[atomicAdd(&n_s, 1)] = harvest_key(v[u], c);
+  }
+  if (WHOLE) {
+    const bool dup = __syncthreads_or(tid > m && tid < q.B && tok_t == tok);  // a later node carries the same token
+    if (tok < 0 || tok >= V || dup) return;
+    const int n = n_s;
+    const float S = fabsf(M) == INFINITY ? NAN : red[4] + red[5] + red[6] + red[7];
+    int32_t* ids = q.ids + (size_t)tok * K;
+    float* scores = q.scores + (size_t)tok * K;
+    rank_pairs(list, n, K, [&](int k, hkey p) { ids[k] = harvest_id(p); scores[k] = exp_below(harvest_value(p), M) / S; });
+    if (tid >= n && tid < K) { ids[tid] = -1; scores[tid] = 0.f; }
+    return;
   }
   __syncthreads();
   const size_t slot = row * gridDim.x + blockIdx.x;
@@ -824,9 +843,24 @@ int launch_argmax_top2(const void* top2, int n_groups, int B, int32_t* argmax, f
   return goose_launch_status();
 }
 
+// A vocabulary of one chunk, in one launch.  What bounds it is a chain of steps of which each goes with the logits that
+// a thread holds, so it holds no more than its 256th of the row needs.  With a merge behind it and 32 logits a thread, 64 rows of
+// 1024 / 4096 / 8192 columns took 10.8 / 11.6 / 12.2 us for K = 1 and 11.4 / 12.2 / 13.2 for K = 10; now 4.2 / 5.9 / 8.0 and
+// 4.6 / 6.4 / 8.5 (the kernel that walked each row twice: 5.9 / 6.9 / 9.9 and 16.7 / 17.9 / 20.8).
+static void launch_harvest_whole(const float* logits, size_t ld, int V, const HarvestTable& t, int b, int n, hipStream_t st) {
+  const dim3 grid(1, b, n);
+  if (V <= 4 * 256)
+    hipLaunchKernelGGL((k_harvest_part<true, 4>), grid, dim3(256), 0, st, logits, ld, V, 0, t, nullptr, nullptr);
+  else if (V <= 16 * 256)
+    hipLaunchKernelGGL((k_harvest_part<true, 16>), grid, dim3(256), 0, st, logits, ld, V, 0, t, nullptr, nullptr);
+  else
+    hipLaunchKernelGGL((k_harvest_part<true, HARVEST_VPT>), grid, dim3(256), 0, st, logits, ld, V, 0, t, nullptr, nullptr);
+}
+
 // One launch of k_harvest_part for all requests.  The tables of different requests are normally distinct and one
 // launch of k_harvest_merge fills them all; where two of them overlap (requests that share a table) they are filled one
-// request after the other, so that the later request wins.
+// request after the other, so that the later request wins.  A vocabulary of one chunk needs no merge: the K best of its rows
+// are known in k_harvest_part (launch_harvest_whole).
 int launch_harvest_topk(const float* logits, size_t ld, int V, const HarvestReq* reqs, int n, void* ws, hipStream_t st) {
   if (n < 1 || n > GOOSE_MAX_REQUESTS || ws == nullptr || V < 1) return GOOSE_ERR_ARG;
   HarvestTable t{};
@@ -849,18 +883,25 @@ int launch_harvest_topk(const float* logits, size_t ld, int V, const HarvestReq*
   const int chunks = (V + HARVEST_CHUNK - 1) / HARVEST_CHUNK;
   float2* lse = static_cast<float2*>(ws);
   hkey* pairs = reinterpret_cast<hkey*>(lse + rows * chunks);
-  hipLaunchKernelGGL(k_harvest_part, dim3(chunks, b_max, n), dim3(256), 0, st, logits, ld, V, k_max, t, pairs, lse);
-  int rc = goose_launch_status();
-  if (rc != GOOSE_OK) return rc;
-  if (!overlap) {
-    hipLaunchKernelGGL(k_harvest_merge, dim3(b_max, n), dim3(256), 0, st, chunks, V, k_max, t, pairs, lse);
-    return goose_launch_status();
+  int rc = GOOSE_OK;
+  if (chunks > 1) {
+    hipLaunchKernelGGL((k_harvest_part<false, HARVEST_VPT>), dim3(chunks, b_max, n), dim3(256), 0, st, logits, ld, V, k_max, t,
+                       pairs, lse);
+    rc = goose_launch_status();
+    if (rc != GOOSE_OK) return rc;
   }
+  auto fill = [&](const HarvestTable& reqs_of, int b, int n_of) {
+    if (chunks > 1)
+      hipLaunchKernelGGL(k_harvest_merge, dim3(b, n_of), dim3(256), 0, st, chunks, V, k_max, reqs_of, pairs, lse);
+    else
+      launch_harvest_whole(logits, ld, V, reqs_of, b, n_of, st);
+    return goose_launch_status();
+  };
+  if (!overlap) return fill(t, b_max, n);
   for (int r = 0; r < n; ++r) {
     HarvestTable one{};
     one.r[0] = reqs[r];
-    hipLaunchKernelGGL(k_harvest_merge, dim3(reqs[r].B, 1), dim3(256), 0, st, chunks, V, k_max, one, pairs, lse);
-    rc = goose_launch_status();
+    rc = fill(one, reqs[r].B, 1);
     if (rc != GOOSE_OK) return rc;
   }
   return GOOSE_OK;

@@ -1,12 +1,15 @@
 """Logit harvest into the unigram successor tables (Sec. 4 stage 2; App. C "adjacency table" tier 1,
 "logit harvesting"): the HIP kernel against the oracle on the same logits -- ids bit-exact (also
 under ties and repeated tokens), scores to fp32 round-off -- alone and inside the fused step."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import goose_inputs as gi
 from oracle import goose_oracle as orc
+from paper_2604_02047_amd.binding import load_library
 from util import gpu_model, torch_model
 
 pytestmark = pytest.mark.gpu
@@ -91,6 +94,29 @@ def test_harvest_chunk_edges(V, K):
     ref_ids, ref_sc = orc.harvest_topk(logits.astype(np.float64), tokens, K)
     assert np.array_equal(d_ids.cpu().numpy(), ref_ids)
     np.testing.assert_allclose(d_sc.cpu().numpy(), ref_sc, rtol=2e-5, atol=1e-12)
+    c.close()
+
+
+@pytest.mark.parametrize("V", [7, 1023, 1024, 1025, 4096, 4097, 8192])
+def test_harvest_of_one_chunk(V):
+    """Vocabularies of one chunk: 4, 16 or 32 logits a thread, on both sides of each; the smallest and the largest K."""
+    for K in (1, min(V, 16)):
+        test_harvest_chunk_edges(V, K)
+
+
+@pytest.mark.parametrize("V,launches", [(1000, 1), (8192, 1), (8193, 2)])
+def test_harvest_launches(V, launches):
+    """A row of one chunk has nothing to merge: a second launch would double the time of a small vocabulary."""
+    dev = "cuda:0"
+    c = _ctx(V)
+    logits, tokens = torch.zeros((4, V), device=dev), torch.zeros(4, dtype=torch.int32, device=dev)
+    ids, sc = torch.zeros((V, 1), dtype=torch.int32, device=dev), torch.zeros((V, 1), device=dev)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        c.goose_harvest_topk(logits, V, tokens, 4, 1, ids, sc)
+    n = ctypes.c_size_t(0)
+    assert load_library().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == launches
     c.close()
 
 
