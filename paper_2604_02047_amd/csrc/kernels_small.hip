@@ -317,22 +317,25 @@ __global__ __launch_bounds__(256) void k_argmax(const float* __restrict__ logits
   }
 }
 
-// Same from the per-workgroup reductions of the LM-head kernel (groups cover ascending column ranges).
-// Four wavefronts, four records of a thread in flight at a time: 64 rows of 1002 records were walked by one
-// wavefront and one record after the other (7.7 us for 128256 columns; now 5.0).
-__global__ __launch_bounds__(256) void k_argmax_top2(const float4* __restrict__ top2, int n_groups,
-                                                     int32_t* __restrict__ argmax, float* __restrict__ margin) {
-  constexpr int U = 4;
+// Same from the per-workgroup reductions of the LM-head kernel (groups cover ascending column ranges): NW wavefronts a row, U records
+// of a thread in flight at a time.  The kernel is one trip to memory and little else, so it takes as few rounds as the
+// records allow, and one wavefront, without the exchange through LDS, where that makes one round: 64 rows of 1002 records took 7.7 us
+// with one wavefront and one record after the other, 5.0 with <4, 4>; the head of 64 rows x 1024 columns (8 records, K = 256) takes
+// 10.2 us with <1, 1> and 10.6 with <4, 4>, that of 32768 columns (256 records) 11.2 with <1, 4>, 11.3 with <4, 4>.
+template <int NW, int U>
+__global__ __launch_bounds__(64 * NW) void k_argmax_top2(const float4* __restrict__ top2, int n_groups,
+                                                         int32_t* __restrict__ argmax, float* __restrict__ margin) {
+  constexpr int NTHR = 64 * NW;
   const int m = blockIdx.x;
   const float4* row = top2 + (size_t)m * n_groups;
   Top2 t = {-INFINITY, -INFINITY, INT_MAX};
-  for (int g0 = threadIdx.x; g0 < n_groups; g0 += 256 * U) {
+  for (int g0 = threadIdx.x; g0 < n_groups; g0 += NTHR * U) {
     float4 e[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) e[u] = row[min(g0 + 256 * u, n_groups - 1)];
+    for (int u = 0; u < U; ++u) e[u] = row[min(g0 + NTHR * u, n_groups - 1)];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (g0 + 256 * u < n_groups) t = top2_merge(t, Top2{e[u].x, e[u].y, __float_as_int(e[u].z)});
+      if (g0 + NTHR * u < n_groups) t = top2_merge(t, Top2{e[u].x, e[u].y, __float_as_int(e[u].z)});
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -342,13 +345,17 @@ __global__ __launch_bounds__(256) void k_argmax_top2(const float4* __restrict__ 
     o.i1 = __shfl_xor(t.i1, off, 64);
     t = top2_merge(t, o);
   }
-  __shared__ Top2 red[4];
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
-  __syncthreads();
+  if constexpr (NW > 1) {
+    __shared__ Top2 red[NW];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    t = red[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) t = top2_merge(t, red[w]);
+  }
   if (threadIdx.x == 0) {
-    const Top2 r = top2_merge(top2_merge(red[0], red[1]), top2_merge(red[2], red[3]));
-    argmax[m] = r.i1;
-    if (margin) margin[m] = r.v1 - r.v2;
+    argmax[m] = t.i1;
+    if (margin) margin[m] = t.v1 - t.v2;
   }
 }
 
@@ -839,7 +846,12 @@ int launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st) 
 }
 
 int launch_argmax_top2(const void* top2, int n_groups, int B, int32_t* argmax, float* margin, hipStream_t st) {
-  hipLaunchKernelGGL(k_argmax_top2, dim3(B), dim3(256), 0, st, (const float4*)top2, n_groups, argmax, margin);
+  if (n_groups <= 64)
+    hipLaunchKernelGGL((k_argmax_top2<1, 1>), dim3(B), dim3(64), 0, st, (const float4*)top2, n_groups, argmax, margin);
+  else if (n_groups <= 4 * 64)
+    hipLaunchKernelGGL((k_argmax_top2<1, 4>), dim3(B), dim3(64), 0, st, (const float4*)top2, n_groups, argmax, margin);
+  else
+    hipLaunchKernelGGL((k_argmax_top2<4, 4>), dim3(B), dim3(256), 0, st, (const float4*)top2, n_groups, argmax, margin);
   return goose_launch_status();
 }
 

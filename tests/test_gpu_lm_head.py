@@ -103,3 +103,10 @@ def test_argmax_over_many_column_groups(vocab, B):
     top = np.sort(lg, axis=1)[:, -2:]
     assert np.array_equal(margin.cpu().numpy(), top[:, 1] - top[:, 0])
     c.close()
+
+
+@pytest.mark.parametrize("vocab", [8192, 8224, 32768, 32800])
+def test_argmax_record_counts(vocab):
+    """64 and 65 records a row (one per lane, then four), 256 and 257 (one wavefront, then four)."""
+    for B in (1, 33):
+        test_argmax_over_many_column_groups(vocab, B)
