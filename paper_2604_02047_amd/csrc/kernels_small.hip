@@ -638,10 +638,11 @@ __global__ __launch_bounds__(128) void k_accept_batch(const ReqTable t, const in
 
 // ------------------------------------------------------------------------------------------
 // Commit of the accepted path: cache slot P + path[j] -> slot P + j, j = 1..L, in every layer and head.
-// fp32 caches, one launch: workgroup 2i moves the rows of K[head i][slot][d], a thread one 16-byte column
-// chunk of all of them; workgroup 2i+1 the columns of Vt[head i][d][slot], a thread single elements along one
-// d-row.  Either way a thread walks j upward and path[j] >= j, so a slot is always read before the
-// same thread can overwrite it.
+// fp32 caches, one launch: workgroup 2i moves the rows of K[head i][slot][d], a thread four columns
+// of all of them (a cache may start on any float: no 16-byte alignment is assumed); workgroup 2i+1 the columns of
+// Vt[head i][d][slot], a thread single elements along one d-row.  Either way a thread walks j upward and path[j] >= j, so a
+// slot is always read before the same thread can overwrite it.
+struct Float4Any { float e[4]; };
 __global__ __launch_bounds__(256) void k_compact_f32(float* __restrict__ kall, float* __restrict__ vall, int cap, int head_dim,
                                                      const int32_t* __restrict__ dP, const int32_t* __restrict__ path,
                                                      const int32_t* __restrict__ accept_len) {
@@ -649,7 +650,7 @@ __global__ __launch_bounds__(256) void k_compact_f32(float* __restrict__ kall, f
   const bool is_v = blockIdx.x & 1;
   if (c >= (is_v ? head_dim : head_dim / 4)) return;
   const size_t base = (size_t)(blockIdx.x >> 1) * cap * head_dim;  // (layer * n_heads + head)
-  uint4* kb = reinterpret_cast<uint4*>(kall + base) + c;
+  Float4Any* kb = reinterpret_cast<Float4Any*>(kall + base) + c;
   float* vb = vall + base + (size_t)c * cap;
   const int P = *dP;
   int L = *accept_len;

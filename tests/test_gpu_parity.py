@@ -178,6 +178,32 @@ def test_fp32_odd_shapes(hidden, heads, head_dim, ffn, vocab):
     gm.ctx.close()
 
 
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_fp32_caches_that_start_on_any_float(shift):
+    """The same steps, bit for bit, on caches that do not start on a 16-byte boundary: attention and commit read and move them
+    in pieces of four floats."""
+    shape = gi.SHAPES["tiny"]
+    gm = gpu_model(shape, torch_model(shape, seed=6, gain_jitter=0.1), max_B=64, cap=256)
+    tree = gi.tree_tiny_spine()
+    aligned, results = (gm.kcache, gm.vcache), []
+    for off in (0, shift):
+        flat = [torch.zeros(t.numel() + 4, device=gm.device) for t in aligned]
+        gm.kcache, gm.vcache = (f[off:off + t.numel()].view(t.shape) for f, t in zip(flat, aligned))
+        assert gm.kcache.data_ptr() % 16 == 4 * off
+        gm.set_P(0)
+        last = _gpu_prefill(gm, gi.prefix_tokens(3, 45, shape.vocab), 16)
+        tokens = gi.draft_tokens_uniform(4, tree.parent, shape.vocab, int(last["argmax"][-1].item()))
+        probe = gm.verify_step_calls(tokens, tree.parent, tree.is_spine, commit=False)
+        best = int(probe["argmax"][0].item())            # the root's prediction goes to a branch child: its row moves in the commit
+        tokens[1], tokens[8] = (best + 1) % shape.vocab, best
+        out = gm.verify_step_calls(tokens, tree.parent, tree.is_spine, want_logits=True)
+        results.append((out["logits"], out["path"].tolist(), gm.P, gm.kcache.clone(), gm.vcache.clone()))
+    a, b = results
+    assert torch.equal(a[0], b[0]) and a[1] == b[1] and a[1][:2] == [0, 8] and a[2] == b[2] >= 47
+    assert torch.equal(a[3], b[3]) and torch.equal(a[4], b[4])
+    gm.ctx.close()
+
+
 @pytest.mark.parametrize("shape_name", ["tiny_bf16", "small_gqa_qknorm_f16"])
 def test_16bit_empty_prefix_and_big_trees(shape_name):
     """MFMA path from an empty cache (no prefix blocks at all, then a ragged first block): every tree shape."""
