@@ -36,9 +36,10 @@ int env_int(const char* name, int dflt) {
 }
 
 // ---- optional per-kernel timing with HIP events on the caller's stream -----------------------
-enum ProfKind { PK_NORM = 0, PK_GEMM_QKV, PK_ROPE, PK_ATTN, PK_GEMM_O, PK_GEMM_GATE_UP, PK_GEMM_DOWN, PK_LM_HEAD,
+// (the first PK_NORM launch of a 16-bit pass also writes the tree's rotary angles)
+enum ProfKind { PK_NORM = 0, PK_GEMM_QKV, PK_ATTN, PK_GEMM_O, PK_GEMM_GATE_UP, PK_GEMM_DOWN, PK_LM_HEAD,
                 PK_ARGMAX, PK_HARVEST, PK_MISC, PK_COUNT };
-const char* const kProfNames[PK_COUNT] = {"rmsnorm_residual", "gemm_qkv", "rope_table", "tree_attention", "gemm_o",
+const char* const kProfNames[PK_COUNT] = {"rmsnorm_residual", "gemm_qkv", "tree_attention", "gemm_o",
                                           "gemm_gate_up_swiglu", "gemm_down", "gemm_lm_head", "argmax",
                                           "harvest_topk", "mask_embed_accept_compact"};
 }  // namespace
