@@ -3,12 +3,16 @@ projection and one attention launch per tree-size class; a request's rows never 
 another's, so with the same number of key splits its results equal, bit for bit, what it gives on
 its own.  With a different split count (more requests -> fewer splits per head) the attention sums
 are ordered differently: then every request is held to the oracle's tolerance instead."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
 
 import goose_inputs as gi
 from oracle import goose_oracle as orc
+from paper_2604_02047_amd import ModelDesc
+from paper_2604_02047_amd.runner import GooseModel
 from util import device_cache_as_oracle, gpu_model, oracle_model, torch_model
 from test_gpu_parity import _gpu_prefill, tol_for
 
@@ -113,7 +117,7 @@ def _rows_of(sizes):
                                               ("small_bf16", [100, 128, 70, 96])])
 def test_batched_step_equals_the_requests_alone(shape_name, sizes):
     """Short prefixes: one key split alone and batched, hence identical arithmetic per request
-    (also beyond 128 stacked rows, where the projections run in chunks of 128 rows)."""
+    (also beyond 128 stacked rows, where the projections and the head run a kernel of their own)."""
     shape = gi.SHAPES[shape_name]
     tm = torch_model(shape, seed=7, gain_jitter=0.1)
     gm = gpu_model(shape, tm, max_B=128, cap=384, max_rows=max(128, _rows_of(sizes)))
@@ -174,6 +178,35 @@ def test_requests_that_share_successor_tables():
     gm.ctx.goose_verify_step_batched(gm.model_ptrs(), reqs, torch.zeros(128, dtype=torch.int32, device=gm.device))
     torch.cuda.synchronize()
     assert torch.equal(reqs[0]["succ_ids"], want_ids) and torch.equal(reqs[0]["succ_scores"], want_sc)
+    gm.ctx.close()
+
+
+@pytest.mark.parametrize("vocab,sizes,act_mode", [(1000, [64, 64, 64], 0), (1056, [33, 64, 32, 20], 1),
+                                                  (22100, [32] * 9, 0), (22100, [64] * 6 + [1], 0), (22100, [64] * 6 + [1], 1)])
+def test_many_row_head_on_ragged_vocabularies(vocab, sizes, act_mode):
+    """The LM head of more than 128 rows, in workgroups of 128, 192 and 256 rows (22100 columns are 87 groups of 256): the last group
+    of columns and the last tile end early, and equal columns lie on both sides of a tile border and of a group border.
+    Predictions, walk and harvest must be, bit for bit, those of the requests alone; two-term operands are a whole pass of their own."""
+    shape = gi.ModelShape(f"ragged{vocab}", 2, 256, 4, 64, 688, vocab, dtype="bf16")
+    tm = torch_model(shape, seed=12, gain_jitter=0.1)
+    lows = [31, 255, (vocab - 1) // 256 * 256 - 1, vocab - 2]     # last column of a tile, of a group (twice), and the end
+    for n, i in enumerate(lows):                                  # large, and two by two of opposite sign: one of them leads every row
+        tm["lm_head"][i] = tm["lm_head"][lows[n - 1]] * -1 if n & 1 else tm["lm_head"][i] * 400
+        tm["lm_head"][i + 1] = tm["lm_head"][i]
+    gm = GooseModel(dataclasses.replace(ModelDesc.from_shape(shape), act_mode=act_mode), 64, 384, lambda l: tm["layers"][l],
+                    tm["embed"], tm["lm_head"], tm["final_norm"], max_rows=_rows_of(sizes))
+    reqs = _requests(gm, shape, sizes, [40 + 9 * r for r in range(len(sizes))], [256 - B for B in sizes])
+    alone = _alone(gm, reqs)
+    _batched(gm, reqs)
+    seen = set()
+    for q, a in zip(reqs, alone):
+        assert torch.equal(q["argmax"], a["argmax"]) and torch.equal(q["path"][:q["B"]], a["path"])
+        assert int(q["accept_len"].item()) == a["L"] and int(q["bonus"].item()) == a["bonus"] and int(q["P"].item()) == a["P"]
+        assert torch.equal(q["succ_ids"], a["ids"]) and torch.equal(q["succ_scores"], a["scores"])
+        first = q["succ_ids"][q["tokens"].long(), :2].cpu().numpy()
+        assert (first[:, 1] == first[:, 0] + 1).all()             # the pair in order of its ids, which are not padding columns
+        seen |= set(q["argmax"].tolist())
+    assert seen == set(lows)                                      # the lower of two equal columns wins, and every pair wins somewhere
     gm.ctx.close()
 
 

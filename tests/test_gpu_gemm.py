@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _a_rows(B):
-    """Rows the operand buffer must hold: whole 32-row tiles, whole 128-row chunks beyond 128 rows."""
+    """Rows of the operand buffer: the whole 32-row tiles that the product must be able to read, and more beyond 128 rows."""
     return (B + 31) // 32 * 32 if B <= 128 else (B + 127) // 128 * 128
 
 
@@ -33,7 +33,8 @@ def _operand(a32, rows, Kp, dt, terms, dev):
     return a2, carried[:B, :K].numpy()
 
 
-def _run(B, N, K, nw, ks, seed=0, dt=torch.bfloat16, terms=1):
+def _run(B, N, K, nw, ks, seed=0, dt=torch.bfloat16, terms=1, guard=0):
+    """guard > 0: that many rows behind the last slab, which must stay as they were, like the rows B.. of every slab."""
     dev = "cuda:0"
     gen = torch.Generator(device="cpu").manual_seed(seed)
     Kp, Np, rows = (K + 127) // 128 * 128, (N + 31) // 32 * 32, (B + 31) // 32 * 32
@@ -42,7 +43,8 @@ def _run(B, N, K, nw, ks, seed=0, dt=torch.bfloat16, terms=1):
     ref = a_exact @ w.double().numpy().T
     packed = torch.zeros(g.goose_packed_matrix_bytes(N, K), dtype=torch.uint8, device=dev)
     g.goose_pack_matrix(w.to(dev), N, K, packed)
-    part = torch.full((ks, rows, Np), float("nan"), dtype=torch.float32, device=dev)
+    whole = torch.full((ks * rows + guard, Np), float("nan"), dtype=torch.float32, device=dev)
+    part = whole[:ks * rows].view(ks, rows, Np)
     if terms == 1:
         g.goose_gemm_packed(a, Kp, packed, N, K, B, nw, ks, part)
     else:
@@ -53,6 +55,8 @@ def _run(B, N, K, nw, ks, seed=0, dt=torch.bfloat16, terms=1):
     err = np.abs(out - ref).max()
     # fp32 accumulation of exact bf16 products: only summation-order rounding remains
     assert err <= 2e-5 * scale * max(1.0, np.sqrt(K) / 16), (B, N, K, nw, ks, err, scale)
+    if guard:
+        assert torch.isnan(part[:, B:]).all() and torch.isnan(whole[ks * rows:]).all(), (B, N, K, nw, ks)
 
 
 @pytest.mark.parametrize("B", [1, 16, 33, 64, 80, 128])
@@ -63,8 +67,8 @@ def test_gemm_row_tiles(B):
 
 @pytest.mark.parametrize("B", [129, 200, 256, 300, 512])
 def test_gemm_row_chunks(B):
-    """More than 128 rows: chunks of 128 rows, each its own workgroups (dealt so that the chunks of a
-    column group share an XCD); grids that are no multiple of 8 workgroups, ragged last chunk."""
+    """More than 128 rows: chunks of a workgroup's rows (128 in these grids), dealt so that the chunks of a
+    column group share an XCD; grids that are no multiple of 8 workgroups, ragged last chunk."""
     _run(B, 256, 512, 2, 1)
     _run(B, 288, 1024, 4, 2)
     _run(B, 1000, 1000, 4, 3)
@@ -73,13 +77,33 @@ def test_gemm_row_chunks(B):
 
 @pytest.mark.parametrize("B", [129, 191, 193, 256, 257, 384, 385, 449])
 def test_gemm_many_rows_edges(B):
-    """The many-row kernel picks workgroups of 128, 192 or 256 rows x 256 columns: row counts on both sides of
-    each, fewer columns than one workgroup, a ragged last one, and ranges of 2 to 6 stages through a ring of two or three slots."""
+    """The many-row kernel with fewer columns than one workgroup, a ragged last one, and ranges of 2 to 6 stages.  Grids as small
+    as these always take workgroups of 128 rows x 256 columns (a ring of three slots); test_gemm_tall_workgroups has the others."""
     for K in (128, 256, 384):
         _run(B, 40, K, 4, 1, dt=torch.float16)
         _run(B, 288, K, 4, 1, terms=2)
     _run(B, 2080, 640, 4, 5)
     _run(B, 2080, 896, 2, 3, dt=torch.float16)
+
+
+# The rows of a workgroup (128, 192 or 256) follow from the grid: the least rounds of 256 workgroups x (height / 64 + 1).  With
+# 86 .. 128 (groups of 256 columns) x (K ranges), as here, 257 .. 384 rows take 192 and 385 .. 512 rows take 256.
+@pytest.mark.parametrize("B", [257, 288, 320, 383, 384, 385, 448, 449, 512])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_tall_workgroups(B, terms):
+    """Workgroups of 192 and 256 rows (rings of two slots, of three in two terms): row counts on both sides of a workgroup and of
+    its halves, one to four stages of 64 inputs a range, K ranges, a ragged last column group.  Nothing is written outside rows < B."""
+    dt = torch.bfloat16 if B & 1 else torch.float16
+    _run(B, 22016, 256, 4, 1, dt=dt, terms=terms, guard=512)
+    _run(B, 22100, 128, 4, 1, terms=terms, guard=512)
+    _run(B, 5504, 512, 4, 4, terms=terms, guard=512)
+
+
+@pytest.mark.parametrize("B", [1, 33, 63, 100, 127, 129, 161, 191, 255])
+def test_gemm_writes_only_its_rows(B):
+    """Row tiles that end inside a tile or lie wholly beyond B, column tiles beyond the last: every other row keeps its contents."""
+    _run(B, 288, 512, 4, 2, guard=512)
+    _run(B, 1000, 384, 2, 3, guard=512, terms=2)
 
 
 @pytest.mark.parametrize("stages,ks", [(1, 1), (2, 1), (2, 2), (3, 1), (3, 3), (4, 2), (5, 1), (5, 2), (6, 3),
@@ -120,6 +144,24 @@ def test_gemm_ragged_shapes():
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
 @pytest.mark.parametrize("terms", [1, 2])
 def test_gemm_swiglu_epilogue(B, F, K, nw, dt, terms):
+    _run_swiglu(B, F, K, nw, dt, terms)
+
+
+@pytest.mark.parametrize("B", [257, 320, 384, 385, 449, 512])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_swiglu_tall_workgroups(B, terms):
+    """The same epilogue in workgroups of 192 and 256 rows (see test_gemm_tall_workgroups), the last column group ragged."""
+    _run_swiglu(B, 11008, 256, 4, torch.float16 if B & 1 else torch.bfloat16, terms, guard=512)
+    _run_swiglu(B, 11104, 128, 4, torch.bfloat16, terms, guard=512)
+
+
+@pytest.mark.parametrize("B", [1, 50, 127, 129, 200])
+def test_gemm_swiglu_writes_only_its_rows(B):
+    _run_swiglu(B, 352, 640, 4, torch.bfloat16, 1, guard=512)
+    _run_swiglu(B, 352, 640, 2, torch.float16, 2, guard=512)
+
+
+def _run_swiglu(B, F, K, nw, dt, terms, guard=0):
     dev = "cuda:0"
     gen = torch.Generator(device="cpu").manual_seed(F)
     Kp, rows = (K + 127) // 128 * 128, (B + 31) // 32 * 32
@@ -132,7 +174,7 @@ def test_gemm_swiglu_epilogue(B, F, K, nw, dt, terms):
     ref = (gd / (1 + torch.exp(-gd)) * ud).numpy()
     packed = torch.zeros(g.goose_packed_matrix_bytes(2 * F, K), dtype=torch.uint8, device=dev)
     g.goose_pack_matrix(inter.to(dev), 2 * F, K, packed)
-    h = torch.full((rows, F * terms), float("nan"), dtype=dt, device=dev)
+    h = torch.full((rows + guard, F * terms), float("nan"), dtype=dt, device=dev)
     if terms == 1:
         g.goose_gemm_swiglu_packed(a, Kp, packed, 2 * F, K, B, nw, h, F)
     else:
@@ -147,6 +189,8 @@ def test_gemm_swiglu_epilogue(B, F, K, nw, dt, terms):
         out = (pair[:, :, 0] + pair[:, :, 1]).reshape(B, F).numpy()
         tol = 2e-5
     assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
+    if guard:
+        assert torch.isnan(h[B:]).all()
 
 
 def test_gemm_more_tiles_than_one_round_of_four_tile_workgroups():
