@@ -246,8 +246,8 @@ int goose_verify_step(goose_ctx* ctx, const goose_model_ptrs* model, const goose
  * every weight read; masks, positions, caches and cache lengths stay per request) ---------------
  * The rows of the requests are stacked, each request starting at a multiple of 32 rows; the sum of
  * the rounded-up B must not exceed the context's max_rows (goose_create_batched), each B its max_B.
- * Projections, norms and the LM head run once over all rows (beyond 128 rows in chunks of 128 that
- * share the weight stream through the L2 cache); the attention runs on every request's own caches
+ * Projections, norms and the LM head run once over all rows (beyond 128 rows in workgroups of 128, 192 or
+ * 256 rows that share the weight stream through the L2 cache); the attention runs on every request's own caches
  * as one launch per tree-size class; walk, compaction and the optional harvest (into the request's own
  * successor tables) run per request.  16-bit models only.
  * d_argmax_all: int32 [max_rows], receives every row's prediction (request r's rows start
@@ -353,12 +353,13 @@ int goose_device_flags(goose_ctx* ctx, void* stream, int32_t* h_flags_out);
 
 /* ---- the projection kernel on its own (unit tests and tuning; dtype = GOOSE_DTYPE_BF16 or _F16) ---
  * out[m][n] = sum_k A[m][k] * W[n][k] for the skinny-M shapes of the pass (M = B <= 128 tree nodes;
- * up to GOOSE_MAX_ROWS stacked rows of a batch, computed in chunks of 128 rows).
+ * up to GOOSE_MAX_ROWS stacked rows of a batch, beyond 128 rows by a kernel of their own).
  * goose_pack_matrix re-tiles a row-major 16-bit W[N][K] into goose_packed_matrix_bytes(N, K) bytes
  * (N padded to 32, K to 128, zero filled).  goose_gemm_packed multiplies: d_a is 16-bit with
- * round_up(B,32) readable rows (round_up(B,128) when B > 128) of lda >= round_up(K,128) elements
- * (columns K.. and rows B.. must be finite),
- * nw = 2 or 4 column tiles per workgroup, ksplit = split-K factor (every split non-empty).
+ * round_up(B,32) readable rows (B > 128: B rows) of lda >= round_up(K,128) elements
+ * (columns K.. and the readable rows B.. must be finite),
+ * nw = 2 or 4 column tiles per workgroup (without effect when B > 128), ksplit = split-K factor
+ * (every split non-empty).
  * d_partials receives fp32 [ksplit][round_up(B,32)][round_up(N,32)]; the result is the sum over
  * the first index, rows < B (other rows are not written). */
 size_t goose_packed_matrix_bytes(int N, int K);

@@ -18,12 +18,13 @@
 //   * A stage issues the copies of the stage D-1 ahead into the slot that the barrier before it
 //     freed, and reads the operands of every k-step from LDS one k-step ahead of the matrix
 //     instructions; one raw s_barrier per stage, behind a wait that leaves the younger copies in flight.
-//   Measured (Llama-3-8B shape, inside a pass, 512 / 240 rows): gate/up 118 / 77 us (four-wavefront workgroups of 128 x 256
-//   with the weights through registers: 145 / 80), down 62 / 38 (73 / 40), q|k|v 37 / 24 (50 / 26), LM head 510 / 290
-//   (the skinny kernel in chunks of 128 rows: 725 / 373).  1.02 PFLOP/s at 512 rows; the parts alone: matrix instructions
+//   Measured (Llama-3-8B shape, by events inside a pass, 512 / 240 rows, on several cards): gate/up 120-131 / 76-78 us
+//   (four-wavefront workgroups of 128 x 256 with the weights through registers: 145 / 80), down 65-70 / 42-48 (73 / 40),
+//   q|k|v 40-41 / 25-26 (50 / 26), LM head 482-529 / 260-277, and 540-546 / 291-293 where it also writes the logits (the skinny kernel
+//   in passes over 128 rows, logits written: 725 / 373).  1.0 PFLOP/s in gate/up at 512 rows; the parts alone: matrix instructions
 //   and LDS reads 82 us (1.47 PFLOP/s, what this card sustains on such data), copies 100 us (A 45, W 62-76): the copies,
 //   4 MB per compute unit at about 40 GB/s, are what bounds it.  Tried without gain: a ring of four to six slots of 32
-//   inputs with the next operands read across the barrier (118 / 85), non-temporal weights, wave priorities, one chunk of
+//   inputs with the next operands read across the barrier, non-temporal weights, wave priorities, one chunk of
 //   256 rows x 128 columns per workgroup (90 at 240 rows).
 //   * Row chunks of one column group run on ONE XCD in neighbouring launch slots (workgroups are
 //     dealt to the 8 XCDs round-robin), so the later chunks find the weights in that XCD's L2.
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_rows(const typename Mma16<F16>:
       const float* crow = ct + (lane & 31) * CT_ROW + hh * 32;
       float v1 = -INFINITY, v2 = -INFINITY;
       int i1 = INT_MAX;
-      for (int c0 = 0; c0 < c_end; c0 += 8) {  // (eight reads in flight: 512 x 128256 542 -> 534 us)
+      for (int c0 = 0; c0 < c_end; c0 += 8) {  // (eight reads in flight: 8 us off 512 x 128256)
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = crow[c0 + e];
