@@ -209,3 +209,31 @@ def test_gemm_repeated_large_launches_are_stable():
         _run(64, 2048, 4096, 2, 1, seed=rep)
         _run(16, 4096, 4096, 2, 4, seed=rep)
         _run(128, 1024, 4096, 4, 2, seed=rep)
+
+
+# Workgroups of 128, 192 and 256 rows over ranges of 6, 10 and 18 stages of 64 inputs: the unrolled loop of four stages once, twice
+# and more often, each with two stages left over (12, 20 and 36 stages in two terms: none left).
+@pytest.mark.parametrize("B,N", [(200, 2080), (320, 22016), (500, 22016)])
+@pytest.mark.parametrize("K", [384, 640, 1152])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_many_rows_stage_remainders(B, N, K, terms):
+    _run(B, N, K, 4, 1, dt=torch.float16 if K == 640 else torch.bfloat16, terms=terms, guard=512)
+
+
+@pytest.mark.parametrize("B,F", [(150, 352), (300, 11104), (400, 11008)])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_swiglu_rows_at_any_even_pitch(B, F, terms):
+    """Result rows that start at odd multiples of four bytes (16-byte stores of the many-row kernel); nothing between them is written."""
+    dev, K, dt = "cuda:0", 256, torch.float16
+    gen = torch.Generator(device="cpu").manual_seed(F)
+    a, _ = _operand(torch.randn((B, K), generator=gen), _a_rows(B), K, dt, terms, dev)
+    packed = torch.zeros(g.goose_packed_matrix_bytes(2 * F, K), dtype=torch.uint8, device=dev)
+    g.goose_pack_matrix((torch.randn((2 * F, K), generator=gen) * 0.05).to(dt).to(dev), 2 * F, K, packed)
+    out = []
+    for ldh in (F * terms, F * terms + 2):
+        h = torch.full((B, ldh), float("nan"), dtype=dt, device=dev)
+        g.goose_gemm_swiglu_packed_ex(a, K * terms, terms, packed, 2 * F, K, B, 4, h, ldh)
+        torch.cuda.synchronize()
+        out.append(h[:, :F * terms].cpu())
+        assert torch.isnan(h[:, F * terms:]).all()
+    assert not torch.isnan(out[0]).any() and torch.equal(out[0], out[1])
