@@ -9,7 +9,7 @@
 //     consecutive kt are consecutive in memory, so each wavefront reads one long contiguous run.
 //   * The M x K activation block is small and shared: the workgroup stages 128-wide K slices of it
 //     in LDS (double buffered) and every wavefront reads its A operands from there.
-//   * 2 or 4 wavefronts per workgroup, one column tile each; split-K over blockIdx.y writes
+//   * 2, 4 or 5 wavefronts per workgroup, one column tile each; split-K over blockIdx.x writes
 //     fp32 partials that the next (reduction / rotary / norm) kernel sums in a fixed order.
 #include <stdlib.h>
 
@@ -87,8 +87,8 @@ __global__ __launch_bounds__(256) void k_pack_bf16(int mode, const bf16_t* __res
 }
 
 // ------------------------------------------------------------------------------------------
-// One workgroup = NW wavefronts, wavefront w owns column tile blockIdx.x*NW + w (32 columns) and
-// all MT row tiles.  blockIdx.y selects the split-K range.
+// One workgroup = NW wavefronts, wavefront w owns one column tile (32 columns; which, below) and
+// all MT row tiles.  blockIdx.x selects the split-K range.
 //
 // Operand A (activations), TERMS = 1 or 2.  With two terms an activation is carried as the sum of
 // two 16-bit values, a = hi + lo with lo = T(a - hi): the rounding of the projection's input then
@@ -124,6 +124,7 @@ __global__ __launch_bounds__(256) void k_pack_bf16(int mode, const bf16_t* __res
 // word 3 of a raw buffer descriptor on this target (32-bit untyped data, range checking on the byte offset)
 #define GOOSE_BUFFER_WORD3 0x00020000
 #define GOOSE_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+constexpr int lgkmcnt_imm(int n) { return 15 | (7 << 4) | (n << 8) | (3 << 14); }  // s_waitcnt lgkmcnt(n) only
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }  // s_waitcnt vmcnt(n) only
 
 template <int MT, int NW, int TERMS, int EPI, bool F16>
@@ -151,32 +152,22 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
   constexpr int TOP2_BYTES = (EPI == EPI_TOP2) ? NW * MT * 32 * (CT_ROW * 4 + 16) : 0;
   constexpr int EPI_BYTES = SWAP_BYTES > TOP2_BYTES ? SWAP_BYTES : TOP2_BYTES;
   constexpr int TAIL_BYTES = EPI_BYTES;
-  // Ring depth D: every wavefront keeps D stages of its weight pieces in flight in registers and the
-  // workgroup D stages of A in LDS.
-#ifndef GOOSE_RING_MAX
-#define GOOSE_RING_MAX 2
-#endif
-  constexpr int LDS_BUDGET = 144 * 1024;
-  constexpr int D_FIT = (LDS_BUDGET - (TAIL_BYTES > STAGE_BYTES ? TAIL_BYTES - STAGE_BYTES : 0)) / STAGE_BYTES;
-  constexpr int D = D_FIT >= GOOSE_RING_MAX ? GOOSE_RING_MAX : (D_FIT < 2 ? 2 : D_FIT);
-  static_assert(D >= 2 && D <= 4, "ring depth");
+  constexpr int D = 2;  // stages of its weights that a wavefront keeps in registers, and of A that the workgroup keeps in LDS
   // The buffers are separate arrays: the compiler then knows that the copy into one does not touch
   // what is read from another (with one array it makes every operand read wait for the copy just
   // issued, i.e. for all loads in flight).  The epilogues reuse the first.
   constexpr int LDS0_BYTES = STAGE_BYTES > TAIL_BYTES ? STAGE_BYTES : TAIL_BYTES;
-  static_assert(LDS0_BYTES + (D - 1) * STAGE_BYTES <= 160 * 1024, "LDS of one compute unit");
+  static_assert(LDS0_BYTES + STAGE_BYTES <= 160 * 1024, "LDS of one compute unit");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS0_BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char lds1[STAGE_BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char lds2[D > 2 ? STAGE_BYTES : 16];
-  __shared__ __attribute__((aligned(1024))) unsigned char lds3[D > 3 ? STAGE_BYTES : 16];
-  auto lds_buf = [&](auto buf_c) -> unsigned char* {
-    constexpr int b = decltype(buf_c)::value;
-    return b == 0 ? lds : (b == 1 ? lds1 : (b == 2 ? lds2 : lds3));
-  };
+  auto lds_buf = [&](auto buf_c) -> unsigned char* { return decltype(buf_c)::value == 0 ? lds : lds1; };
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (in a scalar register: it selects buffer descriptors)
   const int wt = wave;  // this wavefront's column tile
-  const int bx = blockIdx.x, by = blockIdx.y, ngroups = gridDim.x;  // column-tile group, split-K range
+  // Column-tile group, split-K range.  The K range is the fast grid index: workgroups are dealt to the 8 XCDs round-robin, so
+  // an XCD with one of four K ranges fetches a quarter of A into its L2 instead of all of it (a layer of
+  // the 7B model: 1 and 21 rows 1.2 % faster, 64 and 128 rows 0.2-0.7 %).
+  const int bx = blockIdx.y, by = blockIdx.x, ngroups = gridDim.y;
   const int tile = EPI == EPI_TOP2 ? bx * NW + wt : bx + ngroups * wt;
   const bool active = tile < ntiles;
   // a wavefront without a tile runs the same pipeline (no divergent control flow: the compiler can
@@ -251,22 +242,25 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
     asm volatile("" ::: "memory");
   };
   // Loads complete in order as far as the wait counter goes.  Stage j issues, in this order, the A copy
-  // of stage j+D-1 (into the buffer whose readers passed the barrier that ended stage j-1) and, one
+  // of stage j+1 (into the buffer whose readers passed the barrier that ended stage j-1) and, one
   // after each k-step's matrix instructions, the refills of its own register slot with the weights
-  // of stage j+D.  Before the barrier that ends stage j the A copy of stage j+1 must have landed; the
-  // STEADY_WAIT loads issued after that copy may stay in flight.
-  constexpr int STEADY_WAIT = (D - 2) * (STEPS + CPW) + STEPS;
-  static_assert(STEADY_WAIT <= 63, "wait counter");
+  // of stage j+2.  Before the barrier that ends stage j the A copy of stage j+1 must have landed; the
+  // STEPS loads issued after that copy may stay in flight.
   // The operand reads of a k-step are issued PD k-steps ahead of the matrix instructions that use
-  // them (a compute unit runs one wavefront per SIMD here, so nothing else hides the LDS latency).
+  // them (a compute unit runs one wavefront per SIMD here, so nothing else hides the LDS latency).  Left to itself the
+  // compiler places them right before their use.  With three and more matrix instructions per k-step their order and
+  // the waits for them are therefore fixed by hand (two terms, 64 rows: 141.6 -> 139.7 us a layer, 128 rows
+  // 206.7 -> 204.3); with fewer the kernel waits for the weights and the fixed order costs the LM head 0.7 %.
   constexpr int MPS = MT * TERMS;                                   // matrix instructions per k-step
-  constexpr int PD = MPS >= 4 ? 1 : (MPS >= 2 ? 2 : 4), NB = PD + 1;
+  constexpr bool BY_HAND = MPS >= 3;
+  constexpr int PD = MPS >= 6 ? 1 : (MPS >= 2 ? 2 : 4), NB = PD == 2 && BY_HAND ? 4 : PD + 1;
+  static_assert((PD - 1) * MPS <= 15, "wait counter");
   // one stage (slot = i % D, compile-time so that no register array is indexed dynamically; the
   // LDS buffer goes with it)
   auto stage = [&](auto slot_c, int i) {
     constexpr int slot = decltype(slot_c)::value;
     const unsigned char* abuf = lds_buf(slot_c);
-    copy_a(i + D - 1, std::integral_constant<int, (slot + D - 1) % D>());
+    copy_a(i + 1, std::integral_constant<int, 1 - slot>());
     __builtin_amdgcn_sched_barrier(0);   // keep the issue order: the scheduler would sink these loads
     op8 af[NB][TERMS][MT];
     auto read_a = [&](int s, op8 (&dst)[TERMS][MT]) {
@@ -281,9 +275,15 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
     };
 #pragma unroll
     for (int s = 0; s < PD; ++s) read_a(s, af[s % NB]);
-#pragma unroll
-    for (int s = 0; s < STEPS; ++s) {
-      if (s + PD < STEPS) read_a(s + PD, af[(s + PD) % NB]);
+    if constexpr (BY_HAND) __builtin_amdgcn_sched_barrier(0);
+    auto k_step = [&](auto s_c) {
+      constexpr int s = decltype(s_c)::value;
+      if constexpr (BY_HAND) {  // this k-step's operands are there when at most the reads of the PD-1 k-steps after it are pending
+        __builtin_amdgcn_s_waitcnt(lgkmcnt_imm((s + PD <= STEPS ? PD - 1 : STEPS - 1 - s) * MPS));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (s + PD < STEPS) read_a(s + PD, af[(s + PD) % NB]);
+      if constexpr (BY_HAND) __builtin_amdgcn_sched_barrier(0);
       const op8 b = __builtin_bit_cast(op8, wreg[slot][s]);
       // (terms outside, row tiles inside: consecutive matrix instructions then go to different
       // accumulators instead of waiting for each other; every accumulator still takes hi before lo)
@@ -295,35 +295,40 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
       wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, w_lane, ((i + D) * STEPS + s) * 1024, 2);
 #endif
       __builtin_amdgcn_sched_barrier(0);
-    }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(STEADY_WAIT));
+    };
+    k_step(std::integral_constant<int, 0>());
+    k_step(std::integral_constant<int, 1>());
+    k_step(std::integral_constant<int, 2>());
+    k_step(std::integral_constant<int, 3>());
+    k_step(std::integral_constant<int, 4>());
+    k_step(std::integral_constant<int, 5>());
+    k_step(std::integral_constant<int, 6>());
+    k_step(std::integral_constant<int, 7>());
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(STEPS));
     barrier();
   };
+  static_assert(STEPS == 8, "k-steps of a stage");
   const std::integral_constant<int, 0> c0;
   const std::integral_constant<int, 1> c1;
-  const std::integral_constant<int, 2> c2;
-  const std::integral_constant<int, 3> c3;
 
   if (nst > 0) {
+    // (kernel arguments still on their way would make every wait for an LDS read a wait for all of them)
+    if constexpr (BY_HAND) __builtin_amdgcn_s_waitcnt(lgkmcnt_imm(0));
     // the ring is filled in the order the stages themselves would have issued these loads, so that
     // one wait count fits the whole loop
     load_w(0, c0);
     copy_a(0, c0);
     load_w(1, c1);
-    if constexpr (D > 2) { copy_a(1, c1); load_w(2, c2); }
-    if constexpr (D > 3) { copy_a(2, c2); load_w(3, c3); }
     // stage 0 of both streams has arrived, later stages are in flight: the state every stage
     // starts from.  (The compiler counts the copies to LDS and the register loads as two kinds that
     // may overtake each other, and falls back to waiting for ALL loads wherever it has to wait for
     // one with both kinds pending; so the waits are placed here and before each barrier by hand, and
     // inside a stage everything it consumes is known to be there.)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(STEADY_WAIT));
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(STEPS));
     barrier();
     for (int i = 0; i < nst; i += D) {
       stage(c0, i);
       stage(c1, i + 1);
-      if constexpr (D > 2) stage(c2, i + 2);
-      if constexpr (D > 3) stage(c3, i + 3);
     }
     // the copies issued by the last stages still target the LDS buffers that the epilogues reuse
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
@@ -474,7 +479,7 @@ int launch_one(const GemmCall& g) {
   }
   const int granules = g.Kpad / KGRAN;                      // split-K ranges are multiples of 128 inputs
   const int gps = (granules + g.ksplit - 1) / g.ksplit;     // granules (= stages) per split
-  return launch_terms<MT, NW, EPI>(g, dim3(gx, g.ksplit), gps);
+  return launch_terms<MT, NW, EPI>(g, dim3(g.ksplit, gx), gps);
 }
 
 // five-wavefront workgroups: see launch_gemm_16
@@ -482,7 +487,7 @@ template <int MT, int EPI>
 int launch_five(const GemmCall& g) {
   const int granules = g.Kpad / KGRAN;
   const int gps = (granules + g.ksplit - 1) / g.ksplit;
-  return launch_terms<MT, 5, EPI>(g, dim3(g.gx, g.ksplit), gps);
+  return launch_terms<MT, 5, EPI>(g, dim3(g.ksplit, g.gx), gps);
 }
 template <int EPI>
 int launch_mt5(int MT, const GemmCall& g) {
