@@ -24,6 +24,8 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));  // (rows of results start at any multiple of four bytes)
 
 constexpr int KGRAN = 128;  // granularity of K padding and of split-K ranges (inputs)
 
@@ -146,8 +148,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
   // copy instructions per wavefront per stage: the same number for every wavefront (the wait counts
   // below are immediates); where the copies do not divide evenly the last ones are issued twice
   constexpr int CPW = (COPIES + NWAVES - 1) / NWAVES;
-  // SwiGLU: every wavefront passes its accumulators through LDS as fp32
-  constexpr int SWAP_BYTES = (EPI == EPI_SWIGLU) ? NW * MT * 16 * 64 * 4 : 0;
+  // SwiGLU: every wavefront passes its sums through LDS as fp32, a row tile at a time
+  constexpr int SW_ROW = 36;  // floats per row (16-byte accesses of 16 rows meet all banks)
+  constexpr int SWAP_BYTES = (EPI == EPI_SWIGLU) ? NW * 32 * SW_ROW * 4 : 0;
   constexpr int CT_ROW = 33;  // floats per row of a transposed-read C tile (odd: conflict-free row scans)
   constexpr int TOP2_BYTES = (EPI == EPI_TOP2) ? NW * MT * 32 * (CT_ROW * 4 + 16) : 0;
   constexpr int EPI_BYTES = SWAP_BYTES > TOP2_BYTES ? SWAP_BYTES : TOP2_BYTES;
@@ -290,7 +293,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
 #pragma unroll
       for (int t = 0; t < TERMS; ++t)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt] = Mma16<F16>::mfma(af[s % NB][t][mt], b, acc[mt]);
+        for (int mt = 0; mt < MT; ++mt)  // (EPI_SWIGLU: the sums stand transposed, see the epilogue; the same sums in the same order)
+          acc[mt] = EPI == EPI_SWIGLU ? Mma16<F16>::mfma(b, af[s % NB][t][mt], acc[mt]) : Mma16<F16>::mfma(af[s % NB][t][mt], b, acc[mt]);
 #if defined(__HIP_DEVICE_COMPILE__)
       wreg[slot][s] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, w_lane, ((i + D) * STEPS + s) * 1024, 2);
 #endif
@@ -398,44 +402,60 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
       }
     }
   } else {  // EPI_SWIGLU
-    // The wavefront leaves its accumulators in LDS (register r of lane l at [r][l]) and walks its
-    // tile's 16 output columns two at a time in a short loop (compact code; the 16-bit results leave
-    // as 4-byte stores): the gate values of columns 2p, 2p+1 sit at lanes 2p, 2p+1 of a half, the up
-    // values 16 lanes further.  Nothing is shared between wavefronts: no barrier.
-    constexpr int TILE_F = MT * 16 * 64;  // floats of one wavefront's accumulators
-    float* mine = reinterpret_cast<float*>(lds) + (size_t)wt * TILE_F;
+    // Register r of lane l holds row l%32, column 8*(r/4) + 4*(l/32) + r%4 of its tile: one row tile at a time the wavefront
+    // leaves its 32 x 32 sums in LDS, row by row, in four 16-byte writes, and lane (row, half) reads the gate and the up values of
+    // eight outputs back and stores those as 16 bytes.  Rolled over the row tiles (compact code; only the writes
+    // exist once per row tile).  Nothing is shared between wavefronts: no barrier.
+    float* mine = reinterpret_cast<float*>(lds) + (size_t)wt * (32 * SW_ROW);
+    auto dump = [&](auto mt_c) {
+      constexpr int mt = decltype(mt_c)::value;
+      if constexpr (mt < MT) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mine[(mt * 16 + r) * 64 + lane] = acc[mt][r] * out_scale;
-    __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront complete in order)
+        for (int a = 0; a < 4; ++a)
+          *reinterpret_cast<f32x4*>(mine + (lane & 31) * SW_ROW + 8 * a + 4 * a_hh) =
+              f32x4{acc[mt][4 * a], acc[mt][4 * a + 1], acc[mt][4 * a + 2], acc[mt][4 * a + 3]};
+        asm volatile("; row tile %0" ::"n"(mt));  // (keeps the cases apart: merged, the sums would be moved together first)
+      }
+    };
     if (writer) {
-      T* hq = reinterpret_cast<T*>(out);
       bool clamped = false;
-      for (int e = lane; e < MT * 16 * 16; e += 64) {
-        const int pr = e & 7, half = (e >> 3) & 1, rr = (e >> 4) & 15, mt = e >> 8;  // column pair, lane half, register, row tile
-        const int row = mt * 32 + 8 * (rr >> 2) + 4 * half + (rr & 3);
-        const int col = tile * 16 + 2 * pr;
-        const float* src = &mine[(mt * 16 + rr) * 64 + half * 32 + 2 * pr];
-        const float2 g = *reinterpret_cast<const float2*>(src);
-        const float2 u = *reinterpret_cast<const float2*>(src + 16);
-        float h0 = swiglu_f32(g.x, u.x), h1 = swiglu_f32(g.y, u.y);
-        if (F16) {  // beyond fp16: clamp, and say so (GOOSE_FLAG_RANGE)
-          if (fabsf(h0) > 65504.0f) { h0 = copysignf(65504.0f, h0); clamped = clamped || row < B; }
-          if (fabsf(h1) > 65504.0f) { h1 = copysignf(65504.0f, h1); clamped = clamped || row < B; }
+#pragma unroll 1
+      for (int mt = 0; mt < MT; ++mt) {
+        __builtin_amdgcn_wave_barrier();  // (LDS operations of one wavefront complete in order)
+        switch (mt) {
+          case 0: dump(std::integral_constant<int, 0>()); break;
+          case 1: dump(std::integral_constant<int, 1>()); break;
+          case 2: dump(std::integral_constant<int, 2>()); break;
+          case 3: dump(std::integral_constant<int, 3>()); break;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int row = mt * 32 + (lane & 31);
+        const float* src = mine + (lane & 31) * SW_ROW + 8 * a_hh;
+        const f32x4 gu[4] = {*reinterpret_cast<const f32x4*>(src), *reinterpret_cast<const f32x4*>(src + 4),
+                             *reinterpret_cast<const f32x4*>(src + 16), *reinterpret_cast<const f32x4*>(src + 20)};
+        float h[8], big = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          h[e] = swiglu_f32(gu[e >> 2][e & 3] * out_scale, gu[2 + (e >> 2)][e & 3] * out_scale);
+          big = fmaxf(big, fabsf(h[e]));
+        }
+        if (F16 && __builtin_amdgcn_ballot_w64(big > 65504.0f) != 0) {  // beyond fp16: clamp, and say so (GOOSE_FLAG_RANGE)
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (fabsf(h[e]) > 65504.0f) h[e] = copysignf(65504.0f, h[e]);
+          clamped = clamped || (row < B && big > 65504.0f);
+        }
+        op8 hi, lo;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          hi[e] = (T)h[e];
+          if (TERMS == 2) lo[e] = (T)(h[e] - (float)(T)h[e]);
         }
         if (row < B) {
-          // position of column `col` in a row of TERMS terms (two terms: groups of eight hi values, then their lo values)
-          const size_t cpos = TERMS == 1 ? (size_t)col : (size_t)(col >> 3) * 16 + (col & 7);
-          const T a0 = (T)h0, a1 = (T)h1;
-          T* dst = hq + (size_t)row * ldo + cpos;
-          union { T t[2]; unsigned u; } pk;
-          pk.t[0] = a0; pk.t[1] = a1;
-          *reinterpret_cast<unsigned*>(dst) = pk.u;
-          if (TERMS == 2) {
-            pk.t[0] = (T)(h0 - (float)a0); pk.t[1] = (T)(h1 - (float)a1);
-            *reinterpret_cast<unsigned*>(dst + 8) = pk.u;
-          }
+          // (two terms: groups of eight hi values, then their lo values)
+          T* dst = reinterpret_cast<T*>(out) + (size_t)row * ldo + (size_t)(tile * 16 + 8 * a_hh) * TERMS;
+          *reinterpret_cast<u32x4_a4*>(dst) = __builtin_bit_cast(u32x4, hi);
+          if (TERMS == 2) *reinterpret_cast<u32x4_a4*>(dst + 8) = __builtin_bit_cast(u32x4, lo);
         }
       }
       if (F16 && clamped && flags != nullptr) atomicOr(flags, GOOSE_FLAG_RANGE);
