@@ -280,3 +280,38 @@ def test_16bit_tree_that_fills_the_cache_to_its_last_slot():
     with pytest.raises(GooseError):
         gm.verify_step_calls(tokens, tree.parent, tree.is_spine, commit=False)
     gm.ctx.close()
+
+
+@pytest.mark.parametrize("B", [65, 100, 128])
+@pytest.mark.parametrize("bad", [float("nan"), float("-inf")])
+def test_wide_tree_attention_with_a_score_that_is_no_number(B, bad):
+    """Trees of 65 and more nodes take an attention kernel of their own.  A key whose scores are not a number has no weight there
+    either: the first 64 nodes get what the same nodes get alone (a node does not see later ones).  Equal up to the order of
+    fp32 sums and one rounding of the attention output to fp16 (2^-11), through two projections: 2e-3 of the largest."""
+    import paper_2604_02047_amd as g
+    from paper_2604_02047_amd import layout
+    from paper_2604_02047_amd.binding import GooseContext
+    dev, H, d, F, P, cap = "cuda:0", 256, 128, 256, 300, 512
+    gen = torch.Generator(device=dev).manual_seed(B)
+    rnd = lambda *shape, s=1.0: torch.randn(shape, generator=gen, device=dev) * s
+    ctx = GooseContext(g.ModelDesc(1, H, 2, d, F, 64, 10000.0, 1e-5, "bf16", 2, False, 0), B, cap)
+    w = {n: rnd(*shape, s=0.08).bfloat16() for n, shape in (("wq", (H, H)), ("wk", (H, H)), ("wv", (H, H)), ("wo", (H, H)),
+                                                            ("wg", (F, H)), ("wu", (F, H)), ("wd", (H, F)))}
+    w.update({n: torch.ones(H if n[1] in "12" else d, dtype=torch.bfloat16, device=dev) for n in ("g1", "g2", "gq", "gk")})
+    packed = torch.zeros(ctx.goose_packed_layer_bytes(), dtype=torch.uint8, device=dev)
+    ctx.goose_pack_layer(w, packed)
+    kc, vc = rnd(2, cap * d).bfloat16(), rnd(2, cap * d).bfloat16()
+    for slot in (5, 150, 299):   # whole rows: a score against them is NaN (NaN keys; -inf keys and queries of both signs)
+        kc[:, layout.k_offsets(torch.tensor([slot]), d)[0].to(dev)] = bad
+    parent = torch.tensor([-1] + [(i - 1) // 2 for i in range(1, B)], dtype=torch.int32, device=dev)
+    x0, out = rnd(B, H), []
+    for n in (64, B):
+        i32 = dict(dtype=torch.int32, device=dev)
+        mask, depth, pos = torch.zeros(n * ((n + 63) // 64), dtype=torch.int64, device=dev), torch.zeros(n, **i32), torch.zeros(n, **i32)
+        ctx.goose_build_mask(parent, n, P, mask, depth, pos)
+        x = x0[:n].clone()
+        ctx.goose_verify_layer(packed, x, kc.clone(), vc.clone(), P, n, mask, pos)
+        torch.cuda.synchronize()
+        out.append(x[:64].cpu())
+    assert torch.isfinite(out[0]).all() and torch.isfinite(out[1]).all()
+    assert (out[0] - out[1]).abs().max() <= 2e-3 * out[0].abs().max()
