@@ -1122,31 +1122,38 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ at
   const int qi = sg.row0 + r, h = blockIdx.x;
   const size_t base0 = (size_t)h * nsplit * Bpad + qi, step = Bpad;  // split s at base0 + s * step
   constexpr int CH = 8;
-  float mmax = NEG_BIG;
-  for (int s0 = 0; s0 < nsplit; s0 += CH) {
-    float m[CH];
-#pragma unroll
-    for (int k = 0; k < CH; ++k) m[k] = att_ml[(base0 + (size_t)min(s0 + k, nsplit - 1) * step) * 2];
-#pragma unroll
-    for (int k = 0; k < CH; ++k) mmax = fmaxf(mmax, m[k]);
-  }
   f32x4 num = {0.f, 0.f, 0.f, 0.f};
-  float den = 0.f;
-  for (int s0 = 0; s0 < nsplit; s0 += CH) {
-    float2 ml[CH];
-    f32x4 ov[CH];
+  float den = 0.f, mmax = NEG_BIG;
+  float2 ml[CH];
+  f32x4 ov[CH];
+  auto load = [&](int s0) {
 #pragma unroll
     for (int k = 0; k < CH; ++k) {
       const size_t base = base0 + (size_t)min(s0 + k, nsplit - 1) * step;
       ml[k] = *reinterpret_cast<const float2*>(att_ml + base * 2);
       ov[k] = *reinterpret_cast<const f32x4*>(att_o + base * D + c);
     }
+  };
+  load(0);  // (sums and maxima together: the maxima first would be a second trip to memory)
+#pragma unroll
+  for (int k = 0; k < CH; ++k) mmax = fmaxf(mmax, ml[k].x);
+  for (int s0 = CH; s0 < nsplit; s0 += CH) {
+    float m[CH];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) m[k] = att_ml[(base0 + (size_t)min(s0 + k, nsplit - 1) * step) * 2];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) mmax = fmaxf(mmax, m[k]);
+  }
+  for (int s0 = 0;;) {
 #pragma unroll
     for (int k = 0; k < CH; ++k) {
       const float w = (s0 + k < nsplit) ? exp2f(ml[k].x - mmax) : 0.f;
       den += w * ml[k].y;
       num += w * ov[k];
     }
+    s0 += CH;
+    if (s0 >= nsplit) break;
+    load(s0);
   }
   u16x4 v, v2;
 #pragma unroll
