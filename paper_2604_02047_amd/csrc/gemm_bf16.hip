@@ -167,10 +167,12 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // (in a scalar register: it selects buffer descriptors)
   const int wt = wave;  // this wavefront's column tile
-  // Column-tile group, split-K range.  The K range is the fast grid index: workgroups are dealt to the 8 XCDs round-robin, so
-  // an XCD with one of four K ranges fetches a quarter of A into its L2 instead of all of it (a layer of
-  // the 7B model: 1 and 21 rows 1.2 % faster, 64 and 128 rows 0.2-0.7 %).
-  const int bx = blockIdx.y, by = blockIdx.x, ngroups = gridDim.y;
+  // Column-tile group, split-K range.  Of the split products the K range is the fast grid index: workgroups are dealt to the 8
+  // XCDs round-robin, so an XCD with one of four K ranges fetches a quarter of A into its L2 instead of all of
+  // it (a layer of the 7B model: 1 and 21 rows 1.2 % faster, 64 and 128 rows 0.2-0.7 %).
+  const int bx = EPI == EPI_PARTIAL ? blockIdx.y + gridDim.y * blockIdx.z : blockIdx.x;
+  const int by = EPI == EPI_PARTIAL ? blockIdx.x : 0;
+  const int ngroups = EPI == EPI_PARTIAL ? gridDim.y * gridDim.z : gridDim.x;
   const int tile = EPI == EPI_TOP2 ? bx * NW + wt : bx + ngroups * wt;
   const bool active = tile < ntiles;
   // a wavefront without a tile runs the same pipeline (no divergent control flow: the compiler can
@@ -483,6 +485,13 @@ int launch_terms(const GemmCall& g, dim3 grid, int gps) {
   return g.f16 ? launch_k<MT, NW, 1, EPI, true>(g, grid, gps) : launch_k<MT, NW, 1, EPI, false>(g, grid, gps);
 }
 
+// gx column-tile groups x ksplit K ranges (see the kernel); a grid is at most 65535 high: more groups take several layers
+dim3 grid_of(int epi, int gx, int ksplit) {
+  if (epi != EPI_PARTIAL) return dim3(gx);
+  const int layers = (gx + 65534) / 65535;
+  return dim3(ksplit, (gx + layers - 1) / layers, layers);
+}
+
 template <int MT, int NW, int EPI>
 int launch_one(const GemmCall& g) {
   const int ntiles = g.Npad / 32;
@@ -499,7 +508,7 @@ int launch_one(const GemmCall& g) {
   }
   const int granules = g.Kpad / KGRAN;                      // split-K ranges are multiples of 128 inputs
   const int gps = (granules + g.ksplit - 1) / g.ksplit;     // granules (= stages) per split
-  return launch_terms<MT, NW, EPI>(g, dim3(g.ksplit, gx), gps);
+  return launch_terms<MT, NW, EPI>(g, grid_of(EPI, gx, g.ksplit), gps);
 }
 
 // five-wavefront workgroups: see launch_gemm_16
@@ -507,7 +516,7 @@ template <int MT, int EPI>
 int launch_five(const GemmCall& g) {
   const int granules = g.Kpad / KGRAN;
   const int gps = (granules + g.ksplit - 1) / g.ksplit;
-  return launch_terms<MT, 5, EPI>(g, dim3(g.ksplit, g.gx), gps);
+  return launch_terms<MT, 5, EPI>(g, grid_of(EPI, g.gx, g.ksplit), gps);
 }
 template <int EPI>
 int launch_mt5(int MT, const GemmCall& g) {
