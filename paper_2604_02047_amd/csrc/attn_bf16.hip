@@ -591,12 +591,15 @@ __global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
 constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }  // s_waitcnt vmcnt(n) only
 
 // One 32-key block of the online softmax: scores (this lane's 16 keys of one query) -> probabilities as the second product's
-// operand; running maximum, sum and output follow.  The exchange with the twin lane, the rescale and its exponential
-// are skipped while no lane's own scores exceed the running maximum, scale and maximum enter in one fused
-// multiply-add per score.  128 nodes over 16384 slots: a layer 202.1 -> 201.2 us, 13B with 80 over 2048 168.0 -> 166.7.
-// (In k_attn_fused, whose launches are mostly prologue, the same code was 0.2-0.5 % slower.  Raising the maximum only when it is
-// exceeded by 2^8 was no faster and cost precision: the largest probability is then no longer
-// exactly one in 16 bits.)
+// operand; running maximum, sum and output follow.  The arithmetic is that of k_attn_fused: the probabilities come from the
+// rounded products score x scale that the maximum was taken from, so the largest one is exactly one however large the
+// scores are (the unrounded product of a fused multiply-add differs from it by up to 2^6 for scores of 10^10), and a score
+// that is NaN or below NEG_BIG counts as NEG_BIG.  The exchange with the twin lane, the rescale and its exponential are
+// skipped while no lane's own scores exceed the running maximum.  A fused multiply-add per score instead of product, clamp and
+// difference is 0.1-0.2 % of a layer faster (128 nodes over 16384 slots 201.0 against 201.4 us, 13B with 80 over 2048 164.9
+// against 165.0); product and difference alone, with the clamp on a rare branch, 0.2-0.3 % slower than this.
+// (Raising the maximum only when it is exceeded by 2^8 was no faster and cost precision: the largest probability is then no
+// longer exactly one in 16 bits.)
 template <int NDT, typename T, typename op8>
 __device__ __forceinline__ void softmax_block(f32x16& sacc, bool masked, unsigned vis, float scale, float& m_run, float& l_run,
                                               f32x16 (&oacc)[NDT], op8 (&pf)[2]) {
@@ -604,10 +607,12 @@ __device__ __forceinline__ void softmax_block(f32x16& sacc, bool masked, unsigne
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[r] = ((vis >> r) & 1u) ? sacc[r] : NEG_BIG;  // also drops NaNs of stale keys
   }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sacc[r] = fmaxf(sacc[r] * scale, NEG_BIG);
   float t[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) t[r] = fmaxf(fmaxf(sacc[r], sacc[r + 4]), fmaxf(sacc[r + 8], sacc[r + 12]));
-  float tmax = fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])) * scale, NEG_BIG);
+  float tmax = fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]));
   if (__builtin_amdgcn_ballot_w64(tmax > m_run) != 0) {
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
     const float m_new = fmaxf(m_run, tmax);
@@ -621,26 +626,18 @@ __device__ __forceinline__ void softmax_block(f32x16& sacc, bool masked, unsigne
   }
   float p[16];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[r], scale, -m_run));
+  for (int r = 0; r < 16; ++r) p[r] = __builtin_amdgcn_exp2f(sacc[r] - m_run);
   if (masked) {  // a fully masked row must not count
 #pragma unroll
     for (int r = 0; r < 16; ++r) p[r] = ((vis >> r) & 1u) ? p[r] : 0.f;
   }
   float psum = 0.f;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) psum += p[r];
-  // a score that is not a number has no weight (an infinite maximum leaves the row undefined)
-  if (__builtin_amdgcn_ballot_w64(!(psum < INFINITY)) != 0) {
-    psum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      if (p[r] != p[r] && m_run < INFINITY) p[r] = 0.f;
-      psum += p[r];
-    }
+  for (int r = 0; r < 16; ++r) {
+    psum += p[r];
+    pf[r >> 3][r & 7] = (T)p[r];
   }
   l_run += psum;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) pf[r >> 3][r & 7] = (T)p[r];
 }
 
 template <int NQH, bool F16, int TS>

@@ -315,3 +315,45 @@ def test_wide_tree_attention_with_a_score_that_is_no_number(B, bad):
         out.append(x[:64].cpu())
     assert torch.isfinite(out[0]).all() and torch.isfinite(out[1]).all()
     assert (out[0] - out[1]).abs().max() <= 2e-3 * out[0].abs().max()
+
+
+def _layer_of_values(dtype, two_term, B, P, wq, wk, kc, vc, x0, n):
+    """x0 through one layer whose feed-forward part is zero, i.e. plus the attention's contribution, for a binary tree of n
+    of a context's B nodes: (the first n rows, the value caches, the O projection as stored)."""
+    import paper_2604_02047_amd as g
+    from paper_2604_02047_amd.binding import GooseContext
+    dev, H, d, F = "cuda:0", 256, 128, 256
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    ctx = GooseContext(g.ModelDesc(1, H, 2, d, F, 64, 10000.0, 1e-5, dtype, 2, False, int(two_term)), B, kc.shape[1] // d)
+    gen = torch.Generator(device=dev).manual_seed(99)
+    rnd = lambda *shape, s=1.0: torch.randn(shape, generator=gen, device=dev) * s
+    w = {"wq": wq.to(dt), "wk": wk.to(dt), "wv": rnd(H, H, s=0.08).to(dt), "wo": rnd(H, H, s=0.08).to(dt),
+         "wg": rnd(F, H, s=0.08).to(dt), "wu": rnd(F, H, s=0.08).to(dt), "wd": torch.zeros((H, F), dtype=dt, device=dev)}
+    w.update({k: torch.ones(H if k[1] in "12" else d, dtype=dt, device=dev) for k in ("g1", "g2", "gq", "gk")})
+    packed = torch.zeros(ctx.goose_packed_layer_bytes(), dtype=torch.uint8, device=dev)
+    ctx.goose_pack_layer(w, packed)
+    i32 = dict(dtype=torch.int32, device=dev)
+    parent = torch.tensor([-1] + [(i - 1) // 2 for i in range(1, n)], **i32)
+    mask, depth, pos = torch.zeros(n * ((n + 63) // 64), dtype=torch.int64, device=dev), torch.zeros(n, **i32), torch.zeros(n, **i32)
+    ctx.goose_build_mask(parent, n, P, mask, depth, pos)
+    x, k, v = x0[:n].clone(), kc.to(dt), vc.to(dt)
+    ctx.goose_verify_layer(packed, x, k, v, P, n, mask, pos)
+    torch.cuda.synchronize()
+    ctx.close()
+    return x, v, w["wo"]
+
+
+@pytest.mark.parametrize("B", [65, 96, 128])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_wide_tree_attention_with_scores_of_large_magnitude(B, dtype):
+    """Scores around 10^10, hundreds of millions apart: of every row one probability is one and the others are zero, exactly,
+    whatever the rounding of score x scale.  The first 64 nodes therefore get the bits that they get alone, from the other kernel."""
+    dev, H, d, P, cap = "cuda:0", 256, 128, 300, 512
+    gen = torch.Generator(device=dev).manual_seed(B)
+    rnd = lambda *shape, s=1.0: torch.randn(shape, generator=gen, device=dev) * s
+    wq, wk = rnd(H, H, s=600.0), rnd(H, H, s=0.08)         # queries of about 10^4
+    kc, vc = 4e4 * torch.sign(rnd(2, cap * d)), rnd(2, cap * d)
+    x0 = rnd(B, H)
+    alone, together = (_layer_of_values(dtype, dtype == "bf16", B, P, wq, wk, kc, vc, x0, n)[0][:64].cpu() for n in (64, B))
+    assert torch.isfinite(alone).all() and (alone - x0[:64].cpu()).abs().max() > 0.5
+    assert torch.equal(alone, together)
