@@ -164,7 +164,10 @@ int goose_embed(goose_ctx* ctx, const void* d_embed, const int32_t* d_tokens, in
  * d_x fp32 [B][hidden], updated in place.  d_kcache / d_vcache: THIS layer's part of the two
  * cache allocations (n_kv_heads * cap * head_dim elements each, layout above).
  * d_mask/d_pos as written by goose_build_mask.  P from *d_P when d_P != NULL (then the
- * argument P must be an upper bound of *d_P; it sizes the launch), else the argument. */
+ * argument P must be an upper bound of *d_P; it sizes the launch), else the argument.
+ * 16-bit models, trees of any size: an attention score (in base 2) that is NaN or below -1e30 counts as -1e30, i.e. has no weight
+ * beside any other visible score, and a row that has none but such takes the mean of its visible values.  Where the largest
+ * score is +infinity the row is NaN. */
 int goose_verify_layer(goose_ctx* ctx, const void* d_packed_layer, float* d_x, void* d_kcache, void* d_vcache,
                        int P, const int32_t* d_P, int B, const uint64_t* d_mask, const int32_t* d_pos,
                        void* stream);

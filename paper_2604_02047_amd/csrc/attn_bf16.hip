@@ -426,9 +426,12 @@ __global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
       sacc = Mma16<F16>::mfma(__builtin_bit_cast(op8, kreg[s]), ql, sacc);
     }
     if (idx + 1 < total) fetch_k(idx + 1);
+    // A score that is NaN or below NEG_BIG counts as NEG_BIG, and so does a masked one: as -infinity before the scale it becomes
+    // NEG_BIG as well (NEG_BIG there would come out above it and take the place of such scores).  A row with no other
+    // visible score takes the mean of its visible values.
     if (masked) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[r] = ((vis >> r) & 1u) ? sacc[r] : NEG_BIG;  // also drops NaNs of stale keys
+      for (int r = 0; r < 16; ++r) sacc[r] = ((vis >> r) & 1u) ? sacc[r] : -INFINITY;
     }
     float tmax = NEG_BIG;
 #pragma unroll
@@ -605,7 +608,7 @@ __device__ __forceinline__ void softmax_block(f32x16& sacc, bool masked, unsigne
                                               f32x16 (&oacc)[NDT], op8 (&pf)[2]) {
   if (masked) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sacc[r] = ((vis >> r) & 1u) ? sacc[r] : NEG_BIG;  // also drops NaNs of stale keys
+    for (int r = 0; r < 16; ++r) sacc[r] = ((vis >> r) & 1u) ? sacc[r] : -INFINITY;  // NEG_BIG below, as in k_attn_fused
   }
 #pragma unroll
   for (int r = 0; r < 16; ++r) sacc[r] = fmaxf(sacc[r] * scale, NEG_BIG);

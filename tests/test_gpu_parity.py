@@ -357,3 +357,36 @@ def test_wide_tree_attention_with_scores_of_large_magnitude(B, dtype):
     alone, together = (_layer_of_values(dtype, dtype == "bf16", B, P, wq, wk, kc, vc, x0, n)[0][:64].cpu() for n in (64, B))
     assert torch.isfinite(alone).all() and (alone - x0[:64].cpu()).abs().max() > 0.5
     assert torch.equal(alone, together)
+
+
+@pytest.mark.parametrize("B", [33, 64, 65, 96, 128])
+@pytest.mark.parametrize("P", [0, 300, 320])
+@pytest.mark.parametrize("dtype,bad", [("f16", "nan"), ("bf16", "-inf")])
+def test_attention_rows_without_a_finite_score(B, P, dtype, bad):
+    """Scores that are NaN or -inf count as the lowest one there is: a row that has no other takes the mean of its visible
+    values, in every attention kernel, whatever is masked beside them.  The attention's output is rounded once more to fp16."""
+    from paper_2604_02047_amd import layout
+    dev, H, d, cap = "cuda:0", 256, 128, 512
+    gen = torch.Generator(device=dev).manual_seed(B)
+    rnd = lambda *shape, s=1.0: torch.randn(shape, generator=gen, device=dev) * s
+    x0, vc = rnd(B, H), rnd(2, cap * d) + 1.0
+    if bad == "nan":
+        wq, wk, kc = rnd(H, H, s=0.08), torch.full((H, H), float("nan"), device=dev), torch.full((2, cap * d), float("nan"), device=dev)
+    else:   # query component 63 of both heads about 10^14, keys' about -10^25: the product overflows to -inf
+        x0[:, 0] = 3.0
+        wq, wk, kc = torch.zeros((H, H), device=dev), torch.zeros((H, H), device=dev), torch.zeros((2, cap * d), device=dev)
+        wq[63::128, 0], wk[63::128, 0] = 1e14, -1e25
+        kc[:, layout.k_offsets(torch.arange(cap), d)[:, 63].to(dev)] = -1e25
+    x, v, wo = _layer_of_values(dtype, dtype == "bf16", B, P, wq, wk, kc, vc, x0, B)
+    see = torch.zeros((B, P + B), dtype=torch.float64, device=dev)
+    see[:, :P] = 1
+    for i in range(B):
+        j = i
+        while j >= 0:
+            see[i, P + j] = 1
+            j = (j - 1) // 2 if j else -1
+    rows = v[:, layout.v_offsets(torch.arange(P + B), d).to(dev)].double()               # [head][slot][d], as stored
+    att = torch.cat([(see @ rows[h]) / see.sum(1, keepdim=True) for h in range(2)], dim=1)
+    bound = 2.0 ** -10 * (att.abs() @ wo.double().abs().t()).max()
+    assert torch.isfinite(x).all()
+    assert ((x - x0).double() - att @ wo.double().t()).abs().max() <= bound
