@@ -609,6 +609,18 @@ int launch_gemm_16(int dtype, int epi, const void* A, int lda, int terms, const 
   if ((terms != 1 && terms != 2) || lda < Kpad * terms || (lda & 7)) return GOOSE_ERR_ARG;
   if (epi != EPI_PARTIAL && epi != EPI_SWIGLU) return GOOSE_ERR_ARG;
   if (epi == EPI_SWIGLU && (ksplit != 1 || (Npad & 63))) return GOOSE_ERR_ARG;
+  if (B > 128 && (size_t)lda * 2 * 64 > 0xFFFFFFFFu) {
+    // The kernel for more rows addresses the up to 64 rows of a wavefront with 32-bit byte offsets.  Rows further apart than that
+    // go through this one, 128 at a time, with the same bits; the last 128 overlap those before them, whose results are
+    // then written twice (rows beyond B need not be readable here).
+    for (int r = 0; r < B; r += 128) {
+      const size_t r0 = r + 128 <= B ? r : B - 128;
+      const int rc = launch_gemm_16(dtype, epi, (const char*)A + r0 * lda * 2, lda, terms, Wp, Npad, Kpad, 128, nw, ksplit,
+                                    (char*)out + r0 * ldo * (epi == EPI_PARTIAL ? 4 : 2), ldo, out_split_stride, out_scale, flags, st);
+      if (rc != GOOSE_OK) return rc;
+    }
+    return GOOSE_OK;
+  }
   if (B > 128)  // the kernel blocked for the matrix cores
     return launch_gemm_rows_16(dtype, epi, A, lda, terms, Wp, Npad, Kpad, B, ksplit, out, ldo, out_split_stride, nullptr, 0,
                                out_scale, flags, st);

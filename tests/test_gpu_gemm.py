@@ -237,3 +237,32 @@ def test_gemm_swiglu_rows_at_any_even_pitch(B, F, terms):
         out.append(h[:, :F * terms].cpu())
         assert torch.isnan(h[:, F * terms:]).all()
     assert not torch.isnan(out[0]).any() and torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("swiglu", [False, True])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_many_rows_far_apart(swiglu, terms):
+    """129 rows of 128 inputs, 168 MB from one to the next: 32-bit byte offsets reach the first 26 only."""
+    dev, B, N, K, lda = "cuda:0", 129, 288 if not swiglu else 320, 128, 80 << 20
+    gen = torch.Generator(device="cpu").manual_seed(terms)
+    near, exact = _operand(torch.randn((B, K), generator=gen), B, K, torch.float16, terms, dev)
+    a = torch.empty(B * lda, dtype=torch.float16, device=dev)
+    a.view(B, lda)[:, :K * terms] = near
+    w = (torch.randn((N, K), generator=gen) * 0.05).half()
+    packed = torch.zeros(g.goose_packed_matrix_bytes(N, K), dtype=torch.uint8, device=dev)
+    g.goose_pack_matrix(w.to(dev), N, K, packed)
+    rows = 160
+    if swiglu:
+        out = torch.full((rows, N // 2 * terms), float("nan"), dtype=torch.float16, device=dev)
+        g.goose_gemm_swiglu_packed_ex(a, lda, terms, packed, N, K, B, 4, out, N // 2 * terms)
+        same = torch.empty_like(out)
+        g.goose_gemm_swiglu_packed_ex(near, K * terms, terms, packed, N, K, B, 4, same, N // 2 * terms)
+        torch.cuda.synchronize()
+        assert torch.equal(out[:B], same[:B])
+    else:
+        out = torch.full((rows, N), float("nan"), dtype=torch.float32, device=dev)
+        g.goose_gemm_packed_ex(a, lda, terms, packed, N, K, B, 4, 1, out)
+        torch.cuda.synchronize()
+        ref = exact @ w.double().numpy().T
+        assert np.abs(out[:B].double().cpu().numpy() - ref).max() <= 2e-5 * np.abs(ref).max()
+    assert torch.isnan(out[B:]).all()
