@@ -210,6 +210,33 @@ def test_many_row_head_on_ragged_vocabularies(vocab, sizes, act_mode):
     gm.ctx.close()
 
 
+@pytest.mark.parametrize("sizes", [[32] * 5, [32] * 13])
+def test_range_flag_of_a_batched_step(sizes):
+    """GOOSE_FLAG_RANGE from the many-row kernel: one node of one request whose SwiGLU result is beyond fp16."""
+    from paper_2604_02047_amd.binding import GOOSE_FLAG_RANGE
+    shape = dataclasses.replace(gi.SHAPES["tiny_bf16"], n_layers=1)
+    tm = torch_model(shape, seed=13)
+    w = tm["layers"][0]
+    w["wo"][0] = 0                                      # component 0 of the rows: nothing but what the embedding holds
+    w["wg"][7, 0], w["wu"][7, 0] = 250.0, -250.0
+    tm["embed"][:, 0] = 0
+    tm["embed"][5] = 0
+    tm["embed"][5, 0] = 16.0                            # normalised about 16: gate 4000, up -4000
+    gm = gpu_model(shape, tm, max_B=64, cap=384, max_rows=_rows_of(sizes))
+    reqs = _requests(gm, shape, sizes, [40] * len(sizes), [256 - B for B in sizes])
+    for q in reqs:
+        q["tokens"][q["tokens"] == 5] = 6
+    gm.ctx.goose_device_flags()                         # (whatever the prefill raised)
+    _batched(gm, reqs)                                  # (no flag)
+    for q in reqs:
+        q["P"].fill_(q["P0"])
+    reqs[-1]["tokens"][17] = 5
+    gm.ctx.goose_verify_step_batched(gm.model_ptrs(), reqs, torch.zeros(gm.ctx.max_rows, dtype=torch.int32, device=gm.device))
+    torch.cuda.synchronize()
+    assert gm.ctx.goose_device_flags() == GOOSE_FLAG_RANGE
+    gm.ctx.close()
+
+
 def test_batched_step_rejects_what_does_not_fit():
     from paper_2604_02047_amd.binding import GooseError
     shape = gi.SHAPES["tiny_bf16"]

@@ -161,7 +161,8 @@ def test_gemm_swiglu_writes_only_its_rows(B):
     _run_swiglu(B, 352, 640, 2, torch.float16, 2, guard=512)
 
 
-def _run_swiglu(B, F, K, nw, dt, terms, guard=0):
+def _run_swiglu(B, F, K, nw, dt, terms, guard=0, pad=0):
+    """guard > 0: that many rows behind the result, pad > 0: that many elements behind each row, which must stay as they were."""
     dev = "cuda:0"
     gen = torch.Generator(device="cpu").manual_seed(F)
     Kp, rows = (K + 127) // 128 * 128, (B + 31) // 32 * 32
@@ -174,23 +175,68 @@ def _run_swiglu(B, F, K, nw, dt, terms, guard=0):
     ref = (gd / (1 + torch.exp(-gd)) * ud).numpy()
     packed = torch.zeros(g.goose_packed_matrix_bytes(2 * F, K), dtype=torch.uint8, device=dev)
     g.goose_pack_matrix(inter.to(dev), 2 * F, K, packed)
-    h = torch.full((rows + guard, F * terms), float("nan"), dtype=dt, device=dev)
+    whole = torch.full((rows + guard, F * terms + pad), float("nan"), dtype=dt, device=dev)
     if terms == 1:
-        g.goose_gemm_swiglu_packed(a, Kp, packed, 2 * F, K, B, nw, h, F)
+        g.goose_gemm_swiglu_packed(a, Kp, packed, 2 * F, K, B, nw, whole, F + pad)
     else:
-        g.goose_gemm_swiglu_packed_ex(a, Kp * terms, terms, packed, 2 * F, K, B, nw, h, F * terms)
+        g.goose_gemm_swiglu_packed_ex(a, Kp * terms, terms, packed, 2 * F, K, B, nw, whole, F * terms + pad)
     torch.cuda.synchronize()
+    h = whole[:, :F * terms]
     if terms == 1:
         out = h[:B].double().cpu().numpy()
         # one rounding of the result to the storage type (relative to the element, hence to the largest)
         tol = 6e-3 if dt == torch.bfloat16 else 8e-4
     else:   # the result keeps two terms as well: hi + lo carries it to 2^-17 (the silu itself is fp32)
-        pair = h[:B].view(B, F // 8, 2, 8).double().cpu()
+        pair = h[:B].reshape(B, F // 8, 2, 8).double().cpu()
         out = (pair[:, :, 0] + pair[:, :, 1]).reshape(B, F).numpy()
         tol = 2e-5
     assert np.abs(out - ref).max() <= tol * np.abs(ref).max()
-    if guard:
+    if guard or pad:
+        assert torch.isnan(h[B:]).all() and torch.isnan(whole[:, F * terms:]).all()
+
+
+@pytest.mark.parametrize("B,F,nw", [(1, 352, 2), (33, 352, 4), (128, 352, 2), (128, 704, 4), (80, 17920, 4), (150, 352, 4),
+                                    (300, 11104, 4), (400, 11008, 4)])
+@pytest.mark.parametrize("terms", [1, 2])
+@pytest.mark.parametrize("pad", [2, 6])
+def test_gemm_swiglu_pitch_against_the_reference(B, F, nw, terms, pad):
+    """Both kernels, result rows that start at odd multiples of four bytes, against the fp64 product."""
+    _run_swiglu(B, F, 256, nw, torch.float16 if B & 1 else torch.bfloat16, terms, guard=64, pad=pad)
+
+
+@pytest.mark.parametrize("B,F,nw", [(1, 352, 2), (33, 352, 4), (64, 352, 2), (128, 704, 4), (80, 17920, 4), (150, 352, 4),
+                                    (300, 11104, 4), (400, 11008, 4)])
+@pytest.mark.parametrize("terms", [1, 2])
+def test_gemm_swiglu_beyond_fp16(B, F, nw, terms):
+    """Results beyond fp16 become +-65504 exactly; the others of their columns stay what they are, and those of the other columns
+    keep the bits that they have without any large ones beside them."""
+    dev, K, dt = "cuda:0", 128, torch.float16
+    gen = torch.Generator(device="cpu").manual_seed(B)
+    a, exact = _operand(torch.randn((B, K), generator=gen), _a_rows(B), K, dt, terms, dev)
+    wg, wu = ((torch.randn((F, K), generator=gen) * 0.05).to(dt) for _ in range(2))
+    big = torch.zeros(F, dtype=torch.bool)
+    big[[0, 7, 8, 15, 16, 85, F // 2 + 3, F - 17, F - 1]] = True           # first and last columns of groups of 8 and of tiles
+    out = []
+    for scale in (1.0, 2000.0):                                             # gate and up around 1100 in the large columns
+        s = torch.where(big, scale, 1.0).view(F, 1)
+        inter = torch.stack([(w.float() * s).to(dt).view(F // 16, 16, K) for w in (wg, wu)], dim=1).reshape(2 * F, K)
+        packed = torch.zeros(g.goose_packed_matrix_bytes(2 * F, K), dtype=torch.uint8, device=dev)
+        g.goose_pack_matrix(inter.contiguous().to(dev), 2 * F, K, packed)
+        h = torch.full(((B + 31) // 32 * 32, F * terms), float("nan"), dtype=dt, device=dev)
+        g.goose_gemm_swiglu_packed_ex(a, K * terms, terms, packed, 2 * F, K, B, nw, h, F * terms)
+        torch.cuda.synchronize()
         assert torch.isnan(h[B:]).all()
+        out.append(h[:B].view(B, F // 8, terms, 8).transpose(1, 2).reshape(B, terms, F).cpu())   # [row][hi|lo][column]
+    assert torch.equal(out[0][:, :, ~big], out[1][:, :, ~big])
+    gate, up = (torch.from_numpy(exact) @ (w[big].float() * 2000.0).to(dt).double().T for w in (wg, wu))
+    ref = gate / (1 + torch.exp(-gate)) * up
+    got = out[1][:, :, big].double().sum(1)
+    over = ref.abs() > 65504 * 1.001
+    assert over.any() and (~over).any() and (B == 1 or ((ref[over] > 0).any() and (ref[over] < 0).any()))
+    assert torch.equal(got[over], ref[over].sign() * 65504)
+    # fp32 sums of 128 exact products (2^-24 a step) in both factors, one rounding of the result to fp16
+    err = (got - ref.clamp(-65504, 65504)).abs()
+    assert (err <= 2.0 ** -10 * ref.abs() + 2.0 ** -16 * gate.abs().max() * up.abs().max()).all()
 
 
 def test_gemm_more_tiles_than_one_round_of_four_tile_workgroups():
@@ -266,3 +312,20 @@ def test_gemm_many_rows_far_apart(swiglu, terms):
         ref = exact @ w.double().numpy().T
         assert np.abs(out[:B].double().cpu().numpy() - ref).max() <= 2e-5 * np.abs(ref).max()
     assert torch.isnan(out[B:]).all()
+
+
+def test_gemm_more_column_groups_than_a_grid_is_high():
+    """65538 groups of two column tiles: the grid of a split product takes its groups in two layers."""
+    dev, N, K = "cuda:0", 32 * (2 * 65535 + 5), 256
+    gen = torch.Generator(device=dev).manual_seed(1)
+    w = (torch.randn((N, K), generator=gen, device=dev) * 0.05).half()
+    a = torch.zeros((32, K), dtype=torch.float16, device=dev)
+    a[0] = torch.randn(K, generator=gen, device=dev).half()
+    packed = torch.zeros(g.goose_packed_matrix_bytes(N, K), dtype=torch.uint8, device=dev)
+    g.goose_pack_matrix(w, N, K, packed)
+    part = torch.full((2, 32, N), float("nan"), dtype=torch.float32, device=dev)
+    g.goose_gemm_packed(a, K, packed, N, K, 1, 2, 2, part)
+    torch.cuda.synchronize()
+    ref = torch.cat([c.double() @ a[0].double() for c in w.split(1 << 19)])
+    assert (part[:, 0].double().sum(0) - ref).abs().max() <= 2e-5 * ref.abs().max()
+    assert torch.isnan(part[:, 1:]).all()

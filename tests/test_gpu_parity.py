@@ -390,3 +390,50 @@ def test_attention_rows_without_a_finite_score(B, P, dtype, bad):
     bound = 2.0 ** -10 * (att.abs() @ wo.double().abs().t()).max()
     assert torch.isfinite(x).all()
     assert ((x - x0).double() - att @ wo.double().t()).abs().max() <= bound
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("B,row", [(64, 40), (128, 101)])
+def test_range_flag_of_a_layer(dtype, B, row):
+    """A SwiGLU result beyond fp16 raises GOOSE_FLAG_RANGE where it belongs to a row of the tree, and not where it comes of the
+    rows behind a smaller tree, which still hold the operands of the larger one before it."""
+    import paper_2604_02047_amd as g
+    from paper_2604_02047_amd.binding import GOOSE_FLAG_RANGE, GooseContext
+    dev, H, d, F, P, cap = "cuda:0", 256, 64, 352, 40, 256
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    gen = torch.Generator(device=dev).manual_seed(B)
+    rnd = lambda *shape, s=1.0: torch.randn(shape, generator=gen, device=dev) * s
+    ctx = GooseContext(g.ModelDesc(1, H, 4, d, F, 64, 10000.0, 1e-5, dtype, 4, False, 0), B, cap)
+    w = {n: rnd(*shape, s=0.02).to(dt) for n, shape in (("wq", (H, H)), ("wk", (H, H)), ("wv", (H, H)), ("wo", (H, H)),
+                                                         ("wg", (F, H)), ("wu", (F, H)), ("wd", (H, F)))}
+    w.update({k: torch.ones(H if k[1] in "12" else d, dtype=dt, device=dev) for k in ("g1", "g2", "gq", "gk")})
+    w["wo"][0] = 0                                     # component 0 of the rows: nothing but what x holds
+    w["wg"][7, 0], w["wu"][7, 0] = 250.0, -250.0       # xn = 16 there: gate 4000, up -4000
+    packed = torch.zeros(ctx.goose_packed_layer_bytes(), dtype=torch.uint8, device=dev)
+    ctx.goose_pack_layer(w, packed)
+    ctx.goose_device_flags()                           # (a random bf16 weight below 2^-32 raises one of its own)
+    kc, vc = rnd(4, cap * d).to(dt), rnd(4, cap * d).to(dt)
+    x0 = rnd(B, H)
+    x0[:, 0] = 0
+    hot = x0.clone()
+    hot[row] = 0
+    hot[row, 0] = 16.0
+    i32 = dict(dtype=torch.int32, device=dev)
+
+    def layer(x, n):
+        parent = torch.tensor([-1] + [(i - 1) // 2 for i in range(1, n)], **i32)
+        mask, depth, pos = torch.zeros(n * ((n + 63) // 64), dtype=torch.int64, device=dev), torch.zeros(n, **i32), torch.zeros(n, **i32)
+        ctx.goose_build_mask(parent, n, P, mask, depth, pos)
+        x = x[:n].clone()
+        ctx.goose_verify_layer(packed, x, kc.clone(), vc.clone(), P, n, mask, pos)
+        torch.cuda.synchronize()
+        return x, ctx.goose_device_flags()
+
+    plain, flags = layer(x0, B)
+    assert flags == 0
+    x, flags = layer(hot, B)
+    assert flags == GOOSE_FLAG_RANGE and torch.isfinite(x).all()
+    assert (x[row] - (hot[row] - 65504.0 * w["wd"][:, 7].float())).abs().max() <= 1e-2 * 65504 * w["wd"][:, 7].float().abs().max()
+    small, flags = layer(x0, row)                      # the tile of `row` ends behind it or starts with it
+    assert flags == 0 and torch.isfinite(small).all()
+    ctx.close()
