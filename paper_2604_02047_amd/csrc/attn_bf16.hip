@@ -116,9 +116,10 @@ __global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = wave % NG, qh = wave / NG;  // key group, query tile
-  // head = the fast grid index: workgroups are dealt to the 8 XCDs round-robin, so head h runs on
-  // XCD h % 8, where the projection kernel's workgroup of the same 128 columns ran (q, k and v
-  // of head h sit 32 and 64 column groups apart): its partial sums are still in that XCD's L2
+  // head = the fast grid index: workgroups are dealt to the 8 XCDs round-robin, so where 8 divides the heads all key splits of a
+  // head run on one XCD, and what each of them reads (the head's slices of q) is in its L2 after the first.  With the
+  // split as the fast index a layer takes 110.1 us instead of 109.3 (64 nodes), 170.1 instead of 168.3 (13B, 80 nodes),
+  // 209.2 instead of 207.6 (128 nodes over 16384 slots), 92.6 instead of 92.4 (one node)
   const int split = blockIdx.y, nsplit = gridDim.y;
   int h = blockIdx.x;
   if (n_kv_heads != n_heads && (n_kv_heads & 7) == 0) {
@@ -688,7 +689,7 @@ __global__ __launch_bounds__(128 * NQH) void k_attn_wide(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = wave % NG, qh = wave / NG;  // key group, query tile
   const int split = blockIdx.y, nsplit = gridDim.y;
-  int h = blockIdx.x;  // head = the fast grid index, as in k_attn_fused (same XCD as the projection's columns)
+  int h = blockIdx.x;  // head = the fast grid index, as in k_attn_fused
   if (n_kv_heads != n_heads && (n_kv_heads & 7) == 0) {
     const int grp = (int)((unsigned)n_heads / (unsigned)n_kv_heads), xcd = h & 7, s = h >> 3;
     const int t = (int)((unsigned)s / (unsigned)grp);
@@ -1118,7 +1119,8 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ at
   const int tpr = D >> 2;  // threads per row
   const int r = blockIdx.y * (256 / tpr) + threadIdx.x / tpr, c = (threadIdx.x % tpr) * 4;
   if (r >= sg.B) return;
-  // head = the fast grid index: the workgroup runs on the XCD whose L2 holds that head's partials
+  // head = the fast grid index: where the attention kernel had it so too (8 divides the heads, no grouped queries), the
+  // workgroup runs on the XCD whose L2 holds that head's partials
   const int qi = sg.row0 + r, h = blockIdx.x;
   const size_t base0 = (size_t)h * nsplit * Bpad + qi, step = Bpad;  // split s at base0 + s * step
   constexpr int CH = 8;

@@ -116,9 +116,9 @@ __global__ __launch_bounds__(256) void k_pack_bf16(int mode, const bf16_t* __res
 // EPI_SWIGLU: every tile holds the gate rows (columns 0-15 of the tile) and the up rows (columns
 // 16-31) of 16 outputs, so a wavefront forms h = silu(gate) * up (in TERMS terms) from its own
 // accumulators.  Tiles (of EPI_SWIGLU and EPI_PARTIAL) are dealt to the wavefronts with a stride of
-// the grid width (wavefront w of workgroup g takes tile g + w * gridDim.x), and the grid is as wide
-// as the chip when the tiles allow: 688 tiles then load 256 compute units with at most three weight streams each instead of
-// 172 with four.
+// the number of column groups (wavefront w of group g takes tile g + w * groups; the groups are the grid's x, of the split
+// products its y and z), and there are as many workgroups as compute units when the tiles allow: 688 tiles then load 256 of
+// them with at most three weight streams each instead of 172 with four.
 // EPI_TOP2: besides the optional plain output, every workgroup reduces its columns to one
 // (largest, second largest, index of largest) triple per row, for the greedy argmax.
 // The weights are read once by the whole grid, with non-temporal loads that keep them from displacing
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16(const typename Mma16<F16>
   // The operand reads of a k-step are issued PD k-steps ahead of the matrix instructions that use
   // them (a compute unit runs one wavefront per SIMD here, so nothing else hides the LDS latency).  Left to itself the
   // compiler places them right before their use.  With three and more matrix instructions per k-step their order and
-  // the waits for them are therefore fixed by hand (two terms, 64 rows: 141.6 -> 139.7 us a layer, 128 rows
+  // the waits for them are therefore fixed by hand, two k-steps ahead with three and four instructions, one with six and eight (two terms, 64 rows: 141.6 -> 139.7 us a layer, 128 rows
   // 206.7 -> 204.3); with fewer the kernel waits for the weights and the fixed order costs the LM head 0.7 %.
   constexpr int MPS = MT * TERMS;                                   // matrix instructions per k-step
   constexpr bool BY_HAND = MPS >= 3;
@@ -496,11 +496,11 @@ template <int MT, int NW, int EPI>
 int launch_one(const GemmCall& g) {
   const int ntiles = g.Npad / 32;
   int gx = (ntiles + NW - 1) / NW;
-  // SwiGLU tiles stand alone and are dealt with a stride of the grid width: a grid as wide as the
+  // SwiGLU tiles stand alone and are dealt with a stride of the column groups: a grid as wide as the
   // chip (or as the tiles allow) spreads the weight streams over more compute units
   if (g.gx > 0) gx = g.gx;
   else if (EPI == EPI_SWIGLU && gx < 256) gx = ntiles < 256 ? ntiles : 256;
-  // the same for the split-K products: tiles of one K range are dealt with a stride of the grid width,
+  // the same for the split-K products: tiles of one K range are dealt with a stride of the column groups,
   // and the grid is widened until all ranges together fill the chip
   if (g.gx == 0 && EPI == EPI_PARTIAL && gx * g.ksplit < 256) {
     const int want = (256 + g.ksplit - 1) / g.ksplit;

@@ -26,10 +26,13 @@
 //   * The K range is the fastest index of the work items, then the column group, and the row chunks of one
 //     item run on ONE XCD in neighbouring launch slots (workgroups are dealt to the 8 XCDs round-robin): an XCD with one
 //     of eight K ranges fetches an eighth of A, and later chunks find the weights in its L2.  Column groups fastest, each
-//     XCD fetched all of A (7 MB for the down projection at 256 rows, more than its L2): 16 requests 3274 us a pass, now 2917.
+//     XCD fetched all of A (7 MB for the down projection at 256 rows, more than its L2).  The order alone, in this kernel:
+//     passes of 16 / 8 requests over 8 layers 3206 / 2022 us, column groups fastest 3360 / 2065.
 //   Measured (Llama-3-8B shape, kernel trace inside a pass, 512 / 240 rows; in brackets eight wavefronts with both operands through LDS):
-//   gate/up 104 / 74 us (124 / 75), q|k|v 34 / 23 (38 / 23), LM head with logits 466 / 278 (538 / 281); passes of 16 / 8
-//   requests over 8 layers 2917 / 1887 us (3271 / 1902), on another card, slowed by its power limit, 3051 / 1955 (3309 / 1935).  What bounds it, 512 rows of gate/up: loop 88-93 us, of which matrix
+//   gate/up 104 / 74 us (124 / 75), q|k|v 34 / 23 (38 / 23), LM head with logits 466 / 278 (538 / 281).  Whole passes over 8 layers, both
+//   kernels in turn on one card: 16 requests of 32 rows 3083 us (3358), 12 2421 (2623), 10 2255 (2535), 8 1874-1956 (0.99-1.02 times as
+//   fast), 6 1732 (1768), 5 1700 (1765); six in two terms 2194 (2452).  Cards differ by 5 % with their power limits.
+//   What bounds it, 512 rows of gate/up: loop 88-93 us, of which matrix
 //   instructions and LDS reads alone are 77 (1.5 PFLOP/s, what this card sustains on such data), prologue 2.4, epilogue 6.
 //   256 rows: loop 59, 45 with the weights in L2, 39 with no loads at all: the weight stream (4 TB/s) and the
 //   matrix instructions overlap in part only, whatever the depth of the rings (four stages of weights and eight slots: 59).
@@ -449,7 +452,8 @@ int launch_mt(int MT, const RowsCall& g) {
 // rows 115 / 145 / 103; 35840 x 6656, 192 rows 172 / 130 / 133, 384 rows 187 / 233 / 254; LM head of 128256 x 4096, 192 rows
 // 279 / 236 / 248, 512 rows 502 / 521 / 473.  Of 54 products (seven shapes, 160 .. 512 rows) the rule's is the fastest in 46; the
 // others are split-K products with eight ranges, where several workgroups of 128 rows share a unit (up to 20 % in
-// a loop over that product alone; inside a pass 256 rows are no slower).
+// a loop over that product alone).  Inside a pass of 16 requests, where the rule gives O and down 256 rows, 128 rows for
+// them make the pass 1.4 % slower (3247 against 3202 us, 8 layers); with 256 rows in all the rule takes 128 for them itself.
 int pick_mt(int B, int Npad, int ksplit) {
   const int groups = (Npad / 32 + WG_TILES - 1) / WG_TILES * ksplit;
   int best = 4, best_cost = INT_MAX;

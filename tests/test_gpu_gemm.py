@@ -78,7 +78,7 @@ def test_gemm_row_chunks(B):
 @pytest.mark.parametrize("B", [129, 191, 193, 256, 257, 384, 385, 449])
 def test_gemm_many_rows_edges(B):
     """The many-row kernel with fewer columns than one workgroup, a ragged last one, and ranges of 2 to 6 stages.  Grids as small
-    as these always take workgroups of 128 rows x 256 columns (a ring of three slots); test_gemm_tall_workgroups has the others."""
+    as these always take workgroups of 128 rows x 256 columns; test_gemm_tall_workgroups has the others."""
     for K in (128, 256, 384):
         _run(B, 40, K, 4, 1, dt=torch.float16)
         _run(B, 288, K, 4, 1, terms=2)
@@ -91,8 +91,9 @@ def test_gemm_many_rows_edges(B):
 @pytest.mark.parametrize("B", [257, 288, 320, 383, 384, 385, 448, 449, 512])
 @pytest.mark.parametrize("terms", [1, 2])
 def test_gemm_tall_workgroups(B, terms):
-    """Workgroups of 192 and 256 rows (rings of two slots, of three in two terms): row counts on both sides of a workgroup and of
-    its halves, one to four stages of 64 inputs a range, K ranges, a ragged last column group.  Nothing is written outside rows < B."""
+    """Workgroups of 192 and 256 rows: row counts on both sides of a workgroup's end and of the rows that one of its wavefronts
+    copies, ranges of two to four stages of 64 inputs (four to eight of 32 in two terms), K ranges, a ragged last column group.
+    Nothing is written outside rows < B."""
     dt = torch.bfloat16 if B & 1 else torch.float16
     _run(B, 22016, 256, 4, 1, dt=dt, terms=terms, guard=512)
     _run(B, 22100, 128, 4, 1, terms=terms, guard=512)
