@@ -29,7 +29,7 @@
 //     XCD fetched all of A (7 MB for the down projection at 256 rows, more than its L2).  The order alone, in this kernel:
 //     passes of 16 / 8 requests over 8 layers 3206 / 2022 us, column groups fastest 3360 / 2065.
 //   Measured (Llama-3-8B shape, kernel trace inside a pass, 512 / 240 rows; in brackets eight wavefronts with both operands through LDS):
-//   gate/up 104 / 74 us (124 / 75), q|k|v 34 / 23 (38 / 23), LM head with logits 466 / 278 (538 / 281).  Whole passes over 8 layers, both
+//   gate/up 104-106 / 74 us (124 / 75), q|k|v 34 / 23 (38 / 23), LM head with logits 446-466 / 278 (538 / 281).  Whole passes over 8 layers, both
 //   kernels in turn on one card: 16 requests of 32 rows 3083 us (3358), 12 2421 (2623), 10 2255 (2535), 8 1874-1956 (0.99-1.02 times as
 //   fast), 6 1732 (1768), 5 1700 (1765); six in two terms 2194 (2452).  Cards differ by 5 % with their power limits.
 //   What bounds it, 512 rows of gate/up: loop 88-93 us, of which matrix

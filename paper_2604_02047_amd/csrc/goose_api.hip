@@ -216,10 +216,10 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
       if (d.dtype == GOOSE_DTYPE_BF16) { c->w_exp = 8; c->out_scale = 1.0f / 256.0f; }
     }
   }
-  // Rows of the operands at a stride of a power of two (Kh = 4096: 8 KiB) fall on the same L2 channel, and
-  // the projections copy many rows of one column range at a time.  With up to 256 rows that costs
-  // nothing measurable; 512 rows of the 28672 x 4096 gate/up product take 148 us at a stride of 8192
-  // bytes and 122 us with 256 bytes more (256 rows: 80 and 82 us).
+  // Rows of the operands at a stride of a power of two (Kh = 4096: 8 KiB) fall on the same L2 channel, and the projections copy
+  // many rows of one column range at a time.  With more than 256 rows they stand 256 bytes further apart.  The many-row kernel as it is
+  // now does not gain by it (28672 x 4096 in a loop, 512 rows: 105-109 us with and without; passes of 10 to 12 requests 0.4-0.8 %
+  // slower with it, 16 requests 0.1-0.2 %).
   const int pad = is16(d.dtype) && c->Bpad > 256 ? 128 : 0;
   c->ld_xn = c->Kh * c->terms + pad;
   c->ld_o = c->Kq * c->terms + pad;
