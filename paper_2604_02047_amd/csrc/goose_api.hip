@@ -356,18 +356,17 @@ static RopeArgs rope_args(const goose_ctx* c, const int32_t* pos, int rows) {
   return RopeArgs{pos, c->inv_freq, (float2*)c->rope_cs, rows, c->d.head_dim / 2};
 }
 
-// One decoder layer.  `xhat_ready`: the operand buffer already holds RMSNorm(x)*g1 (the previous
+// One decoder layer of a 16-bit model.  `xhat_ready`: the operand buffer already holds RMSNorm(x)*g1 (the previous
 // layer's closing kernel wrote it); `rope`, with xhat_ready false only: the rotary angles of the
-// tree, written by the launch that normalises.  dP null (16-bit storage): the cache length is P.  `g_next`: gain of the normalisation that follows this layer
+// tree, written by the launch that normalises.  dP null: the cache length is P.  `g_next`: gain of the normalisation that follows this layer
 // (the next layer's g1 or the final norm), folded into the closing residual add; null to skip.
 // A batch of requests shares every projection (their rows are stacked, each request starting at a
 // multiple of 32 rows); in the attention every request is a slice of the grid with its own caches,
 // mask and length (`segs`; none = the single request given by the plain arguments).
 static_assert(GOOSE_MAX_REQUESTS <= ATTN_MAX_SEGS, "a batch must fit the attention's request table");
 static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, void* d_vcache, int P,
-                      const int32_t* dP, int B, const uint64_t* d_mask, const int32_t* d_pos, hipStream_t st,
-                      bool xhat_ready, const void* g_next, const RopeArgs* rope, const AttnSeg* segs = nullptr,
-                      int nseg = 0) {
+                      const int32_t* dP, int B, const uint64_t* d_mask, hipStream_t st, bool xhat_ready,
+                      const void* g_next, const RopeArgs* rope, const AttnSeg* segs = nullptr, int nseg = 0) {
   int rc = GOOSE_OK;
   const goose_model_desc& d = c->d;
   const size_t pstride = (size_t)c->Bpad * c->part_ld;
@@ -381,79 +380,72 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   }
   if (rc) return rc;
 
-  if (is16(d.dtype)) {
-    const int T = c->terms;
-    const int Nqkv = round_up(Hq + 2 * c->Hkv, 32), Nh = round_up(H, 32), Ngu = 2 * round_up(d.ffn, 32);
-    static const int splits_env = env_int("GOOSE_ATTN_SPLITS", 0);
-    const GemmCfg cq = gemm_cfg(c, "GOOSE_CFG_QKV", Nqkv, c->Kh);
-    int ks = cq.ks;
-    { PROF(PK_GEMM_QKV);
-      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->xn, c->ld_xn, T, w + c->pl.wqkv, Nqkv, c->Kh, B, cq.nw, ks,
-                          c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
-    if (rc) return rc;
-    // rotary embedding of q and k, KV rows of the tree into the cache, tree attention: one kernel
-    static const int ng_env = env_int("GOOSE_ATTN_NG", 4) == 2 ? 2 : 4;
-    const AttnSeg whole{0, B, P, d_kcache, d_vcache, dP, d_mask};
-    if (nseg == 0) { segs = &whole; nseg = 1; }
-    { PROF(PK_ATTN);
-      rc = launch_attn_16(d.dtype, c->part, ks, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, segs,
-                            nseg, splits_env, c->max_splits, ng_env, d.qk_norm ? w + c->pl.gq : nullptr,
-                            d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o,
-                            T, c->act_dtype, c->flags, st); }
-    if (rc) return rc;
-    const GemmCfg co = gemm_cfg(c, "GOOSE_CFG_O", Nh, c->Kq);
-    ks = co.ks;
-    { PROF(PK_GEMM_O);
-      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->o, c->ld_o, T, w + c->pl.wo, Nh, c->Kq, B, co.nw, ks, c->part,
-                          c->part_ld, pstride, c->out_scale, c->flags, st); }
-    if (rc) return rc;
-    // x += attention projection; x_hat = RMSNorm(x) * g2
-    { PROF(PK_NORM);
-      rc = launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks, pstride, c->part_ld, w + c->pl.g2, d.rms_eps,
-                             c->xn, c->ld_xn, T, B, st); }
-    if (rc) return rc;
-    static const int gu_nw = env_int("GOOSE_GU_NW", 4) == 2 ? 2 : 4;
-    { PROF(PK_GEMM_GATE_UP);
-      rc = launch_gemm_16(c->act_dtype, EPI_SWIGLU, c->xn, c->ld_xn, T, w + c->pl.wgu, Ngu, c->Kh, B, gu_nw, 1, c->h,
-                          (size_t)c->ld_h, 0, c->out_scale, c->flags, st); }
-    if (rc) return rc;
-    const GemmCfg cd = gemm_cfg(c, "GOOSE_CFG_DOWN", Nh, c->Fpad);
-    ks = cd.ks;
-    { PROF(PK_GEMM_DOWN);
-      rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->h, c->ld_h, T, w + c->pl.wd, Nh, c->Fpad, B, cd.nw, ks,
-                          c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
-    if (rc) return rc;
-    // x += MLP output (and the following normalisation when its gain is known)
-    PROF(PK_NORM);
-    return launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks, pstride, c->part_ld, g_next, d.rms_eps,
-                             g_next ? c->xn : nullptr, g_next ? c->ld_xn : 0, T, B, st);
-  }
+  const int T = c->terms;
+  const int Nqkv = round_up(Hq + 2 * c->Hkv, 32), Nh = round_up(H, 32), Ngu = 2 * round_up(d.ffn, 32);
+  static const int splits_env = env_int("GOOSE_ATTN_SPLITS", 0);
+  const GemmCfg cq = gemm_cfg(c, "GOOSE_CFG_QKV", Nqkv, c->Kh);
+  int ks = cq.ks;
+  { PROF(PK_GEMM_QKV);
+    rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->xn, c->ld_xn, T, w + c->pl.wqkv, Nqkv, c->Kh, B, cq.nw, ks,
+                        c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
+  if (rc) return rc;
+  // rotary embedding of q and k, KV rows of the tree into the cache, tree attention: one kernel
+  static const int ng_env = env_int("GOOSE_ATTN_NG", 4) == 2 ? 2 : 4;
+  const AttnSeg whole{0, B, P, d_kcache, d_vcache, dP, d_mask};
+  if (nseg == 0) { segs = &whole; nseg = 1; }
+  { PROF(PK_ATTN);
+    rc = launch_attn_16(d.dtype, c->part, ks, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, segs,
+                          nseg, splits_env, c->max_splits, ng_env, d.qk_norm ? w + c->pl.gq : nullptr,
+                          d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o,
+                          T, c->act_dtype, c->flags, st); }
+  if (rc) return rc;
+  const GemmCfg co = gemm_cfg(c, "GOOSE_CFG_O", Nh, c->Kq);
+  ks = co.ks;
+  { PROF(PK_GEMM_O);
+    rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->o, c->ld_o, T, w + c->pl.wo, Nh, c->Kq, B, co.nw, ks, c->part,
+                        c->part_ld, pstride, c->out_scale, c->flags, st); }
+  if (rc) return rc;
+  // x += attention projection; x_hat = RMSNorm(x) * g2
+  { PROF(PK_NORM);
+    rc = launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks, pstride, c->part_ld, w + c->pl.g2, d.rms_eps,
+                           c->xn, c->ld_xn, T, B, st); }
+  if (rc) return rc;
+  static const int gu_nw = env_int("GOOSE_GU_NW", 4) == 2 ? 2 : 4;
+  { PROF(PK_GEMM_GATE_UP);
+    rc = launch_gemm_16(c->act_dtype, EPI_SWIGLU, c->xn, c->ld_xn, T, w + c->pl.wgu, Ngu, c->Kh, B, gu_nw, 1, c->h,
+                        (size_t)c->ld_h, 0, c->out_scale, c->flags, st); }
+  if (rc) return rc;
+  const GemmCfg cd = gemm_cfg(c, "GOOSE_CFG_DOWN", Nh, c->Fpad);
+  ks = cd.ks;
+  { PROF(PK_GEMM_DOWN);
+    rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->h, c->ld_h, T, w + c->pl.wd, Nh, c->Fpad, B, cd.nw, ks,
+                        c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
+  if (rc) return rc;
+  // x += MLP output (and the following normalisation when its gain is known)
+  PROF(PK_NORM);
+  return launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks, pstride, c->part_ld, g_next, d.rms_eps,
+                           g_next ? c->xn : nullptr, g_next ? c->ld_xn : 0, T, B, st);
+}
 
-  // fp32 storage: plain kernels (one request)
-  if (nseg > 1) return GOOSE_ERR_SHAPE;
-  const float* xn = (const float*)c->xn;
-  rc = launch_gemm_f32(xn, c->Kh, (const float*)(w + c->pl.wqkv), 3 * Hq, H, B, c->part, c->part_ld, st);
+// One decoder layer of an fp32 model (one request): five launches, the norms inside the projections behind them.
+static int layer_f32(goose_ctx* c, const char* w, float* x, float* kc, float* vc, int P, const int32_t* dP, int B,
+                     const uint64_t* mask, const int32_t* pos, hipStream_t st) {
+  const goose_model_desc& d = c->d;
+  if (!f32_hidden_ok(d.hidden)) return GOOSE_ERR_SHAPE;
+  auto at = [&](size_t off) { return reinterpret_cast<const float*>(w + off); };
+  float* q = (float*)c->q;
+  float* o = (float*)c->o;
+  float* h = (float*)c->h;
+  int rc = launch_qkv_f32(x, d.hidden, at(c->pl.g1), d.rms_eps, at(c->pl.wqkv), d.n_heads, d.head_dim, B, pos, c->inv_freq, dP,
+                          c->cap, q, c->Kq, kc, vc, c->flags, st);
   if (rc) return rc;
-  rc = launch_rope_kv(d.dtype, c->part, 1, pstride, c->part_ld, B, d.n_heads, d.head_dim, d_pos, c->inv_freq, dP,
-                      c->cap, c->q, c->Kq, d_kcache, d_vcache, c->flags, st);
+  rc = launch_attn_f32(q, c->Kq, kc, vc, d.n_heads, d.head_dim, c->cap, dP, B, mask, o, c->Kq, P, c->flags, st);
   if (rc) return rc;
-  rc = launch_attn_f32((const float*)c->q, c->Kq, (const float*)d_kcache, (const float*)d_vcache, d.n_heads,
-                       d.head_dim, c->cap, dP, B, d_mask, (float*)c->o, c->Kq, P, c->flags, st);
+  rc = launch_resid_f32(o, c->Kq, at(c->pl.wo), d.hidden, c->Hq, B, x, st);
   if (rc) return rc;
-  rc = launch_gemm_f32((const float*)c->o, c->Kq, (const float*)(w + c->pl.wo), H, Hq, B, c->part, c->part_ld, st);
+  rc = launch_swiglu_f32(x, d.hidden, at(c->pl.g2), d.rms_eps, at(c->pl.wgu), d.ffn, B, h, c->Fpad, st);
   if (rc) return rc;
-  rc = launch_resid_norm(d.dtype, d.dtype, d_x, H, c->part, 1, pstride, c->part_ld, w + c->pl.g2, d.rms_eps, c->xn, c->Kh,
-                         1, B, st);
-  if (rc) return rc;
-  rc = launch_gemm_f32(xn, c->Kh, (const float*)(w + c->pl.wgu), 2 * d.ffn, H, B, c->part, c->part_ld, st);
-  if (rc) return rc;
-  rc = launch_swiglu_f32(c->part, c->part_ld, d.ffn, (float*)c->h, c->Fpad, B, st);
-  if (rc) return rc;
-  rc = launch_gemm_f32((const float*)c->h, c->Fpad, (const float*)(w + c->pl.wd), H, d.ffn, B, c->part, c->part_ld,
-                       st);
-  if (rc) return rc;
-  return launch_resid_norm(d.dtype, d.dtype, d_x, H, c->part, 1, pstride, c->part_ld, g_next, d.rms_eps,
-                           g_next ? c->xn : nullptr, g_next ? c->Kh : 0, 1, B, st);
+  return launch_resid_f32(h, c->Fpad, at(c->pl.wd), d.hidden, d.ffn, B, x, st);
 }
 
 int goose_verify_layer(goose_ctx* c, const void* d_packed_layer, float* d_x, void* d_kcache, void* d_vcache, int P,
@@ -465,12 +457,12 @@ int goose_verify_layer(goose_ctx* c, const void* d_packed_layer, float* d_x, voi
   const char* w = (const char*)d_packed_layer;
   if (is16(c->d.dtype)) {
     const RopeArgs rope = rope_args(c, d_pos, B);
-    return layer_impl(c, w, d_x, d_kcache, d_vcache, P, d_P, B, d_mask, d_pos, st, false, nullptr, &rope);
+    return layer_impl(c, w, d_x, d_kcache, d_vcache, P, d_P, B, d_mask, st, false, nullptr, &rope);
   }
   const int32_t* dP;
   rc = resolve_P(c, P, d_P, st, &dP);
   if (rc) return rc;
-  return layer_impl(c, w, d_x, d_kcache, d_vcache, P, dP, B, d_mask, d_pos, st, false, nullptr, nullptr);
+  return layer_f32(c, w, d_x, (float*)d_kcache, (float*)d_vcache, P, dP, B, d_mask, d_pos, st);
 }
 
 struct HarvestArgs {  // optional harvest of the logits into the requests' successor tables
@@ -497,11 +489,11 @@ static int lm_head_impl(goose_ctx* c, const void* d_packed_head, const float* d_
   const char* w = (const char*)d_packed_head;
   // the residual stream is left untouched: normalise into the operand buffer only
   int rc = GOOSE_OK;
-  if (!xhat_ready)
-    rc = launch_resid_norm(d.dtype, c->act_dtype, const_cast<float*>(d_x), d.hidden, nullptr, 0, 0, 0, w + c->ph.gf,
-                           d.rms_eps, c->xn, c->ld_xn, c->terms, B, st);
-  if (rc) return rc;
   if (is16(d.dtype)) {
+    if (!xhat_ready)
+      rc = launch_resid_norm(d.dtype, c->act_dtype, const_cast<float*>(d_x), d.hidden, nullptr, 0, 0, 0, w + c->ph.gf,
+                             d.rms_eps, c->xn, c->ld_xn, c->terms, B, st);
+    if (rc) return rc;
     // the projection kernel reduces its own columns to (max, second, index) per row; logits are
     // written only on request (through the padded workspace when rows are no multiple of a tile)
     static const int lm_env = env_int("GOOSE_LM_NW", 4) == 2 ? 2 : 4;
@@ -526,7 +518,9 @@ static int lm_head_impl(goose_ctx* c, const void* d_packed_head, const float* d_
   }
   float* logits = d_logits_or_null ? d_logits_or_null : c->logits;
   const size_t ld = d_logits_or_null ? (size_t)d.vocab : (size_t)c->Vpad;
-  rc = launch_gemm_f32((const float*)c->xn, c->Kh, (const float*)(w + c->ph.wlm), d.vocab, d.hidden, B, logits, ld, st);
+  if (!f32_hidden_ok(d.hidden)) return GOOSE_ERR_SHAPE;
+  rc = launch_logits_f32(d_x, d.hidden, (const float*)(w + c->ph.gf), d.rms_eps, (const float*)(w + c->ph.wlm), d.vocab, B, logits, ld,
+                         st);
   if (rc) return rc;
   rc = launch_argmax(logits, ld, d.vocab, B, d_argmax, d_margin_or_null, st);
   if (rc || hv.n == 0) return rc;
@@ -565,6 +559,35 @@ int goose_compact_kv(goose_ctx* c, void* d_kcache_all, void* d_vcache_all, int P
                         d.head_dim, dP, d_path, d_accept_len, d_new_P_or_null, c->flags, st);
 }
 
+static int harvest_of(const goose_step_io* io, int B, HarvestArgs* hv) {
+  if (!io->d_succ_ids_or_null) return GOOSE_OK;
+  if (!io->d_succ_scores_or_null || io->harvest_k < 1 || io->harvest_k > 16) return GOOSE_ERR_ARG;
+  hv->req[hv->n++] = HarvestReq{io->d_tokens, io->d_succ_ids_or_null, io->d_succ_scores_or_null, B, 0, io->harvest_k};
+  return GOOSE_OK;
+}
+
+// goose_verify_step for an fp32 model
+static int step_f32(goose_ctx* c, const goose_model_ptrs* m, const goose_step_io* io, int B, int P_max, hipStream_t st) {
+  const goose_model_desc& d = c->d;
+  int rc = launch_begin_f32((const float*)m->d_embed, io->d_tokens, d.hidden, d.vocab, c->s_x, io->d_parent, B, io->d_P, c->s_mask,
+                            c->s_depth, c->s_pos, c->s_P, c->flags, c->cap, P_max, st);
+  if (rc) return rc;
+  const size_t layer_cache = (size_t)c->n_kv * c->cap * d.head_dim;
+  for (int l = 0; l < d.n_layers; ++l) {
+    rc = layer_f32(c, (const char*)m->d_packed_layers + (size_t)l * c->pl.total, c->s_x, (float*)m->d_kcache_all + l * layer_cache,
+                   (float*)m->d_vcache_all + l * layer_cache, P_max, io->d_P, B, c->s_mask, c->s_pos, st);
+    if (rc) return rc;
+  }
+  HarvestArgs hv;
+  rc = harvest_of(io, B, &hv);
+  if (rc) return rc;
+  rc = lm_head_impl(c, m->d_packed_head, c->s_x, B, io->d_argmax, io->d_logits_or_null, io->d_margin_or_null, st, true, hv);
+  if (rc) return rc;
+  return launch_commit_f32(io->d_parent, io->d_tokens, io->d_is_spine, io->d_argmax, B, io->d_accept_len, io->d_path, io->d_bonus,
+                           io->d_next_root_or_null, io->d_P, c->s_P, (float*)m->d_kcache_all, (float*)m->d_vcache_all, d.n_layers,
+                           c->n_kv, c->cap, d.head_dim, c->flags, st);
+}
+
 int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_io* io, int B, int P_max,
                       void* stream) {
   if (!c || !m || !io) return GOOSE_ERR_ARG;
@@ -576,6 +599,7 @@ int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_
     return GOOSE_ERR_ARG;
   hipStream_t st = as_stream(stream);
   const goose_model_desc& d = c->d;
+  if (!is16(d.dtype)) return step_f32(c, m, io, B, P_max, st);
   rc = launch_build_mask(io->d_parent, B, io->d_P, c->s_mask, c->s_depth, c->s_pos, c->flags, c->cap, P_max, st);
   if (rc) return rc;
   rc = launch_embed(d.dtype, m->d_embed, io->d_tokens, B, d.hidden, d.vocab, c->s_x, st);
@@ -588,14 +612,12 @@ int goose_verify_step(goose_ctx* c, const goose_model_ptrs* m, const goose_step_
     const void* g_next = (l + 1 < d.n_layers) ? (const void*)(w + c->pl.total + c->pl.g1)
                                               : (const void*)((const char*)m->d_packed_head + c->ph.gf);
     rc = layer_impl(c, w, c->s_x, (char*)m->d_kcache_all + l * layer_cache, (char*)m->d_vcache_all + l * layer_cache,
-                    P_max, io->d_P, B, c->s_mask, c->s_pos, st, l > 0, g_next, is16(d.dtype) && l == 0 ? &rope : nullptr);
+                    P_max, io->d_P, B, c->s_mask, st, l > 0, g_next, l == 0 ? &rope : nullptr);
     if (rc) return rc;
   }
   HarvestArgs hv;
-  if (io->d_succ_ids_or_null) {
-    if (!io->d_succ_scores_or_null || io->harvest_k < 1 || io->harvest_k > 16) return GOOSE_ERR_ARG;
-    hv.req[hv.n++] = HarvestReq{io->d_tokens, io->d_succ_ids_or_null, io->d_succ_scores_or_null, B, 0, io->harvest_k};
-  }
+  rc = harvest_of(io, B, &hv);
+  if (rc) return rc;
   rc = lm_head_impl(c, m->d_packed_head, c->s_x, B, io->d_argmax, io->d_logits_or_null, io->d_margin_or_null, st,
                     true, hv);
   if (rc) return rc;
@@ -650,8 +672,8 @@ int goose_verify_step_batched(goose_ctx* c, const goose_model_ptrs* m, const goo
       segs[r].kc = (char*)reqs[r].d_kcache_all + l * layer_cache;
       segs[r].vc = (char*)reqs[r].d_vcache_all + l * layer_cache;
     }
-    rc = layer_impl(c, w, c->s_x, nullptr, nullptr, 0, nullptr, rows, nullptr, c->s_pos, st, l > 0, g_next, l == 0 ? &rope : nullptr,
-                    segs, n_req);
+    rc = layer_impl(c, w, c->s_x, nullptr, nullptr, 0, nullptr, rows, nullptr, st, l > 0, g_next, l == 0 ? &rope : nullptr, segs,
+                    n_req);
     if (rc) return rc;
   }
   HarvestArgs hv;

@@ -100,18 +100,13 @@ struct RopeArgs {
   float2* cs;
   int32_t rows, half;
 };
-// x[m][:] += sum_s part[s][m][:H] (S may be 0); xn[m][:] = Ta(rmsnorm(x[m]) * g) if xn != NULL, in `terms`
-// terms (two: hi + lo in groups of eight columns, the operand layout of the projections; 16-bit types only).
+// 16-bit types.  x[m][:] += sum_s part[s][m][:H] (S may be 0); xn[m][:] = Ta(rmsnorm(x[m]) * g) if xn != NULL, in `terms`
+// terms (two: hi + lo in groups of eight columns, the operand layout of the projections).
 // gain_dtype: type of g; act_dtype: type Ta of xn (equal, or fp16 activations under bf16 gains).
-// rope (16-bit types; its rows must equal B): the same launch writes these angles too.
+// rope (its rows must equal B): the same launch writes these angles too.
 int launch_resid_norm(int gain_dtype, int act_dtype, float* x, int H, const float* part, int S, size_t part_stride,
                       size_t part_ld, const void* g, float eps, void* xn, int ldxn, int terms, int B, hipStream_t st,
                       const RopeArgs* rope = nullptr);
-// qkv = sum_s part[s][m][0:3Hq]; rotary on q,k; q -> qout, k/v -> cache slots P+m
-int launch_rope_kv(int dtype, const float* part, int S, size_t part_stride, size_t part_ld, int B, int n_heads,
-                   int head_dim, const int32_t* pos, const double* inv_freq, const int32_t* dP, int cap, void* qout,
-                   int ldq, void* kcache, void* vcache, int32_t* flags, hipStream_t st);
-int launch_swiglu_f32(const float* gu, size_t ld, int F, float* h, int ldh, int B, hipStream_t st);
 int launch_argmax(const float* logits, size_t ld, int V, int B, int32_t* argmax, float* margin, hipStream_t st);
 // dP (or null): cache length, replaced by P + L + 1 after its old value went to *P_old
 int launch_accept(const int32_t* parent, const int32_t* tokens, const uint8_t* is_spine, const int32_t* argmax, int B,
@@ -142,10 +137,28 @@ int launch_compact(int elem_bytes, void* kall, void* vall, int n_layers, int n_h
                    const int32_t* dP, const int32_t* path, const int32_t* accept_len, int32_t* new_P, int32_t* flags,
                    hipStream_t st);
 
-// ---- fp32 path (f32_path.hip)
-// out[m][n] = sum_k A[m][k] * W[n][k]
-int launch_gemm_f32(const float* A, int lda, const float* W, int N, int K, int M, float* out, size_t ldo,
-                    hipStream_t st);
+// the same walk, results and compaction as one launch (fp32 caches; P_old: the length before the step)
+int launch_commit_f32(const int32_t* parent, const int32_t* tokens, const uint8_t* is_spine, const int32_t* argmax, int B,
+                      int32_t* accept_len, int32_t* path, int32_t* bonus, int32_t* next_root, int32_t* dP, const int32_t* P_old,
+                      float* kall, float* vall, int n_layers, int n_heads, int cap, int head_dim, int32_t* flags, hipStream_t st);
+
+// ---- fp32 path (f32_path.hip); x: f32 [M][H] residual rows, norm(x) = RMSNorm(x) * g, H a multiple of 4 as in launch_resid_norm
+static inline bool f32_hidden_ok(int H) { return H % 4 == 0 && H <= 16 * 1024; }
+// embedding rows, ancestor bits, depth and position of every node; *P_old = *dP
+int launch_begin_f32(const float* E, const int32_t* tokens, int H, int V, float* x, const int32_t* parent, int B, const int32_t* dP,
+                     uint64_t* mask, int32_t* depth, int32_t* pos, int32_t* P_old, int32_t* flags, int cap, int P_max,
+                     hipStream_t st);
+// q | k | v of norm(x); rotary on q, k; q -> [M][ldq], k and v -> cache slots *dP + m
+int launch_qkv_f32(const float* x, int H, const float* g, float eps, const float* W, int n_heads, int head_dim, int M,
+                   const int32_t* pos, const double* inv_freq, const int32_t* dP, int cap, float* q, int ldq, float* kc, float* vc,
+                   int32_t* flags, hipStream_t st);
+// h = silu(norm(x) Wg^T) * (norm(x) Wu^T), W = the F rows of Wg, then those of Wu
+int launch_swiglu_f32(const float* x, int H, const float* g, float eps, const float* W, int F, int M, float* h, int ldh, hipStream_t st);
+// out = norm(x) W^T
+int launch_logits_f32(const float* x, int H, const float* g, float eps, const float* W, int V, int M, float* out, size_t ldo,
+                      hipStream_t st);
+// x += A W^T
+int launch_resid_f32(const float* A, int lda, const float* W, int H, int K, int M, float* x, hipStream_t st);
 int launch_attn_f32(const float* q, int ldq, const float* kc, const float* vc, int n_heads, int head_dim, int cap,
                     const int32_t* dP, int B, const uint64_t* mask, float* o, int ldo, int P_max, int32_t* flags,
                     hipStream_t st);

@@ -123,10 +123,6 @@ __global__ __launch_bounds__(256) void k_embed_batch(const T* __restrict__ E, co
 template <typename T>
 __device__ inline void store4(T* p, float a, float b, float c, float d);
 template <>
-__device__ inline void store4<float>(float* p, float a, float b, float c, float d) {
-  *reinterpret_cast<float4*>(p) = make_float4(a, b, c, d);
-}
-template <>
 __device__ inline void store4<bf16_t>(bf16_t* p, float a, float b, float c, float d) {
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
   bf16x4 v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
@@ -225,63 +221,6 @@ __global__ __launch_bounds__(NTHR) void k_resid_norm(float* __restrict__ x, int 
 }
 
 // ------------------------------------------------------------------------------------------
-// Sum the split-K partials of the fused q|k|v projection, rotate q and k by the node's
-// position (half-split pairing (j, j+d/2), angle pos * base^(-2j/d)) and store q for the
-// attention kernel, k into cache slot P + m of K[head][slot][d], and v into the TRANSPOSED
-// value cache Vt[head][d][slot].  Grid (node, head); thread j owns the pair (j, j + d/2).
-template <typename T>
-__global__ void k_rope_kv(const float* __restrict__ part, int S, size_t part_stride, size_t part_ld, int n_heads,
-                          int head_dim, const int32_t* __restrict__ pos, const double* __restrict__ inv_freq,
-                          const int32_t* __restrict__ dP, int cap, T* __restrict__ qout, int ldq,
-                          T* __restrict__ kcache, T* __restrict__ vtcache, int32_t* __restrict__ flags) {
-  const int m = blockIdx.x, h = blockIdx.y, j = threadIdx.x;
-  const int half = head_dim >> 1;
-  const int Hq = n_heads * head_dim;
-  const int slot = *dP + m;
-  if (slot < 0 || slot >= cap) {  // no room for this node: say so instead of writing outside the cache
-    if (j == 0 && h == 0) atomicOr(flags, GOOSE_FLAG_CAPACITY);
-    return;
-  }
-  float v6[6] = {0, 0, 0, 0, 0, 0};
-  for (int s = 0; s < S; ++s) {
-    const float* r = part + s * part_stride + (size_t)m * part_ld + h * head_dim + j;
-    v6[0] += r[0];
-    v6[1] += r[half];
-    v6[2] += r[Hq];
-    v6[3] += r[Hq + half];
-    v6[4] += r[2 * Hq];
-    v6[5] += r[2 * Hq + half];
-  }
-  // reduce the angle in double, then evaluate in float: |error| ~ 1e-7 rad at any position
-  double ang = (double)pos[m] * inv_freq[j];
-  const double two_pi = 6.283185307179586476925286766559;
-  ang -= two_pi * rint(ang / two_pi);
-  float sn, cs;
-  sincosf((float)ang, &sn, &cs);
-  const float q1 = v6[0] * cs - v6[1] * sn, q2 = v6[1] * cs + v6[0] * sn;
-  const float k1 = v6[2] * cs - v6[3] * sn, k2 = v6[3] * cs + v6[2] * sn;
-  T* qo = qout + (size_t)m * ldq + h * head_dim + j;
-  qo[0] = (T)q1;
-  qo[half] = (T)q2;
-  const size_t row = ((size_t)h * cap + slot) * head_dim + j;
-  kcache[row] = (T)k1;
-  kcache[row + half] = (T)k2;
-  T* vcol = vtcache + ((size_t)h * head_dim + j) * cap + slot;
-  vcol[0] = (T)v6[4];
-  vcol[(size_t)half * cap] = (T)v6[5];
-}
-
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_swiglu_f32(const float* __restrict__ gu, size_t ld, int F,
-                                                    float* __restrict__ h, int ldh) {
-  const int m = blockIdx.y;
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= F) return;
-  const float g = gu[(size_t)m * ld + c], u = gu[(size_t)m * ld + F + c];
-  h[(size_t)m * ldh + c] = g / (1.0f + expf(-g)) * u;
-}
-
-// ------------------------------------------------------------------------------------------
 struct Top2 {
   float v1, v2;
   int i1;
@@ -300,9 +239,13 @@ __global__ __launch_bounds__(256) void k_argmax(const float* __restrict__ logits
   const int m = blockIdx.x;
   const float* row = logits + (size_t)m * ld;
   Top2 t = {-INFINITY, -INFINITY, INT_MAX};
-  for (int c = threadIdx.x; c < V; c += 256) {
-    Top2 e = {row[c], -INFINITY, c};
-    t = top2_merge(t, e);
+  for (int c0 = threadIdx.x; c0 < V; c0 += 256 * 4) {  // (four loads in flight)
+    float e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) e[u] = row[min(c0 + 256 * u, V - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (c0 + 256 * u < V) t = top2_merge(t, Top2{e[u], -INFINITY, c0 + 256 * u});
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -575,48 +518,63 @@ __global__ __launch_bounds__(256) void k_harvest_merge(int chunks, int table_row
 // the winners from the root; node indices grow along any path, so the walk is finite.
 // dP (or null): the cache length becomes P + L + 1 here, and its old value goes to *P_old, which the commit that
 // follows reads (a kernel of its own for this one word was the last launch of every step).
+// `won` and `pred` take B ints of LDS each; nodes of the accepted path -> route[0 .. L] (LDS), *L_out = L, returns the bonus token to
+// thread 0.  All threads (at least B) call it.
+__device__ inline int walk(const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
+                           const uint8_t* __restrict__ is_spine, const int32_t* __restrict__ argmax, int B, int* won, int* pred,
+                           int* route, int* L_out) {
+  const int i = threadIdx.x;
+  int bid_at = -1, token = 0, branch = 0, bonus = 0;
+  if (i < B) {
+    won[i] = INT_MAX;
+    pred[i] = argmax[i];
+    bid_at = parent[i];
+    token = tokens[i];
+    branch = (is_spine != nullptr && is_spine[i] == 0) ? 1 : 0;
+  }
+  __syncthreads();
+  if (i >= 1 && i < B && bid_at >= 0 && bid_at < i && token == pred[bid_at]) atomicMin(&won[bid_at], (branch << 16) | i);
+  __syncthreads();
+  if (i == 0) {
+    int v = 0, L = 0;
+    route[0] = 0;
+    while (won[v] != INT_MAX && L < B - 1) {
+      v = won[v] & 0xFFFF;
+      route[++L] = v;
+    }
+    *L_out = L;
+    bonus = pred[v];
+  }
+  __syncthreads();
+  return bonus;
+}
+
+// What a walk hands back; p: cache length before the step.
+__device__ inline void accept_store(int B, const int* route, int L, int bonus_token, int32_t* __restrict__ accept_len,
+                                    int32_t* __restrict__ path, int32_t* __restrict__ bonus, int32_t* __restrict__ next_root,
+                                    int32_t* __restrict__ dP, int p, int cap, int32_t* __restrict__ flags) {
+  const int i = threadIdx.x;
+  if (i < B) path[i] = i <= L ? route[i] : -1;
+  if (i != 0) return;
+  *accept_len = L;
+  *bonus = bonus_token;
+  if (next_root) *next_root = bonus_token;
+  if (dP) {
+    if (p < 0 || p + L + 1 > cap) atomicOr(flags, GOOSE_FLAG_CAPACITY);
+    *dP = p + L + 1;
+  }
+}
+
 __device__ inline void accept_body(const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
                                    const uint8_t* __restrict__ is_spine, const int32_t* __restrict__ argmax, int B,
                                    int32_t* __restrict__ accept_len, int32_t* __restrict__ path,
                                    int32_t* __restrict__ bonus, int32_t* __restrict__ next_root, int32_t* __restrict__ dP,
                                    int32_t* __restrict__ P_old, int cap, int32_t* __restrict__ flags) {
-  __shared__ int nxt[GOOSE_MAX_B];
-  __shared__ int xh[GOOSE_MAX_B];
-  __shared__ int L_sh;
-  const int i = threadIdx.x;
-  if (i < B) {
-    nxt[i] = INT_MAX;
-    xh[i] = argmax[i];
-  }
-  __syncthreads();
-  if (i >= 1 && i < B) {
-    const int p = parent[i];
-    if (p >= 0 && p < i && tokens[i] == xh[p]) {
-      const int branch = (is_spine != nullptr && is_spine[i] == 0) ? 1 : 0;
-      atomicMin(&nxt[p], (branch << 16) | i);
-    }
-  }
-  __syncthreads();
-  if (i == 0) {
-    int v = 0, L = 0;
-    path[0] = 0;
-    while (nxt[v] != INT_MAX && L < B - 1) {
-      v = nxt[v] & 0xFFFF;
-      path[++L] = v;
-    }
-    *accept_len = L;
-    *bonus = xh[v];
-    if (next_root) *next_root = xh[v];
-    if (dP) {
-      const int p = *dP;
-      if (p < 0 || p + L + 1 > cap) atomicOr(flags, GOOSE_FLAG_CAPACITY);
-      *P_old = p;
-      *dP = p + L + 1;
-    }
-    L_sh = L;
-  }
-  __syncthreads();
-  if (i > L_sh && i < B) path[i] = -1;
+  __shared__ int won[GOOSE_MAX_B], pred[GOOSE_MAX_B], route[GOOSE_MAX_B], L_sh;
+  const int p = dP ? *dP : 0;
+  const int word = walk(parent, tokens, is_spine, argmax, B, won, pred, route, &L_sh);
+  if (dP && threadIdx.x == 0) *P_old = p;
+  accept_store(B, route, L_sh, word, accept_len, path, bonus, next_root, dP, p, cap, flags);
 }
 
 __global__ __launch_bounds__(128) void k_accept(const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
@@ -643,17 +601,14 @@ __global__ __launch_bounds__(128) void k_accept_batch(const ReqTable t, const in
 // Vt[head i][d][slot], a thread single elements along one d-row.  Either way a thread walks j upward and path[j] >= j, so a
 // slot is always read before the same thread can overwrite it.
 struct Float4Any { float e[4]; };
-__global__ __launch_bounds__(256) void k_compact_f32(float* __restrict__ kall, float* __restrict__ vall, int cap, int head_dim,
-                                                     const int32_t* __restrict__ dP, const int32_t* __restrict__ path,
-                                                     const int32_t* __restrict__ accept_len) {
+__device__ inline void compact_f32_body(float* __restrict__ kall, float* __restrict__ vall, int cap, int head_dim, int P,
+                                        const int32_t* __restrict__ path, int L) {
   const int c = threadIdx.x;
   const bool is_v = blockIdx.x & 1;
   if (c >= (is_v ? head_dim : head_dim / 4)) return;
   const size_t base = (size_t)(blockIdx.x >> 1) * cap * head_dim;  // (layer * n_heads + head)
   Float4Any* kb = reinterpret_cast<Float4Any*>(kall + base) + c;
   float* vb = vall + base + (size_t)c * cap;
-  const int P = *dP;
-  int L = *accept_len;
   if (L > GOOSE_MAX_B - 1) L = GOOSE_MAX_B - 1;
   for (int j = 1; j <= L; ++j) {
     const int src = path[j];
@@ -662,6 +617,26 @@ __global__ __launch_bounds__(256) void k_compact_f32(float* __restrict__ kall, f
     if (is_v) vb[P + j] = vb[P + src];
     else kb[(size_t)(P + j) * (head_dim / 4)] = kb[(size_t)(P + src) * (head_dim / 4)];
   }
+}
+__global__ __launch_bounds__(256) void k_compact_f32(float* __restrict__ kall, float* __restrict__ vall, int cap, int head_dim,
+                                                     const int32_t* __restrict__ dP, const int32_t* __restrict__ path,
+                                                     const int32_t* __restrict__ accept_len) {
+  compact_f32_body(kall, vall, cap, head_dim, *dP, path, *accept_len);
+}
+// Walk and commit of an fp32 step in one launch: every workgroup walks the tree itself (it is a few hundred bytes), the first one
+// hands the results back.  The cache length before the step comes from *P_old (k_begin_f32), as the first workgroup replaces *dP.
+__global__ __launch_bounds__(256) void k_commit_f32(const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
+                                                    const uint8_t* __restrict__ is_spine, const int32_t* __restrict__ argmax, int B,
+                                                    int32_t* __restrict__ accept_len, int32_t* __restrict__ path,
+                                                    int32_t* __restrict__ bonus, int32_t* __restrict__ next_root,
+                                                    int32_t* __restrict__ dP, const int32_t* __restrict__ P_old,
+                                                    float* __restrict__ kall, float* __restrict__ vall, int cap, int head_dim,
+                                                    int32_t* __restrict__ flags) {
+  __shared__ int won[GOOSE_MAX_B], pred[GOOSE_MAX_B], route[GOOSE_MAX_B], L_sh;
+  const int P = *P_old;
+  const int word = walk(parent, tokens, is_spine, argmax, B, won, pred, route, &L_sh);
+  if (blockIdx.x == 0) accept_store(B, route, L_sh, word, accept_len, path, bonus, next_root, dP, P, cap, flags);
+  compact_f32_body(kall, vall, cap, head_dim, P, route, L_sh);
 }
 
 // The same for bf16 caches in MFMA operand order (32-key blocks; the layouts are spelled out in
@@ -784,32 +759,13 @@ int launch_resid_norm(int gain_dtype, int act_dtype, float* x, int H, const floa
                       size_t part_ld, const void* g, float eps, void* xn, int ldxn, int terms, int B, hipStream_t st,
                       const RopeArgs* rope) {
   if ((H & 3) || H > 16 * 1024 || (terms == 2 && (H & 7))) return GOOSE_ERR_SHAPE;
-  if (terms != 1 && !(terms == 2 && act_dtype != GOOSE_DTYPE_F32)) return GOOSE_ERR_ARG;
+  if (terms != 1 && terms != 2) return GOOSE_ERR_ARG;
   if (rope != nullptr && (rope->rows != B || rope->half < 1 || rope->half > 128)) return GOOSE_ERR_ARG;
   const NormArgs a{x, H, part, S, part_stride, part_ld, g, eps, xn, ldxn, B, rope != nullptr ? *rope : RopeArgs{}, st};
   if (gain_dtype == GOOSE_DTYPE_BF16 && act_dtype == GOOSE_DTYPE_BF16) launch_resid_norm_terms<bf16_t, bf16_t>(terms, a);
   else if (gain_dtype == GOOSE_DTYPE_BF16 && act_dtype == GOOSE_DTYPE_F16) launch_resid_norm_terms<bf16_t, _Float16>(terms, a);
   else if (gain_dtype == GOOSE_DTYPE_F16 && act_dtype == GOOSE_DTYPE_F16) launch_resid_norm_terms<_Float16, _Float16>(terms, a);
-  else if (gain_dtype == GOOSE_DTYPE_F32 && act_dtype == GOOSE_DTYPE_F32 && rope == nullptr) launch_resid_norm_t<float, float, 1>(a);
   else return GOOSE_ERR_ARG;
-  return goose_launch_status();
-}
-
-int launch_rope_kv(int dtype, const float* part, int S, size_t part_stride, size_t part_ld, int B, int n_heads,
-                   int head_dim, const int32_t* pos, const double* inv_freq, const int32_t* dP, int cap, void* qout,
-                   int ldq, void* kcache, void* vcache, int32_t* flags, hipStream_t st) {
-  dim3 grid(B, n_heads), block(head_dim / 2);
-  if (dtype == GOOSE_DTYPE_BF16)
-    hipLaunchKernelGGL(k_rope_kv<bf16_t>, grid, block, 0, st, part, S, part_stride, part_ld, n_heads, head_dim, pos,
-                       inv_freq, dP, cap, (bf16_t*)qout, ldq, (bf16_t*)kcache, (bf16_t*)vcache, flags);
-  else
-    hipLaunchKernelGGL(k_rope_kv<float>, grid, block, 0, st, part, S, part_stride, part_ld, n_heads, head_dim, pos,
-                       inv_freq, dP, cap, (float*)qout, ldq, (float*)kcache, (float*)vcache, flags);
-  return goose_launch_status();
-}
-
-int launch_swiglu_f32(const float* gu, size_t ld, int F, float* h, int ldh, int B, hipStream_t st) {
-  hipLaunchKernelGGL(k_swiglu_f32, dim3((F + 255) / 256, B), dim3(256), 0, st, gu, ld, F, h, ldh);
   return goose_launch_status();
 }
 
@@ -976,6 +932,14 @@ int launch_accept(const int32_t* parent, const int32_t* tokens, const uint8_t* i
                   int32_t* flags, hipStream_t st) {
   hipLaunchKernelGGL(k_accept, dim3(1), dim3(128), 0, st, parent, tokens, is_spine, argmax, B, accept_len, path,
                      bonus, next_root, dP, P_old, cap, flags);
+  return goose_launch_status();
+}
+
+int launch_commit_f32(const int32_t* parent, const int32_t* tokens, const uint8_t* is_spine, const int32_t* argmax, int B,
+                      int32_t* accept_len, int32_t* path, int32_t* bonus, int32_t* next_root, int32_t* dP, const int32_t* P_old,
+                      float* kall, float* vall, int n_layers, int n_heads, int cap, int head_dim, int32_t* flags, hipStream_t st) {
+  hipLaunchKernelGGL(k_commit_f32, dim3(2 * n_layers * n_heads), dim3(head_dim <= 128 && B <= 128 ? 128 : 256), 0, st, parent, tokens,
+                     is_spine, argmax, B, accept_len, path, bonus, next_root, dP, P_old, kall, vall, cap, head_dim, flags);
   return goose_launch_status();
 }
 
