@@ -79,9 +79,16 @@ struct SegDev {
 template <int TS>
 struct SegTable { SegDev s[TS]; };
 
+// Workgroups of four wavefronts of a batch's launch run in pairs on a compute unit, at most 256 registers a wavefront: a launch of 16 requests
+// x 32 heads is 512 of them, and while one sums its projection slices the other one streams its key blocks.  What a thread
+// prepares goes one item at a time instead of two for that (the pair of items took 335 registers).  16 requests x 32
+// nodes over 1024 slots, Llama-3-8B heads: 53.7 -> 36.8 us a layer, a pass over 8 layers 3074 -> 2956; 8 requests 23.3 -> 22.0, 3 requests
+// (a pass) 1294 -> 1285.  A single request has no second round of workgroups and keeps its loads together (HOLD below).
+constexpr bool paired(int D, int wavefronts, int TS) { return TS > 1 && D == 128 && wavefronts == 4; }
+
 // F16: fp16 instead of bf16 storage (caches, operands, probabilities, output).
 template <int D, int NG, int NQH, bool F16, int TS>
-__global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
+__global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) void k_attn_fused(
     // (what the first cache loads depend on comes first: the leading kernel arguments are preloaded)
     const SegTable<TS> segs, int n_heads, int n_kv_heads, int cap, const float* part, int ks, size_t part_stride,
     size_t part_ld, const float2* cs, const typename Mma16<F16>::T* __restrict__ gq,
@@ -100,6 +107,7 @@ __global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
   cs += (size_t)row0 * (D / 2);
   o_out += (size_t)row0 * ldo;
   constexpr int NTHR = 64 * NG * NQH;
+  constexpr bool PAIR = paired(D, NG * NQH, TS);
   constexpr int NS = D / 16;               // operand loads (1 KiB pieces) per block, for K and for V
   constexpr int TROWS = NQH * 32;          // tree rows the LDS buffers hold (>= B for this instantiation)
   constexpr int KROW = D * 2 + 16;         // bytes per K / Q row in LDS (padded)
@@ -148,11 +156,11 @@ __global__ __launch_bounds__(64 * NG * NQH) void k_attn_fused(
   const int rows = nbt * 32;
   constexpr int NIT = TROWS * (D / 8) / NTHR;
   static_assert(TROWS * (D / 8) % NTHR == 0 && NIT >= 1, "items must divide over the workgroup");
-  // Items are handled UG at a time.  With at most two per thread (trees of up to 64 nodes) their
-  // loads are issued here, before anything waits for the cache length; larger trees take them two
+  // Items are handled UG at a time.  With at most two per thread (trees of up to 64 nodes, see paired() for batches) their
+  // loads are issued here, before anything waits for the cache length; the others take them one or two
   // at a time in a loop further down (registers, and code that runs once is fetched at memory speed).
-  constexpr bool HOLD = NIT <= 2;
-  constexpr int UG = HOLD ? NIT : 2;
+  constexpr bool HOLD = NIT <= 2 && !PAIR;
+  constexpr int UG = HOLD ? NIT : (PAIR ? 1 : 2);
   static_assert(NIT % UG == 0, "item groups");
   const float* prow[UG];
   f32x4 acc[UG][6], acc1[UG][6];  // q lo/hi, k lo/hi, v lo/hi of the first / second slice
