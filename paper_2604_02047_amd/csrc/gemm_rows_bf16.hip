@@ -67,7 +67,8 @@ static_assert(WG_TILES == GOOSE_ROWS_TILES, "the LM head's reductions are one pe
 
 // TERMS: terms of the activation operand (gemm_bf16.hip): with two, every weight operand meets the hi
 // and then the lo operand of its rows, as in the skinny kernel
-template <int MT, int EPI, bool F16, int TERMS>
+// STREAM: the weights come through non-temporal loads (see launch_rows)
+template <int MT, int EPI, bool F16, int TERMS, bool STREAM>
 __global__ __launch_bounds__(256, 1) void k_gemm_rows(const typename Mma16<F16>::T* __restrict__ A, int lda,
                                                       const u32x4* __restrict__ Wp, int ntiles, int ksteps_total,
                                                       int stages_per_split, int B, void* __restrict__ out, size_t ldo,
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_rows(const typename Mma16<F16>:
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
-      wreg[slot][s][nt] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc[nt], w_lane, (i * STEPS + s) * 1024, 0);
+      wreg[slot][s][nt] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc[nt], w_lane, (i * STEPS + s) * 1024, STREAM ? 2 : 0);
 #endif
   };
   auto barrier = [&]() {  // (raw: __syncthreads would also drain every copy in flight)
@@ -426,18 +427,30 @@ struct RowsCall {
   float out_scale; int32_t* flags; hipStream_t st;
 };
 
-template <int MT, int EPI, bool F16, int TERMS>
-int launch_rows(const RowsCall& g) {
+template <int MT, int EPI, bool F16, int TERMS, bool STREAM>
+int launch_rows_as(const RowsCall& g) {
   const int ntiles = g.Npad / 32, ksteps = g.Kpad / 16;
   const int gx = (ntiles + WG_TILES - 1) / WG_TILES;
   const int nchunk = (g.B + 32 * MT - 1) / (32 * MT);
   const int granules = g.Kpad / 128;                        // split-K ranges are multiples of 128 inputs,
   const int gps = (granules + g.ksplit - 1) / g.ksplit;     // the same ranges as the skinny kernel's
   const dim3 grid((gx * g.ksplit + 7) / 8 * 8 * nchunk);
-  hipLaunchKernelGGL((k_gemm_rows<MT, EPI, F16, TERMS>), grid, dim3(256), 0, g.st, (const typename Mma16<F16>::T*)g.A, g.lda,
+  hipLaunchKernelGGL((k_gemm_rows<MT, EPI, F16, TERMS, STREAM>), grid, dim3(256), 0, g.st, (const typename Mma16<F16>::T*)g.A, g.lda,
                      (const u32x4*)g.Wp, ntiles, ksteps, gps * 2 * TERMS, g.B, g.out, g.ldo, g.split_stride, (float4*)g.top2,
                      g.n_valid, gx, g.ksplit, nchunk, g.out_scale, g.flags);
   return goose_launch_status();
+}
+
+// Non-temporal weights leave the lines of A in the L2 alone, and the chunks of an item run side by side, so the later ones still find
+// the weights there.  The loads of 28672 x 4096 at 256 / 512 rows on their own (copies, no arithmetic) take 53.5 / 61.6 us, plain 56.3 / 67.0; the
+// product 65.8 / 102.7 (69.4 / 105.6), O, down and q|k|v 0.5-1.5 us less each; passes of 16 / 14 / 8 requests over 8 layers 2909 / 2720 / 1905 us
+// (2931 / 2738 / 1943), 7 in two terms 2404 (2426).  Only gate/up with a second chunk of at most 32 rows, which runs ahead of the first, is slower:
+// 160 rows 66.1 (61.4), 192 rows 64.5 (64.5).
+template <int MT, int EPI, bool F16, int TERMS>
+int launch_rows(const RowsCall& g) {
+  if constexpr (MT == 4 && EPI == EPI_SWIGLU)
+    if (g.B <= 160) return launch_rows_as<MT, EPI, F16, TERMS, false>(g);
+  return launch_rows_as<MT, EPI, F16, TERMS, true>(g);
 }
 
 template <int EPI, bool F16, int TERMS>
