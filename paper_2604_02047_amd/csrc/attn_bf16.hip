@@ -28,6 +28,7 @@
 // lane).  Groups are merged through LDS; splits write (max, sum, unnormalised O) partials that
 // k_attn_merge combines in fixed order (a single split writes the normalised 16-bit rows itself).
 
+#include "fold.h"
 #include "goose_internal.h"
 #include "mma16.h"
 
@@ -1131,44 +1132,11 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* __restrict__ at
   // workgroup runs on the XCD whose L2 holds that head's partials
   const int qi = sg.row0 + r, h = blockIdx.x;
   const size_t base0 = (size_t)h * nsplit * Bpad + qi, step = Bpad;  // split s at base0 + s * step
-  constexpr int CH = 8;
-  f32x4 num = {0.f, 0.f, 0.f, 0.f};
-  float den = 0.f, mmax = NEG_BIG;
-  float2 ml[CH];
-  f32x4 ov[CH];
-  auto load = [&](int s0) {
-#pragma unroll
-    for (int k = 0; k < CH; ++k) {
-      const size_t base = base0 + (size_t)min(s0 + k, nsplit - 1) * step;
-      ml[k] = *reinterpret_cast<const float2*>(att_ml + base * 2);
-      ov[k] = *reinterpret_cast<const f32x4*>(att_o + base * D + c);
-    }
-  };
-  load(0);  // (sums and maxima together: the maxima first would be a second trip to memory)
-#pragma unroll
-  for (int k = 0; k < CH; ++k) mmax = fmaxf(mmax, ml[k].x);
-  for (int s0 = CH; s0 < nsplit; s0 += CH) {
-    float m[CH];
-#pragma unroll
-    for (int k = 0; k < CH; ++k) m[k] = att_ml[(base0 + (size_t)min(s0 + k, nsplit - 1) * step) * 2];
-#pragma unroll
-    for (int k = 0; k < CH; ++k) mmax = fmaxf(mmax, m[k]);
-  }
-  for (int s0 = 0;;) {
-#pragma unroll
-    for (int k = 0; k < CH; ++k) {
-      const float w = (s0 + k < nsplit) ? exp2f(ml[k].x - mmax) : 0.f;
-      den += w * ml[k].y;
-      num += w * ov[k];
-    }
-    s0 += CH;
-    if (s0 >= nsplit) break;
-    load(s0);
-  }
+  const f32x4 f4 = merge_splits(att_o, att_ml, base0, step, nsplit, D, c, []() {});
   u16x4 v, v2;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const float f = num[e] / den;
+    const float f = f4[e];
     v[e] = out_bits16(f, o_f16);
     v2[e] = out_bits16(f - out_back16(v[e], o_f16), o_f16);
   }
@@ -1273,7 +1241,7 @@ int pick_attn_splits(int n_heads, int keys_max, int max_splits) {
 int launch_attn_16(int dtype, const float* part, int ks, size_t part_stride, size_t part_ld, const void* cs,
                    int n_heads, int n_kv_heads, int head_dim, int cap, const AttnSeg* segs, int nseg, int splits_or_0,
                    int max_splits, int key_groups, const void* gq, const void* gk, float eps, float* att_o,
-                   float* att_ml, int Bpad, void* o, int ldo, int oterms, int o_dtype, int32_t* flags, hipStream_t st) {
+                   float* att_ml, int Bpad, void* o, int ldo, int oterms, int o_dtype, int32_t* flags, hipStream_t st, int* left) {
   if (dtype != GOOSE_DTYPE_BF16 && dtype != GOOSE_DTYPE_F16) return GOOSE_ERR_ARG;
   if (n_kv_heads < 1 || n_heads % n_kv_heads != 0 || (gq == nullptr) != (gk == nullptr)) return GOOSE_ERR_ARG;
   if (nseg < 1 || nseg > ATTN_MAX_SEGS || max_splits < 1 || (key_groups != 2 && key_groups != 4) || (cap & 31))
@@ -1306,7 +1274,8 @@ int launch_attn_16(int dtype, const float* part, int ks, size_t part_stride, siz
     const dim3 grid(n_heads, splits, n);
     int rc = head_dim == 128 ? launch_d<128>(cls, key_groups, grid, st, a, t) : launch_d<64>(cls, key_groups, grid, st, a, t);
     if (rc != GOOSE_OK) return rc;
-    if (splits == 1) continue;
+    if (left != nullptr) *left = splits;
+    if (splits == 1 || left != nullptr) continue;
     const int rows_per_wg = 1024 / head_dim;
     const dim3 mgrid(n_heads, (b_max + rows_per_wg - 1) / rows_per_wg, n);
     rc = a.f16 ? launch_merge<true>(mgrid, head_dim, st, a, splits, t)

@@ -356,6 +356,82 @@ static RopeArgs rope_args(const goose_ctx* c, const int32_t* pos, int rows) {
   return RopeArgs{pos, c->inv_freq, (float2*)c->rope_cs, rows, c->d.head_dim / 2};
 }
 
+// One decoder layer of a 16-bit model for a single row: the projections form their operand row themselves, which leaves six launches instead
+// of eight or nine.  The residual rows stay as they are until
+// the closing add, which takes the slices of both products that add to them, in the same order.
+static bool one_row(const goose_ctx* c, int B, int ks_qkv, int ks_o, int ks_down) {
+  const goose_model_desc& d = c->d;
+  const int widest = 1 << 20;  // (columns: far below the grid's limit)
+  return B == 1 && d.hidden <= ROW_MAX_HIDDEN && ks_o + ks_down <= c->max_ksplit && one_row_fits(c->Kh, ks_qkv, c->terms) &&
+         one_row_fits(c->Kq, ks_o, c->terms) && one_row_fits(c->Kh, 1, c->terms) && one_row_fits(c->Fpad, ks_down, c->terms) &&
+         d.ffn < widest && c->Hq + 2 * c->Hkv < widest;
+}
+static int layer_row(goose_ctx* c, const char* w, float* d_x, const AttnSeg& seg, int ks_qkv, int ks_o, int ks_down, hipStream_t st,
+                     bool xhat_ready, const void* g_next, const RopeArgs* rope) {
+  const goose_model_desc& d = c->d;
+  const size_t pstride = (size_t)c->Bpad * c->part_ld;
+  const int H = d.hidden, T = c->terms;
+  const int Nqkv = round_up(c->Hq + 2 * c->Hkv, 32), Nh = round_up(H, 32), Ngu = 2 * round_up(d.ffn, 32);
+  const int g_f16 = d.dtype == GOOSE_DTYPE_F16;
+  OneRow r{};
+  r.kind = xhat_ready ? ROW_COPY : ROW_NORM;
+  r.src = xhat_ready ? c->xn : (const void*)d_x;
+  r.H = H;
+  r.g = w + c->pl.g1;
+  r.g_f16 = g_f16;
+  r.eps = d.rms_eps;
+  if (rope != nullptr) r.rope = *rope;
+  int rc;
+  { PROF(PK_GEMM_QKV);
+    rc = launch_gemm_row_16(c->act_dtype, EPI_PARTIAL, r, T, w + c->pl.wqkv, Nqkv, c->Kh, ks_qkv, c->part, pstride,
+                            c->out_scale, c->flags, st); }
+  if (rc) return rc;
+  int splits = 1;
+  { PROF(PK_ATTN);
+    rc = launch_attn_16(d.dtype, c->part, ks_qkv, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, &seg, 1,
+                        env_int("GOOSE_ATTN_SPLITS", 0), c->max_splits, 4, d.qk_norm ? w + c->pl.gq : nullptr,
+                        d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o, T, c->act_dtype,
+                        c->flags, st, &splits); }
+  if (rc) return rc;
+  r = OneRow{};
+  r.kind = splits > 1 ? ROW_MERGE : ROW_COPY;
+  r.src = c->o;
+  r.H = c->Hq;
+  r.part = c->att_o;
+  r.S = splits;
+  r.att_ml = c->att_ml;
+  r.Bpad = c->Bpad;
+  r.head_dim = d.head_dim;
+  { PROF(PK_GEMM_O);
+    rc = launch_gemm_row_16(c->act_dtype, EPI_PARTIAL, r, T, w + c->pl.wo, Nh, c->Kq, ks_o, c->part, pstride, c->out_scale,
+                            c->flags, st); }
+  if (rc) return rc;
+  r = OneRow{};
+  r.kind = ROW_NORM;
+  r.src = d_x;
+  r.H = H;
+  r.part = c->part;
+  r.S = ks_o;
+  r.part_stride = pstride;
+  r.g = w + c->pl.g2;
+  r.g_f16 = g_f16;
+  r.eps = d.rms_eps;
+  { PROF(PK_GEMM_GATE_UP);
+    rc = launch_gemm_row_16(c->act_dtype, EPI_SWIGLU, r, T, w + c->pl.wgu, Ngu, c->Kh, 1, c->h, 0, c->out_scale,
+                            c->flags, st); }
+  if (rc) return rc;
+  r = OneRow{};
+  r.kind = ROW_COPY;
+  r.src = c->h;
+  { PROF(PK_GEMM_DOWN);
+    rc = launch_gemm_row_16(c->act_dtype, EPI_PARTIAL, r, T, w + c->pl.wd, Nh, c->Fpad, ks_down, c->part + (size_t)ks_o * pstride, pstride,
+                            c->out_scale, c->flags, st); }
+  if (rc) return rc;
+  PROF(PK_NORM);
+  return launch_resid_norm(d.dtype, c->act_dtype, d_x, H, c->part, ks_o + ks_down, pstride, c->part_ld, g_next, d.rms_eps,
+                           g_next ? c->xn : nullptr, g_next ? c->ld_xn : 0, T, 1, st);
+}
+
 // One decoder layer of a 16-bit model.  `xhat_ready`: the operand buffer already holds RMSNorm(x)*g1 (the previous
 // layer's closing kernel wrote it); `rope`, with xhat_ready false only: the rotary angles of the
 // tree, written by the launch that normalises.  dP null: the cache length is P.  `g_next`: gain of the normalisation that follows this layer
@@ -371,6 +447,12 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   const goose_model_desc& d = c->d;
   const size_t pstride = (size_t)c->Bpad * c->part_ld;
   const int H = d.hidden, Hq = c->Hq;
+  const int Nqkv = round_up(Hq + 2 * c->Hkv, 32), Nh = round_up(H, 32), Ngu = 2 * round_up(d.ffn, 32);
+  const GemmCfg cq = gemm_cfg(c, "GOOSE_CFG_QKV", Nqkv, c->Kh), co = gemm_cfg(c, "GOOSE_CFG_O", Nh, c->Kq),
+                cd = gemm_cfg(c, "GOOSE_CFG_DOWN", Nh, c->Fpad);
+  const AttnSeg whole{0, B, P, d_kcache, d_vcache, dP, d_mask};
+  if (nseg == 0 && one_row(c, B, cq.ks, co.ks, cd.ks))
+    return layer_row(c, w, d_x, whole, cq.ks, co.ks, cd.ks, st, xhat_ready, g_next, rope);
 
   // x_hat = RMSNorm(x) * g1
   if (!xhat_ready) {
@@ -381,9 +463,7 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   if (rc) return rc;
 
   const int T = c->terms;
-  const int Nqkv = round_up(Hq + 2 * c->Hkv, 32), Nh = round_up(H, 32), Ngu = 2 * round_up(d.ffn, 32);
   static const int splits_env = env_int("GOOSE_ATTN_SPLITS", 0);
-  const GemmCfg cq = gemm_cfg(c, "GOOSE_CFG_QKV", Nqkv, c->Kh);
   int ks = cq.ks;
   { PROF(PK_GEMM_QKV);
     rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->xn, c->ld_xn, T, w + c->pl.wqkv, Nqkv, c->Kh, B, cq.nw, ks,
@@ -391,7 +471,6 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   if (rc) return rc;
   // rotary embedding of q and k, KV rows of the tree into the cache, tree attention: one kernel
   static const int ng_env = env_int("GOOSE_ATTN_NG", 4) == 2 ? 2 : 4;
-  const AttnSeg whole{0, B, P, d_kcache, d_vcache, dP, d_mask};
   if (nseg == 0) { segs = &whole; nseg = 1; }
   { PROF(PK_ATTN);
     rc = launch_attn_16(d.dtype, c->part, ks, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, segs,
@@ -399,7 +478,6 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
                           d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o,
                           T, c->act_dtype, c->flags, st); }
   if (rc) return rc;
-  const GemmCfg co = gemm_cfg(c, "GOOSE_CFG_O", Nh, c->Kq);
   ks = co.ks;
   { PROF(PK_GEMM_O);
     rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->o, c->ld_o, T, w + c->pl.wo, Nh, c->Kq, B, co.nw, ks, c->part,
@@ -415,7 +493,6 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
     rc = launch_gemm_16(c->act_dtype, EPI_SWIGLU, c->xn, c->ld_xn, T, w + c->pl.wgu, Ngu, c->Kh, B, gu_nw, 1, c->h,
                         (size_t)c->ld_h, 0, c->out_scale, c->flags, st); }
   if (rc) return rc;
-  const GemmCfg cd = gemm_cfg(c, "GOOSE_CFG_DOWN", Nh, c->Fpad);
   ks = cd.ks;
   { PROF(PK_GEMM_DOWN);
     rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->h, c->ld_h, T, w + c->pl.wd, Nh, c->Fpad, B, cd.nw, ks,

@@ -196,6 +196,26 @@ enum { GOOSE_ROWS_TILES = 8 };
 int launch_gemm_rows_16(int dtype, int epi, const void* A, int lda, int terms, const void* Wp, int Npad, int Kpad, int B,
                         int ksplit, void* out, size_t ldo, size_t out_split_stride, void* top2, int n_valid, float out_scale,
                         int32_t* flags, hipStream_t st);
+// The same products for one row, which the kernel itself forms (gemm_row_bf16.hip), with the same bits:
+enum { ROW_MAX_HIDDEN = 8192 };
+enum { ROW_COPY, ROW_NORM, ROW_MERGE };
+struct OneRow {
+  int kind;
+  const void* src;  // COPY: the operand row.  NORM: x (f32 [H])
+  int H;            // columns (NORM; MERGE: n_heads * head_dim); the padding up to Kpad becomes zero
+  const float* part;  // NORM: S slices to add to x.  MERGE: the attention's partial outputs (row 0 of the Bpad of every head and split), S of them
+  int S;
+  size_t part_stride;
+  const void* g;        // NORM: gain, bf16 or (g_f16) fp16
+  int g_f16;
+  float eps;
+  RopeArgs rope;        // NORM: rows > 0: the same launch writes these angles
+  const float* att_ml;  // MERGE
+  int Bpad, head_dim;
+};
+bool one_row_fits(int Kpad, int ksplit, int terms);
+int launch_gemm_row_16(int dtype, int epi, const OneRow& row, int terms, const void* Wp, int Npad, int Kpad, int ksplit, void* out,
+                       size_t out_split_stride, float out_scale, int32_t* flags, hipStream_t st);
 // Projection whose workgroups (nw column tiles each) also emit per-row (max, second max, index of
 // max) over their valid columns (< n_valid): top2 is float4 [B][ceil(Npad/32/nw)], index bits in .z.
 // `out` (f32 [B][ldo]) may be null when only the reduction is wanted.  nw is 2 or 4, and GOOSE_ROWS_TILES beyond 128 rows.
@@ -237,8 +257,10 @@ enum { ATTN_MAX_SEGS = 16 };
 // (the operand layout of the O projection, see launch_gemm_16).
 // Requests with the same number of 32-row query tiles share one launch
 // (grid z = request).  splits_or_0: key splits per head, 0 = chosen here (at most max_splits).
+// left (a single request): the splits are not merged into o and their number goes to *left; with 1 there is nothing to merge and o is written.
 int launch_attn_16(int dtype, const float* part, int ks, size_t part_stride, size_t part_ld, const void* cs,
                    int n_heads, int n_kv_heads, int head_dim, int cap, const AttnSeg* segs, int nseg, int splits_or_0,
                    int max_splits, int key_groups, const void* gq, const void* gk, float eps, float* att_o,
-                   float* att_ml, int Bpad, void* o, int ldo, int oterms, int o_dtype, int32_t* flags, hipStream_t st);
+                   float* att_ml, int Bpad, void* o, int ldo, int oterms, int o_dtype, int32_t* flags, hipStream_t st,
+                   int* left = nullptr);
 int pick_attn_splits(int n_heads, int keys_max, int max_splits);

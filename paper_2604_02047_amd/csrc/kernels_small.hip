@@ -2,6 +2,7 @@
 // RMSNorm, rotary embedding + KV-tail write, argmax, greedy walk, KV compaction.
 #include <limits.h>
 
+#include "fold.h"
 #include "goose_internal.h"
 
 namespace {
@@ -135,17 +136,6 @@ __device__ inline void store4<_Float16>(_Float16* p, float a, float b, float c, 
   *reinterpret_cast<f16x4*>(p) = v;
 }
 
-// (cos, sin) of pos[m] * base^(-2j/d): the angle is reduced in double, then evaluated in float
-// (|error| ~ 1e-7 rad at any position).
-__device__ inline void rope_entry(const RopeArgs& a, int m, int j) {
-  double ang = (double)a.pos[m] * a.inv_freq[j];
-  const double two_pi = 6.283185307179586476925286766559;
-  ang -= two_pi * rint(ang / two_pi);
-  float sn, c;
-  sincosf((float)ang, &sn, &c);
-  a.cs[(size_t)m * a.half + j] = make_float2(c, sn);
-}
-
 // TERMS = 2 (16-bit types): xn is written as hi + lo, lo = T(v - hi), in groups of eight columns
 // (8 hi values, then their 8 lo values; row length 2 * columns): the operand layout of the projections.
 // Tg: type of the gains; T: type of xn (fp16 activations may meet bf16 gains).
@@ -172,23 +162,9 @@ __global__ __launch_bounds__(NTHR) void k_resid_norm(float* __restrict__ x, int 
     const int c4 = threadIdx.x + i * NTHR;
     if (c4 < nvec) {
       float4 a = *reinterpret_cast<const float4*>(xr + c4 * 4);
-      // the slices are added in index order, four loads in flight at a time (one load per loop
-      // round would make every slice its own trip to memory)
-      const float* pp = part + (size_t)m * part_ld + c4 * 4;
-      int s = 0;
-      for (; s + 4 <= S; s += 4) {
-        float4 p[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) p[k] = *reinterpret_cast<const float4*>(pp + (size_t)(s + k) * part_stride);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) { a.x += p[k].x; a.y += p[k].y; a.z += p[k].z; a.w += p[k].w; }
-      }
-      for (; s < S; ++s) {
-        const float4 p = *reinterpret_cast<const float4*>(pp + (size_t)s * part_stride);
-        a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
-      }
+      add_slices(a, part + (size_t)m * part_ld + c4 * 4, S, part_stride);
       if (S > 0) *reinterpret_cast<float4*>(xr + c4 * 4) = a;
-      ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
+      ss = add_squares(ss, a);
       v[i] = a;
     }
   }
