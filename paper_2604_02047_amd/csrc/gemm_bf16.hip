@@ -561,7 +561,9 @@ int launch_pack_16(int mode, const void* s0, const void* s1, const void* s2, int
 // workgroup count, every split at least 4 stages long.  With at most two row tiles (64 rows) half
 // the splits of two-wavefront workgroups stream as fast when that still gives 256 workgroups (the
 // 7B O and down projections: 4 splits instead of 8, and a microsecond less in each residual
-// kernel); with more rows the narrower workgroup's extra copies of the A block cost more than that.
+// kernel).  Exactly 256: beyond that some units get two of them and the launch takes as long as those, so the workgroups stay four
+// wavefronts wide, dealt over 256 (33B q|k|v, 624 tiles: 312 narrow workgroups 54 us, 256 wide ones 42; layers of 5 / 33 / 64 nodes 210.1 /
+// 230.3 / 236.5 -> 197.9 / 210.7 / 217.5 us, 40 in two terms 273.2 -> 241.8).  With more rows the narrower workgroup's extra copies of the A block cost more than that.
 void pick_gemm_config(int Npad, int Kpad, int max_ksplit, int max_rows, int* nw_out, int* ksplit_out) {
   const int ntiles = Npad / 32, nstages = Kpad / KGRAN;
   const int groups4 = (ntiles + 3) / 4, groups2 = (ntiles + 1) / 2;
@@ -573,7 +575,7 @@ void pick_gemm_config(int Npad, int Kpad, int max_ksplit, int max_rows, int* nw_
   int nw = groups4 * ks >= 160 ? 4 : 2;
   if (nw == 4 && ks >= 2 && max_rows <= 64 && groups2 * (ks / 2) >= 256) {
     ks /= 2;
-    nw = 2;
+    nw = groups2 * ks <= 256 ? 2 : 4;
   }
   // Contexts of more than 256 rows: a range of fewer than 8 stages writes and reads back as many bytes of partial sums as it multiplies
   // for, so ranges are joined where three quarters of the chip still have a workgroup of 128 rows x 256 columns (Llama-3-8B's O projection, 8 -> 4 ranges:
