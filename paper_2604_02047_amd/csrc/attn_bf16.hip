@@ -32,6 +32,8 @@
 #include "goose_internal.h"
 #include "mma16.h"
 
+#include <type_traits>
+
 namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -39,6 +41,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
+#define GOOSE_N(n) std::integral_constant<int, (n)>()
 constexpr float NEG_BIG = -1e30f;  // finite stand-in for -inf: keeps exp2(m_old - m_new) well defined
 constexpr int TAIL_COST = 3;       // a tree block costs the last split about this many prefix blocks
 
@@ -150,9 +153,9 @@ __global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) v
   const bool last = blockIdx.y == gridDim.y - 1;
   // ---- q of all query tiles (every split), k and v of the tree (last split): sum the split-K
   // slices, rotate q and k, bf16 into LDS.  One item = 4 columns j0.. and their rotation partners
-  // j0+d/2..: 16 neighbouring lanes read 256 contiguous bytes of a projection row.  The loads of
-  // the first two slices of all of a thread's items are issued together: the buffer was written
-  // by another kernel, so every dependent load is a trip to memory.
+  // j0+d/2..: 16 neighbouring lanes read 256 contiguous bytes of a projection row.  The buffer was written
+  // by another kernel, so every dependent load is a trip to memory: the loads of the first SG slices of UG items are issued
+  // together, and further slices FG at a time.
   const int nbt = (B + 31) >> 5;
   const int rows = nbt * 32;
   constexpr int NIT = TROWS * (D / 8) / NTHR;
@@ -163,12 +166,26 @@ __global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) v
   constexpr bool HOLD = NIT <= 2 && !PAIR;
   constexpr int UG = HOLD ? NIT : (PAIR ? 1 : 2);
   static_assert(NIT % UG == 0, "item groups");
+  // Grouped queries with their narrow q|k|v product have four slices.  One at a time beyond the second: layers of Qwen3-8B, 33 nodes, 102.3 us
+  // (now 100.8), Llama-3-8B in two terms, 61 nodes, 144.8 (143.3); passes over 8 layers of 8 / 16 requests 1971 / 3072 (1952 / 3058).
+  constexpr int SG = PAIR ? 4 : 2, FG = PAIR || HOLD ? 2 : 1;
+  // Where those loads need the registers of the first block's values, these are fetched behind them (they are used after scores and softmax).
+  constexpr bool LATE_V = PAIR || (HOLD && NQH == 2 && D == 128);
   const float* prow[UG];
-  f32x4 acc[UG][6], acc1[UG][6];  // q lo/hi, k lo/hi, v lo/hi of the first / second slice
+  f32x4 acc[UG][6], more[SG - 1][UG][6];  // q lo/hi, k lo/hi, v lo/hi of the first slice / of those loaded with it
   f32x4 c01[UG], c23[UG];         // the rotation angles: cos, sin of columns j0, j0+1 / j0+2, j0+3
   bool kv[UG];
   const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-  const bool two = ks > 1;
+  auto load_slice = [&](int u, int sl, f32x4 (&dst)[6], auto lo_c, auto hi_c) {  // of q, k, v those from lo to hi - 1; a slice that is not there: zeros
+    const float* p = prow[u] + sl * part_stride;
+#pragma unroll
+    for (int w = decltype(lo_c)::value; w < decltype(hi_c)::value; ++w) {
+      const bool on = (w == 0 || kv[u]) && sl < ks;
+      const int col = w == 0 ? 0 : (w == 1 ? kcol : vcol);
+      dst[2 * w] = on ? *reinterpret_cast<const f32x4*>(p + col) : zero4;
+      dst[2 * w + 1] = on ? *reinterpret_cast<const f32x4*>(p + col + D / 2) : zero4;
+    }
+  };
   auto load_items = [&](int u0) {
 #pragma unroll
     for (int u = 0; u < UG; ++u) {
@@ -176,16 +193,9 @@ __global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) v
       const int i = it / (D / 8), j0 = (it % (D / 8)) * 4;
       prow[u] = part + (size_t)i * part_ld + h * D + j0;  // row i < Bpad exists in the buffer
       kv[u] = last && i < B;
-      const float* p1 = prow[u] + part_stride;
+      load_slice(u, 0, acc[u], GOOSE_N(0), GOOSE_N(3));
 #pragma unroll
-      for (int w = 0; w < 3; ++w) {
-        const bool on = w == 0 || kv[u];
-        const int col = w == 0 ? 0 : (w == 1 ? kcol : vcol);
-        acc[u][2 * w] = on ? *reinterpret_cast<const f32x4*>(prow[u] + col) : zero4;
-        acc[u][2 * w + 1] = on ? *reinterpret_cast<const f32x4*>(prow[u] + col + D / 2) : zero4;
-        acc1[u][2 * w] = (on && two) ? *reinterpret_cast<const f32x4*>(p1 + col) : zero4;
-        acc1[u][2 * w + 1] = (on && two) ? *reinterpret_cast<const f32x4*>(p1 + col + D / 2) : zero4;
-      }
+      for (int k = 1; k < SG; ++k) load_slice(u, k, more[k - 1][u], GOOSE_N(0), GOOSE_N(3));
       c01[u] = *reinterpret_cast<const f32x4*>(cs + (size_t)i * (D / 2) + j0);
       c23[u] = *reinterpret_cast<const f32x4*>(cs + (size_t)i * (D / 2) + j0 + 2);
     }
@@ -261,25 +271,37 @@ __global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) v
     }
   };
   // the first block is on its way while q (and the tree's k, v) are prepared
-  if (nblk > 0) { fetch_k(0); fetch_v(0); }
+  if (nblk > 0) {
+    fetch_k(0);
+    if (!LATE_V) fetch_v(0);
+  }
 
   auto finish_items = [&](int u0) {
+    // the sums take the slices in their order
 #pragma unroll
-    for (int u = 0; u < UG; ++u)
+    for (int k = 0; k < SG - 1; ++k)
 #pragma unroll
-      for (int w = 0; w < 6; ++w) acc[u][w] += acc1[u][w];
-    for (int sl = 2; sl < ks; ++sl) {
+      for (int u = 0; u < UG; ++u)
 #pragma unroll
-      for (int u = 0; u < UG; ++u) {
-        const float* p = prow[u] + sl * part_stride;
+        for (int w = 0; w < 6; ++w) acc[u][w] += more[k][u][w];
+    // further slices FG at a time; q and k, then v (registers)
+    for (int sl = SG; sl < ks; sl += FG) {
+      auto add = [&](auto lo_c, auto hi_c) {
+        constexpr int lo = decltype(lo_c)::value, hi = decltype(hi_c)::value;
+        f32x4 t[FG][UG][6];
 #pragma unroll
-        for (int w = 0; w < 3; ++w)
-          if (w == 0 || kv[u]) {
-            const int col = w == 0 ? 0 : (w == 1 ? kcol : vcol);
-            acc[u][2 * w] += *reinterpret_cast<const f32x4*>(p + col);
-            acc[u][2 * w + 1] += *reinterpret_cast<const f32x4*>(p + col + D / 2);
-          }
-      }
+        for (int k = 0; k < FG; ++k)
+#pragma unroll
+          for (int u = 0; u < UG; ++u) load_slice(u, sl + k, t[k][u], lo_c, hi_c);
+#pragma unroll
+        for (int k = 0; k < FG; ++k)
+#pragma unroll
+          for (int u = 0; u < UG; ++u)
+#pragma unroll
+            for (int w = 2 * lo; w < 2 * hi; ++w) acc[u][w] += t[k][u][w];
+      };
+      add(GOOSE_N(0), GOOSE_N(2));
+      if (last) add(GOOSE_N(2), GOOSE_N(3));
     }
     if (gq != nullptr) {
       // per-head RMSNorm of q and k over the head's D columns: the D/8 items of a row sit in
@@ -359,6 +381,7 @@ __global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) v
       finish_items(u0);
     }
   }
+  if (LATE_V && nblk > 0) fetch_v(0);
   __syncthreads();
 
   // ---- this wavefront's q operand and ancestor row
