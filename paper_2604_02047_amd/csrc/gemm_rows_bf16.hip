@@ -444,12 +444,15 @@ int launch_rows_as(const RowsCall& g) {
 // Non-temporal weights leave the lines of A in the L2 alone, and the chunks of an item run side by side, so the later ones still find
 // the weights there.  The loads of 28672 x 4096 at 256 / 512 rows on their own (copies, no arithmetic) take 53.5 / 61.6 us, plain 56.3 / 67.0; the
 // product 65.8 / 102.7 (69.4 / 105.6), O, down and q|k|v 0.5-1.5 us less each; passes of 16 / 14 / 8 requests over 8 layers 2909 / 2720 / 1905 us
-// (2931 / 2738 / 1943), 7 in two terms 2404 (2426).  Only gate/up with a second chunk of at most 32 rows, which runs ahead of the first, is slower:
-// 160 rows 66.1 (61.4), 192 rows 64.5 (64.5).
+// (2931 / 2738 / 1943), 7 in two terms 2404 (2426).  A short last chunk has little of A to copy and runs ahead of the others, whose weights
+// then have left the L2 again: below three quarters of the height they are loaded plainly.  Passes of 5 / 6 / 9 requests and of five of 48 nodes
+// 1704 / 1762 / 2135 / 2170 us, non-temporal throughout 1743 / 1780 / 2211 / 2191 (9 requests on another card 2064, 2197); 11 requests
+// (352 rows, the last chunk five sixths full) 2164 plain, 2156 non-temporal, 12 (full) 2300, 2246.
 template <int MT, int EPI, bool F16, int TERMS>
 int launch_rows(const RowsCall& g) {
-  if constexpr (MT == 4 && EPI == EPI_SWIGLU)
-    if (g.B <= 160) return launch_rows_as<MT, EPI, F16, TERMS, false>(g);
+  constexpr int H = 32 * MT;
+  const int last = g.B - (g.B - 1) / H * H;
+  if (g.B > H && 4 * last < 3 * H) return launch_rows_as<MT, EPI, F16, TERMS, false>(g);
   return launch_rows_as<MT, EPI, F16, TERMS, true>(g);
 }
 
