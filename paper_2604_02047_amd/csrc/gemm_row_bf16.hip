@@ -12,7 +12,8 @@
 // weights: loads return in order, and the gains asked for after them cost 1.5 us a launch.  For the same reason a second row, whose loads
 // would follow, made a layer of two rows slower than its launches (94.1 against 92.7 us), and more weights in flight first make everything wait
 // (four stages of 128 inputs 91.9 us).
-// Layers of one row: 7B over 1024 slots 92.9 -> 89.1 us, 13B 124.1 -> 119.9, 33B 209.0 -> 204.9, Qwen3-8B in two terms over 5000 100.5 -> 93.1.
+// Layers of one row: 7B over 1024 slots 92.6 -> 88.3 us, over 16000 128.2 -> 123.7, 13B 124.6 -> 118.5, 33B 209.2 -> 186.1, Qwen3-8B in two terms over 5000
+// 101.0 -> 94.1.
 #include "fold.h"
 #include "goose_internal.h"
 #include "mma16.h"
