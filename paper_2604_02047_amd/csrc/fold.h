@@ -20,9 +20,9 @@ static __device__ __forceinline__ void add_slices(float4& a, const float* p, int
   }
 }
 
-// ss + the squares of a, each step rounded as written
+// ss + the squares of a, each step rounded as written: y first (the order that every norm here has had; another one moves results in rare places)
 static __device__ __forceinline__ float add_squares(float ss, const float4& a) {
-  return ss + fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.y, a.y, a.x * a.x)));
+  return ss + fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.x, a.x, a.y * a.y)));
 }
 
 // (cos, sin) of pos[m] * base^(-2j/d): the angle is reduced in double, then evaluated in float
