@@ -577,15 +577,6 @@ void pick_gemm_config(int Npad, int Kpad, int max_ksplit, int max_rows, int* nw_
     ks /= 2;
     nw = groups2 * ks <= 256 ? 2 : 4;
   }
-  // Contexts of more than 256 rows: a range of fewer than 8 stages writes and reads back as many bytes of partial sums as it multiplies
-  // for, so ranges are joined where three quarters of the chip still have a workgroup of 128 rows x 256 columns (Llama-3-8B's O projection, 8 -> 4 ranges:
-  // 27 -> 23 us at 512 rows, 21 -> 21 at 384, and half of the residual kernel's reads; passes of 16 / 14 / 12 / 10 requests over 8 layers
-  // 3135 / 2916 / 2639 / 2449 -> 3035 / 2809 / 2543 / 2385 us, 8 requests in such a context 1925 -> 1943).  Joining longer ranges too costs more than it gives: down
-  // (14 stages) 3113 / 2890 / 2680 / 2488, q|k|v (8 stages) 3097 / 2888 / 2639 / 2460, and 8 requests in such a context 4-5 % more.
-  if (max_rows > 256) {
-    const int wide = (Npad + 255) / 256 * ((max_rows + 127) / 128);
-    while (ks >= 2 && nstages < 8 * ks && wide * (ks / 2) >= 192) ks /= 2;
-  }
   *nw_out = nw;
   *ksplit_out = ks;
 }

@@ -33,3 +33,23 @@ def test_slices_of_every_number_of_ranges(hidden, kv, norm, dtype):
         tokens = gi.draft_tokens_uniform(5, tree.parent, shape.vocab, root)
         _compare_step(shape, gm, om, device_cache_as_oracle(gm, gm.P), np.asarray(tokens, np.int32), tree, tol_for(shape))
     gm.ctx.close()
+
+
+@pytest.mark.parametrize("kv,dtype", [(8, "bf16"), (32, "f16")])
+def test_contexts_of_more_rows_give_the_same_bits(kv, dtype):
+    """A K range's sum is part of a result, so the O product (eight ranges here) has the same ones in contexts of 128, 256 and 512 rows."""
+    shape = gi.ModelShape("context", 1, 4096, 32, 128, 512, 512, dtype=dtype, n_kv_heads=kv)
+    tm = torch_model(shape, seed=9, gain_jitter=0.1)
+    first = None
+    for max_rows in (128, 256, 512):
+        gm = gpu_model(shape, tm, max_B=128, cap=256, max_rows=max_rows)
+        got = []
+        for B in (40, 1):
+            gm.set_P(0)
+            root = int(_gpu_prefill(gm, gi.prefix_tokens(3, 90, shape.vocab), 64)["argmax"][-1].item())
+            tree = gi.tree_random(B, seed=3, spine_len=8) if B > 1 else gi.tree_single()
+            tokens = np.asarray(gi.draft_tokens_uniform(5, tree.parent, shape.vocab, root), np.int32)
+            got.append(gm.verify_step_calls(tokens, tree.parent, tree.is_spine, want_logits=True)["logits"].clone())
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
+        gm.ctx.close()
