@@ -167,8 +167,37 @@ __global__ __launch_bounds__(256) void k_proj_f32(const F32Proj p) {
     const float sq = wave_sum8(ss, lane, &sq_lo), v = sq / (float)K + p.eps;
     const float y = 1.0f / sqrtf(v), h = v * y, h_lo = fmaf(v, y, -h);
     const float y_lo = 0.5f * y * (fmaf(-h, y, 1.0f) - h_lo * y);
+    // A row whose squares or sums leave the range (finite values from about 1e18 on, infinities, NaN) has no such product: it is scaled
+    // before it is summed, and squares that overflow scale it to zeros.
+    bool beyond = !(v < INFINITY);
+#pragma unroll
+    for (int u = 0; u < NW; ++u) beyond = beyond || !(fabsf(s[u]) < INFINITY);
 #pragma unroll
     for (int u = 0; u < NW; ++u) s[u] = fmaf(s[u], y, fmaf(s[u], y_lo, s_lo[u] * y));
+    if (__any(beyond)) {
+      float scale[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) scale[r] = __shfl(y, 8 * r, 64);
+#pragma unroll
+      for (int u = 0; u < NW; ++u)
+#pragma unroll
+        for (int r = 0; r < 8; ++r) acc[u][r] = 0.f;
+#pragma unroll 1
+      for (int k = lane; k < K; k += 64) {
+        const float gk = p.g[k];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const float xn = a[r][k] * scale[r] * gk;
+          acc[0][r] += xn * w0[k];
+          if constexpr (NW == 2) acc[1][r] += xn * w1[k];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        const float scaled = wave_sum8(acc[u], lane, &sq_lo);
+        if (beyond) s[u] = scaled;
+      }
+    }
   }
   if constexpr (KW == 4) {  // (resid only: one sum a row)
     __shared__ float sums[4][8];

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import goose_inputs as gi
+from oracle import goose_oracle as orc
 from util import gpu_model, oracle_model, torch_model
 from test_gpu_parity import TOL, _compare_step
 
@@ -73,4 +74,38 @@ def test_a_node_without_finite_values_stays_alone():
                                         commit=False)["logits"])
     rest = [i for i in range(9) if i != 3]
     assert torch.equal(out[0][rest], out[1][rest]) and torch.isfinite(out[1][rest]).all()
+    gm.ctx.close()
+
+
+@pytest.mark.parametrize("hidden", [256, 260])
+def test_rows_beyond_the_range_of_a_sum(hidden):
+    """Squares of a finite row that overflow scale it to zeros; sums that would overflow before they are scaled do not; an infinity gives NaN."""
+    shape = gi.ModelShape("f32", 2, hidden, 4, 64, 516, 300, dtype="f32")
+    tm = torch_model(shape, seed=4, gain_jitter=0.1)
+    tm["lm_head"][7] *= 1e25
+    tm["embed"][5] = tm["embed"][50] * 1e22     # (embedding values are about 0.02)
+    tm["embed"][6] = tm["embed"][50] * 1e18
+    tm["embed"][8, 3] = float("inf")
+    gm = gpu_model(shape, tm, max_B=16, cap=256)
+    om = oracle_model(shape, tm)
+    for at in (1, 9):                           # in both groups of eight rows
+        tokens = np.arange(20, 31, dtype=np.int32)
+        tokens[at] = 5
+        tokens[at - 1] = 6
+        gm.set_P(0)
+        gm.kcache.fill_(float("nan"))
+        gm.vcache.fill_(float("nan"))
+        tree = gi.tree_star(11)
+        logits = gm.verify_step_calls(tokens, tree.parent, tree.is_spine, want_logits=True, commit=False)["logits"]
+        k, v = gm.k_rows(0, 11), gm.v_rows(0, 11)
+        zero = [at]
+        rest = [i for i in range(11) if i != at]
+        assert not logits[zero].any() and not k[:, :, zero].any() and not v[:, :, zero].any()
+        assert torch.isfinite(logits).all() and torch.isfinite(k).all() and torch.isfinite(v).all()
+        ref = orc.tree_logits(om, orc.empty_cache(om), tokens[rest], gi.tree_star(10).parent)[0]
+        assert np.abs(logits[rest].cpu().numpy() - ref).max(0)[7] <= TOL["f32"] * np.abs(ref[:, 7]).max()
+        small = [c for c in range(300) if c != 7]
+        assert np.abs(logits[rest].cpu().numpy() - ref)[:, small].max() <= TOL["f32"] * np.abs(ref[:, small]).max()
+    tokens[9] = 8
+    assert torch.isnan(gm.verify_step_calls(tokens, tree.parent, tree.is_spine, want_logits=True, commit=False)["logits"][9]).all()
     gm.ctx.close()
