@@ -233,13 +233,16 @@ int goose_create_batched(const goose_model_desc* desc, int max_B, int max_rows, 
   c->part_ld = widest;
   int rc = GOOSE_OK;
   auto A = [&](void** p, size_t bytes) { if (rc == GOOSE_OK) rc = dev_alloc(p, bytes); };
-  A(&c->xn, (size_t)c->Bpad * c->ld_xn * es);
-  A((void**)&c->part, (size_t)c->max_ksplit * c->Bpad * c->part_ld * sizeof(float));
-  A(&c->q, (size_t)c->Bpad * c->Kq * es);
+  if (is16(d.dtype)) {
+    A(&c->xn, (size_t)c->Bpad * c->ld_xn * es);
+    A((void**)&c->part, (size_t)c->max_ksplit * c->Bpad * c->part_ld * sizeof(float));
+    A((void**)&c->att_o, (size_t)d.n_heads * c->max_splits * c->Bpad * d.head_dim * sizeof(float));
+    A((void**)&c->att_ml, (size_t)d.n_heads * c->max_splits * c->Bpad * 2 * sizeof(float));
+  } else {
+    A(&c->q, (size_t)c->Bpad * c->Kq * es);
+  }
   A(&c->o, (size_t)c->Bpad * c->ld_o * es);
   A(&c->h, (size_t)c->Bpad * c->ld_h * es);
-  A((void**)&c->att_o, (size_t)d.n_heads * c->max_splits * c->Bpad * d.head_dim * sizeof(float));
-  A((void**)&c->att_ml, (size_t)d.n_heads * c->max_splits * c->Bpad * 2 * sizeof(float));
   A((void**)&c->logits, (size_t)c->Bpad * c->Vpad * sizeof(float));
   A(&c->top2, (size_t)c->Bpad * (c->Vpad / 64 + 1) * 16);
   // (goose_harvest_topk takes up to GOOSE_MAX_B rows whatever the context's max_B)

@@ -63,10 +63,10 @@ struct goose_ctx {
 
   // device workspace
   int ld_xn, ld_o, ld_h;  // row lengths (elements) of the GEMM operands below: K * terms, padded in large contexts
-  void* xn;        // T [Bpad][ld_xn] normalised activations (GEMM operand)
-  float* part;     // f32 [max_ksplit][Bpad][part_ld]   GEMM outputs / split-K partials
+  void* xn;        // T [Bpad][ld_xn] normalised activations (GEMM operand; 16-bit models, as part, att_o and att_ml)
+  float* part;     // f32 [max_ksplit][Bpad][part_ld]   split-K partials
   size_t part_ld;  // row length of `part`
-  void* q;         // T [Bpad][Kq]   rotated queries
+  void* q;         // f32 [Bpad][Kq]  rotated queries (fp32 models)
   void* o;         // T [Bpad][ld_o] attention output (GEMM operand)
   void* h;         // T [Bpad][ld_h] SwiGLU output (GEMM operand)
   float* att_o;    // f32 [n_heads][max_splits][Bpad][head_dim]

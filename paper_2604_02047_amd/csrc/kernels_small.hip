@@ -1,5 +1,5 @@
 // Small kernels of the verification step: ancestor mask, embedding gather, residual +
-// RMSNorm, rotary embedding + KV-tail write, argmax, greedy walk, KV compaction.
+// RMSNorm, rotary angles, argmax, logit harvest, greedy walk, KV compaction.
 #include <limits.h>
 
 #include "fold.h"

@@ -109,3 +109,14 @@ def test_rows_beyond_the_range_of_a_sum(hidden):
     tokens[9] = 8
     assert torch.isnan(gm.verify_step_calls(tokens, tree.parent, tree.is_spine, want_logits=True, commit=False)["logits"][9]).all()
     gm.ctx.close()
+
+
+def test_workspace_of_an_fp32_context():
+    """No partial sums, operand rows or attention splits: those are of 16-bit models (250 MB at this size)."""
+    from paper_2604_02047_amd import ModelDesc
+    from paper_2604_02047_amd.binding import GooseContext
+    torch.zeros(1, device="cuda:0")
+    before = torch.cuda.mem_get_info()[0]
+    ctx = GooseContext(ModelDesc(1, 4096, 32, 128, 11008, 32000, 10000.0, 1e-5, "f32"), 128, 256)
+    assert before - torch.cuda.mem_get_info()[0] < 64 << 20
+    ctx.close()
