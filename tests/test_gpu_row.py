@@ -16,17 +16,23 @@ from test_gpu_parity import _compare_step, _gpu_prefill, tol_for
 pytestmark = pytest.mark.gpu
 
 
-# rows of up to 1024, 4096 and 8192 columns, no multiple of 128; head sizes, grouped queries and q/k norm; 1120 gate/up tiles (five
-# wavefronts); prefixes of one key split, two and three (merged in the O projection); both types and operand modes; K in one, two and four ranges
-@pytest.mark.parametrize("hidden,heads,head_dim,ffn,kv,norm,dtype,act_mode,P", [
-    (256, 4, 64, 688, 4, False, "bf16", 0, 40), (1032, 8, 128, 264, 2, True, "f16", 0, 600), (1024, 8, 64, 1000, 8, False, "bf16", 1, 300),
-    (4096, 32, 128, 512, 8, False, "bf16", 0, 300), (4360, 34, 128, 360, 34, False, "bf16", 0, 550), (256, 4, 64, 17920, 4, False, "f16", 1, 20),
-    (4360, 4, 64, 17920, 2, False, "bf16", 0, 300)])
-def test_one_row_alone_and_beside_another_request(hidden, heads, head_dim, ffn, kv, norm, dtype, act_mode, P):
+# rows of up to 1024, 4096 and 8192 columns, no multiple of 128; head sizes, grouped queries and q/k norm; prefixes of one key split, two and
+# three (merged in the O projection); both types and operand modes; K in one, two and four ranges; workgroups of five wavefronts (1120 gate/up
+# tiles; 516 of q|k|v and 137 of O in contexts of more than 64 rows), whose rows gather four slices, eight, or none; contexts of more than 64 rows,
+# where O has eight ranges; O and down in 17 ranges together, which is one too many for the row kernels
+@pytest.mark.parametrize("hidden,heads,head_dim,ffn,kv,norm,dtype,act_mode,P,max_rows,own", [
+    (256, 4, 64, 688, 4, False, "bf16", 0, 40, 64, True), (1032, 8, 128, 264, 2, True, "f16", 0, 600, 64, True),
+    (1024, 8, 64, 1000, 8, False, "bf16", 1, 300, 64, True), (4096, 32, 128, 512, 8, False, "bf16", 0, 300, 64, True),
+    (4360, 34, 128, 360, 34, False, "bf16", 0, 550, 64, True), (256, 4, 64, 17920, 4, False, "f16", 1, 20, 64, False),
+    (4360, 4, 64, 17920, 2, False, "bf16", 0, 300, 64, True), (2560, 4, 64, 17920, 4, False, "f16", 1, 20, 64, True),
+    (4360, 34, 128, 17920, 2, False, "f16", 0, 300, 64, True), (1024, 43, 128, 264, 43, False, "bf16", 0, 40, 128, True),
+    (4096, 32, 128, 512, 8, True, "bf16", 0, 300, 128, True), (4360, 40, 128, 17920, 2, False, "bf16", 1, 300, 128, True),
+    (4096, 32, 128, 512, 32, False, "f16", 0, 550, 512, True)])
+def test_one_row_alone_and_beside_another_request(hidden, heads, head_dim, ffn, kv, norm, dtype, act_mode, P, max_rows, own):
     shape = gi.ModelShape("row", 1 if ffn > 10000 else 2, hidden, heads, head_dim, ffn, 512, dtype=dtype, n_kv_heads=kv, qk_norm=norm)
     tm = torch_model(shape, seed=4, gain_jitter=0.1)
     gm = GooseModel(dataclasses.replace(ModelDesc.from_shape(shape), act_mode=act_mode), 64, 768, lambda l: tm["layers"][l], tm["embed"],
-                    tm["lm_head"], tm["final_norm"], max_rows=64)
+                    tm["lm_head"], tm["final_norm"], max_rows=max_rows)
     reqs = _requests(gm, shape, [1, 5], [P, 33], [P + 8, max(P, 33) + 8])
     alone = _alone(gm, reqs)
     _batched(gm, reqs)
@@ -35,6 +41,10 @@ def test_one_row_alone_and_beside_another_request(hidden, heads, head_dim, ffn, 
         k_b, v_b = _rows(gm, q["kcache"], q["vcache"], 0, a["P"])
         k_a, v_a = _rows(gm, a["k"], a["v"], 0, a["P"])
         assert torch.equal(k_b, k_a) and torch.equal(v_b, v_a)
+    # the row was verified by its own kernels: the only norm left a launch is the one behind the down projection
+    gm.ctx.goose_profile_enable(True)
+    _alone(gm, reqs[:1])
+    assert gm.ctx.goose_profile_read()["rmsnorm_residual"][1] == (shape.n_layers if own else 2 * shape.n_layers + 1)
     gm.ctx.close()
 
 
