@@ -166,8 +166,9 @@ __global__ __launch_bounds__(64 * NG * NQH, (paired(D, NG * NQH, TS) ? 2 : 1)) v
   constexpr bool HOLD = NIT <= 2 && !PAIR;
   constexpr int UG = HOLD ? NIT : (PAIR ? 1 : 2);
   static_assert(NIT % UG == 0, "item groups");
-  // Grouped queries with their narrow q|k|v product have four slices.  One at a time beyond the second: layers of Qwen3-8B, 33 nodes, 102.3 us
-  // (now 100.8), Llama-3-8B in two terms, 61 nodes, 144.8 (143.3); passes over 8 layers of 8 / 16 requests 1971 / 3072 (1952 / 3058).
+  // Grouped queries with their narrow q|k|v product have four slices.  With a branch around each load beyond the second slice (a trip each) layers of
+  // Qwen3-8B, 33 nodes, took 102.5 us (now 101.2), passes over 8 layers of 8 / 16 requests 1971 / 3072 (1952 / 3058); one slice at a time without
+  // branches costs single requests 0-0.3 %, 64 nodes over 5000 slots 1 % (120.2, now 118.3).
   constexpr int SG = PAIR ? 4 : 2, FG = PAIR || HOLD ? 2 : 1;
   // Where those loads need the registers of the first block's values, these are fetched behind them (they are used after scores and softmax).
   constexpr bool LATE_V = PAIR || (HOLD && NQH == 2 && D == 128);

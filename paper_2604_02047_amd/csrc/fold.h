@@ -1,4 +1,4 @@
-// Device arithmetic that exists in a kernel of its own and, for passes of a few rows, inside the projections: both must give the same bits.
+// Device arithmetic that exists in a kernel of its own and, for passes of one row, inside the projections: both must give the same bits.
 // Device code only (included by .hip files).
 #pragma once
 #include "goose_internal.h"

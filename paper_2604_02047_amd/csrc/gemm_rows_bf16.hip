@@ -443,11 +443,11 @@ int launch_rows_as(const RowsCall& g) {
 
 // Non-temporal weights leave the lines of A in the L2 alone, and the chunks of an item run side by side, so the later ones still find
 // the weights there.  The loads of 28672 x 4096 at 256 / 512 rows on their own (copies, no arithmetic) take 53.5 / 61.6 us, plain 56.3 / 67.0; the
-// product 65.8 / 102.7 (69.4 / 105.6), O, down and q|k|v 0.5-1.5 us less each; passes of 16 / 14 / 8 requests over 8 layers 2909 / 2720 / 1905 us
-// (2931 / 2738 / 1943), 7 in two terms 2404 (2426).  A short last chunk has little of A to copy and runs ahead of the others, whose weights
-// then have left the L2 again: below three quarters of the height they are loaded plainly.  Passes of 5 / 6 / 9 requests and of five of 48 nodes
-// 1704 / 1762 / 2135 / 2170 us, non-temporal throughout 1743 / 1780 / 2211 / 2191 (9 requests on another card 2064, 2197); 11 requests
-// (352 rows, the last chunk five sixths full) 2164 plain, 2156 non-temporal, 12 (full) 2300, 2246.
+// product 65.8 / 102.7 (69.4 / 105.6), O, down and q|k|v 0.5-1.5 us less each; passes of 16 / 14 / 12 / 8 / 7 requests over 8 layers, prefix 500, 2764 /
+// 2617 / 2318 / 1870 / 1806 us (plain throughout 2776 / 2632 / 2353 / 1894 / 1835), 7 in two terms 2404 (2426).  A short last chunk has little of A to copy and
+// runs ahead of the others, whose weights then have left the L2 again: below three quarters of the height they are loaded plainly.  Passes of 5 / 6 /
+// 9 / 10 requests and of five of 48 nodes 1682 / 1748 / 2122 / 2203 / 2169 us, non-temporal throughout 1750 / 1765 / 2291 / 2259 / 2225, plain
+// throughout 1706 / 1767 / 2124 / 2202 / 2172; 11 requests (352 rows, the last chunk five sixths full) 2263, 2261, 2282.
 template <int MT, int EPI, bool F16, int TERMS>
 int launch_rows(const RowsCall& g) {
   constexpr int H = 32 * MT;
