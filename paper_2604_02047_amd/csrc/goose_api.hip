@@ -355,6 +355,16 @@ int goose_embed(goose_ctx* c, const void* d_embed, const int32_t* d_tokens, int 
   return launch_embed(c->d.dtype, d_embed, d_tokens, B, c->d.hidden, c->d.vocab, d_x, as_stream(stream));
 }
 
+// attention launch shape: key splits per head (0: chosen there), key groups per workgroup
+static int attn_splits() {
+  static const int v = env_int("GOOSE_ATTN_SPLITS", 0);
+  return v;
+}
+static int attn_groups() {
+  static const int v = env_int("GOOSE_ATTN_NG", 4) == 2 ? 2 : 4;
+  return v;
+}
+
 static RopeArgs rope_args(const goose_ctx* c, const int32_t* pos, int rows) {
   return RopeArgs{pos, c->inv_freq, (float2*)c->rope_cs, rows, c->d.head_dim / 2};
 }
@@ -392,7 +402,7 @@ static int layer_row(goose_ctx* c, const char* w, float* d_x, const AttnSeg& seg
   int splits = 1;
   { PROF(PK_ATTN);
     rc = launch_attn_16(d.dtype, c->part, ks_qkv, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, &seg, 1,
-                        env_int("GOOSE_ATTN_SPLITS", 0), c->max_splits, 4, d.qk_norm ? w + c->pl.gq : nullptr,
+                        attn_splits(), c->max_splits, attn_groups(), d.qk_norm ? w + c->pl.gq : nullptr,
                         d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o, T, c->act_dtype,
                         c->flags, st, &splits); }
   if (rc) return rc;
@@ -466,18 +476,16 @@ static int layer_impl(goose_ctx* c, const char* w, float* d_x, void* d_kcache, v
   if (rc) return rc;
 
   const int T = c->terms;
-  static const int splits_env = env_int("GOOSE_ATTN_SPLITS", 0);
   int ks = cq.ks;
   { PROF(PK_GEMM_QKV);
     rc = launch_gemm_16(c->act_dtype, EPI_PARTIAL, c->xn, c->ld_xn, T, w + c->pl.wqkv, Nqkv, c->Kh, B, cq.nw, ks,
                         c->part, c->part_ld, pstride, c->out_scale, c->flags, st); }
   if (rc) return rc;
   // rotary embedding of q and k, KV rows of the tree into the cache, tree attention: one kernel
-  static const int ng_env = env_int("GOOSE_ATTN_NG", 4) == 2 ? 2 : 4;
   if (nseg == 0) { segs = &whole; nseg = 1; }
   { PROF(PK_ATTN);
     rc = launch_attn_16(d.dtype, c->part, ks, pstride, c->part_ld, c->rope_cs, d.n_heads, c->n_kv, d.head_dim, c->cap, segs,
-                          nseg, splits_env, c->max_splits, ng_env, d.qk_norm ? w + c->pl.gq : nullptr,
+                          nseg, attn_splits(), c->max_splits, attn_groups(), d.qk_norm ? w + c->pl.gq : nullptr,
                           d.qk_norm ? w + c->pl.gk : nullptr, d.rms_eps, c->att_o, c->att_ml, c->Bpad, c->o, c->ld_o,
                           T, c->act_dtype, c->flags, st); }
   if (rc) return rc;
