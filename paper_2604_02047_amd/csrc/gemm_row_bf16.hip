@@ -9,10 +9,10 @@
 //   ROW_MERGE  the attention's key splits combined   (k_attn_merge's)
 // It stays in LDS for the whole K range: the loop copies nothing and has no barrier.  A wavefront owns one column
 // tile and keeps two stages (64 inputs, 4 KiB each) of its weights in flight.  All that the row is made of is asked for before the first
-// weights (with none or four slices to add, as contexts of up to 64 rows have; other numbers of slices come four at a time and column group after column
-// group, and the weights behind the last): loads return in order, and the gains asked for after them cost 1.5 us a launch.  For the same reason a second
-// row, whose loads would follow, made a layer of two rows slower than its launches (94.1 against 92.7 us), and more weights in flight first make
-// everything wait (four stages of 128 inputs 91.9 us).
+// weights (with none or four slices to add, which is what contexts of up to 64 rows have at hidden sizes of 4096 and more; other numbers of slices come
+// four at a time and column group after column group, and the weights behind the last): loads return in order, and the gains asked for after them cost
+// 1.5 us a launch.  For the same reason a second row, whose loads would follow, made a layer of two rows slower than its launches (94.1 against
+// 92.7 us), and more weights in flight first make everything wait (four stages of 128 inputs 91.9 us).
 // Layers of one row against the launches that it replaces: 7B over 1024 slots 92.6 -> 88.3 us, over 16000 128.2 -> 123.7, 13B 124.6 -> 118.5, 33B
 // 209.2 -> 186.1, Qwen3-8B in two terms over 5000 101.0 -> 94.1.  In contexts for trees of 80 nodes (O in eight ranges at a hidden size of 4096), over 1024: 7B
 // 98.2 -> 92.9, Llama-3-8B 102.1 -> 96.3, Qwen3-8B 94.3 -> 88.4, 13B 136.6 -> 128.8, 33B 207.2 -> 199.2; of 256 rows 98.4 -> 93.5, 101.6 -> 95.7.
